@@ -262,3 +262,45 @@ def tolerance(case):
     if case["call"] not in ("gemv", "step"):
         return "exact"
     return {"rel": 1e-6, "max": 1e-5} if case["out"] == "f32" else {"rel": 4e-3, "max": 8e-3}
+
+
+def _quantised(w, bits, dist):
+    """(q - z, s) of fp32 weights, by the definition of the grid (fp32, true division, half to even), the difference as fp32."""
+    top = (1 << bits) - 1
+    lo, hi = w.min(), w.max()
+    unsigned = dist == "uniform"
+    s = (hi / torch.full_like(hi, top)) if unsigned else (hi - lo) / torch.full_like(hi, top)
+    z = torch.zeros_like(s) if unsigned else torch.round(-lo / s)
+    return torch.round(w / s).add_(z).clamp_(0, top).sub_(z), s
+
+
+def exact(case, seed):
+    """What run() returns, in 64 bits from the same weights: q and z are integers, s is the fp32 number that the grid has."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(int(seed))
+    call, out = case["call"], case["out"]
+    if call == "compress":
+        w = _weights(case["rows"] * case["cols"], case["dist"], False, gen)
+        return [None, None, None, float((w.max() - w.min()).item() / ((1 << case["bits"]) - 1)), None]
+    shapes = _shapes(case)
+    if out in ("u8", "u4") or call not in ("gemv", "step") and sum(r * c for r, c, _ in shapes) > 1 << 28:
+        return None                              # whole numbers, or too much to hold in 64 bits
+    held = []
+    for rows, cols, dist in shapes:
+        d, s = _quantised(_weights(rows * cols, dist, case["model"] == "smol" and dist != "uniform", gen), case["bits"], dist)
+        held.append((d.to(torch.bfloat16), s.double()))          # (integers of at most 256 in magnitude)
+    if call in ("gemv", "step"):
+        flat, ys = _views([r for r, _, _ in shapes], torch.float64, 16 * 8 // torch.empty(0, dtype=DTYPES[out]).element_size())
+        per = len(shapes) // case["layers"] if case["model"] else 1
+        groups = [(per * l + a, per * l + b) for l in range(case["layers"]) for a, b in GROUPS[case["model"]]] if case["model"] \
+            else [(i, i + 1) for i in range(len(shapes))]
+        for a, b in groups:
+            x = torch.randn(shapes[a][1], device=DEV, generator=gen).to(torch.bfloat16).double()
+            for i in range(a, b):
+                ys[i].copy_((held[i][0].view(shapes[i][0], shapes[i][1]).double() * x).sum(1) * held[i][1])
+        return flat
+    sizes = [r * c for r, c, _ in shapes]
+    flat, views = _views(sizes, torch.float64, 16 * 8 // torch.empty(0, dtype=DTYPES[out]).element_size())
+    for v, (d, s) in zip(views, held):
+        v.copy_(d.double() * s)
+    return flat
