@@ -195,6 +195,27 @@ def test_more_long_prefixes_than_the_second_level_holds():
         assert np.array_equal(_gpu_decode(enc, E.ENTRO_U8, batch=True), sym)
 
 
+@pytest.mark.parametrize("bits,deepest", [(8, 9), (8, 10), (8, 11), (8, 14), (8, 15), (8, 20), (8, 21), (4, 9), (4, 10), (4, 14), (4, 15)])
+def test_staircase_codes_around_the_widths_of_the_tables(bits, deepest):
+    # lengths 1, 2, ..., d, d with d at the widths of the table pieces (10 bits searched and copied, 14 indexed, 20 in
+    # the second level; 9 for the single codes of pair tables), decoded through every kind of table
+    ln = np.zeros(1 << bits, np.uint8)
+    ln[: deepest + 1] = list(range(1, deepest + 1)) + [deepest]
+    rng = np.random.default_rng(100 * bits + deepest)
+    cols, chunk = 512, 2048
+    sym = rng.integers(0, deepest + 1, 70 * cols).astype(np.uint8)
+    code = oracle.canonical_codes(ln)
+    stream, off = oracle.encode(sym, ln, code, chunk)
+    qp = B.QParams(np.float32(0.25), 7, bits, E.ENTRO_ASYMMETRIC)
+    enc = B.EncodedTensor(stream, off, sym.size, chunk, E.entro_codebook_from_lengths(ln, bits), qp, sym.size // cols, cols)
+    x = synth.make_x_bf16(9, deepest, cols)
+    y_ref, _ = oracle.gemv(sym, enc.rows, cols, 0.25, 7, x)
+    for batch in (False, True):
+        assert np.array_equal(_gpu_decode(enc, E.ENTRO_U8, batch), sym)
+        assert np.array_equal(_gpu_dequant(enc, E.ENTRO_F32, batch), oracle.dequant_f32(sym, 0.25, 7))
+        _assert_gemv_close(_gpu_gemv(enc, x, E.ENTRO_F32, batch), y_ref)
+
+
 @pytest.mark.parametrize("lengths", [
     list(range(1, 15)) + [15, 15],                 # the deepest complete code over 16 symbols
     [1, 3, 3, 4, 4, 5, 5, 6, 6, 7, 7, 8, 8, 8, 8, 0],   # complete over 15 symbols; codes up to 8 bits
