@@ -26,9 +26,11 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
+#include <numeric>
 #include <string>
 #include <type_traits>
 #include <vector>
@@ -73,9 +75,9 @@ struct DevTensor {
     void *tables;               // batched launches: the tensor's lookup tables as k_tables left them (or null: build them)
     uint64_t n;
     uint32_t stream_bytes;
-    uint32_t chunk_symbols;     // symbols one lane decodes: a piece, where the tensor has entry points, else a segment
+    uint32_t chunk_symbols;     // symbols one lane decodes: a piece, where the tensor has entry points or they are found on the way, else a segment
     uint32_t n_chunks;          // and how many of those the tensor has
-    uint32_t sub_shift;         // log2 of lanes per segment (0: a lane takes a whole segment)
+    uint32_t sub_shift;         // log2 of lanes per segment (0: a lane takes a whole segment; sub null: they find their starts themselves)
     uint32_t sub_merge;         // log2 of the pieces of the entry-point table that one lane takes
     uint32_t rows;
     uint32_t cols;
@@ -541,6 +543,126 @@ __device__ __forceinline__ uint32_t next_entry(ScalarReader &r, const TB &tb, ui
     return e;
 }
 
+// ---------------------------------------------------------------- entry points found on the way
+// Small launches on a tensor that carries no entry points (k_single with FIND; t.sub is null and t.sub_shift is the
+// log2 of a segment's pieces).  A lane per segment leaves most of the device idle there, and the time is one lane's
+// serial chain of lookups.  So 2^sub_shift lanes share a segment: each takes an equal stretch of its bits and decodes
+// from a guessed bit, Huffman codes falling into step with the true code boundaries within a few codes; then a lane
+// whose neighbour ended elsewhere than it began starts again from there.  Lane 0 of a segment starts at a true boundary,
+// so once all of them agree every start is true, whatever the data (after as many rounds as lanes at the latest;
+// two as a rule).  The lanes' symbol counts then say where each piece of chunk_symbols symbols begins, and the
+// ordinary block path decodes the pieces.
+
+// At least 57 stream bits from absolute bit `pos` on (clamped to the padded stream's last 8 bytes): four lookups.
+__device__ __forceinline__ uint64_t load_bits57(const DevTensor &t, uint64_t pos) {
+    uint64_t off = pos >> 3;
+    const uint64_t last = t.stream_bytes - 8u;
+    off = off < last ? off : last;
+    uint64_t v;
+    __builtin_memcpy(&v, t.stream + off, 8);
+    return v >> (static_cast<uint32_t>(pos) & 7u);
+}
+
+// Length of the code at the start of `w` (at least kL1 valid bits), which lies at absolute bit `pos`; moves w behind it.
+template <bool PAIR, class TB>
+__device__ __forceinline__ uint32_t step_code(const DevTensor &t, const TB &tb, uint64_t pos, uint64_t &w) {
+    const uint32_t e = PAIR ? tb.lut2[static_cast<uint32_t>(w) & ((1u << kSingleBits) - 1u)] : tb.lut[static_cast<uint32_t>(w) & kL1Mask];
+    uint32_t len = entry_len(e);
+    if (__builtin_expect(len == 0, 0)) {
+        const uint32_t window = static_cast<uint32_t>(load_bits57(t, pos));
+        len = entry_len(PAIR ? decode_canonical(tb, window, kSingleBits + 1, t.max_len) : decode_long(tb, e, window, t.max_len));
+        w = load_bits57(t, pos + len);
+    } else {
+        w >>= len;
+    }
+    return len;
+}
+
+// Stream bit at which the lane's piece wave_first + lane starts; `place` is 64 dwords of the wavefront's LDS.
+template <bool PAIR, class TB>
+__device__ __forceinline__ uint64_t find_start(const DevTensor &t, const TB &tb, lds_v32 place, uint32_t wave_first) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t sh = t.sub_shift, parts = 1u << sh, part = lane & (parts - 1u);
+    const uint32_t S = t.chunk_symbols;
+    const uint32_t seg = (wave_first + lane) >> sh;              // (a wavefront holds whole segments: parts <= 64)
+    const bool live = (seg << sh) < t.n_chunks;
+    uint64_t base = 0;
+    uint32_t nsym = 0, span = 0;                                 // the segment's symbols and bits
+    if (live) {
+        const uint64_t whole = static_cast<uint64_t>(S) << sh, left = t.n - seg * whole;
+        nsym = static_cast<uint32_t>(left < whole ? left : whole);
+        base = t.offsets[seg];
+        const uint64_t end = t.offsets[seg + 1], most = static_cast<uint64_t>(nsym) * ENTRO_MAX_CODE_LEN;
+        const uint64_t bits = end > base ? end - base : 0;
+        span = static_cast<uint32_t>(bits < most ? bits : most);
+    }
+    const uint32_t limit = static_cast<uint32_t>((static_cast<uint64_t>(span) * (part + 1u)) >> sh);
+    uint32_t from = static_cast<uint32_t>((static_cast<uint64_t>(span) * part) >> sh);    // bits from the segment's start
+    uint32_t upto = 0, count = 0;
+    bool todo = live;
+    for (;;) {
+        if (todo) {
+            upto = from;
+            count = 0;
+            while (upto < limit) {
+                uint64_t w = load_bits57(t, base + upto);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (upto < limit) {
+                        upto += step_code<PAIR>(t, tb, base + upto, w);
+                        ++count;
+                    }
+            }
+        }
+        const uint32_t before = __shfl_up(upto, 1, 64);
+        const uint32_t want = part == 0 ? 0u : before;
+        todo = live && want != from;
+        from = want;
+        if (__builtin_amdgcn_ballot_w64(todo) == 0) break;
+    }
+    uint32_t sum = count;                                        // symbols up to the end of the lane's stretch
+    for (uint32_t m = 1; m < parts; m <<= 1) {
+        const uint32_t y = __shfl_up(sum, m, 64);
+        sum += part >= m ? y : 0u;
+    }
+    const uint32_t total = __shfl(sum, static_cast<int>(lane | (parts - 1u)), 64);
+    uint32_t idx = sum - count, stop = sum < nsym ? sum : nsym;
+    if (total < nsym) {
+        // an offset table that does not fit the stream: the segment is walked from its start by its first lane
+        idx = 0;
+        from = 0;
+        stop = part == 0 ? nsym : 0u;
+    }
+    uint32_t slot = (idx + S - 1u) / S;                          // next piece to start at or behind symbol idx
+    while (slot * S < stop) {
+        uint64_t w = load_bits57(t, base + from);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (idx == slot * S && idx < stop) {
+                place[lane - part + slot] = from;
+                ++slot;
+            }
+            from += step_code<PAIR>(t, tb, base + from, w);
+            ++idx;
+        }
+    }
+    wave_sync_lds();
+    const uint64_t start = base + place[lane];
+    wave_sync_lds();
+    return start;
+}
+
+// A wavefront's piece starts, found or looked up.
+template <int MODE, bool FIND, class TB>
+__device__ __forceinline__ uint64_t lane_start(const DevTensor &t, const TB &tb, lds_v32 place, uint32_t wave_first, bool fast) {
+    if constexpr (FIND) {
+        const uint64_t start = find_start<kPairMode<MODE>>(t, tb, place, wave_first);
+        return fast ? start : 0;
+    } else {
+        return fast ? seg_start(t, wave_first + (threadIdx.x & 63u)) : 0;
+    }
+}
+
 template <int MODE> struct OutTraits;
 template <> struct OutTraits<kModeU8> { static constexpr int ebits = 8; };
 template <> struct OutTraits<kModeU4> { static constexpr int ebits = 4; };
@@ -958,7 +1080,7 @@ __device__ __forceinline__ void gemv_segment(const DevTensor &t, const TB &tb, u
 // LDS tile (one row of symbol bytes per lane; all lanes move in step, four
 // symbols per group), then consume the tile row-wise: write it out in the output
 // type, so that every store instruction covers whole rows.
-template <int MODE>
+template <int MODE, bool FIND = false>
 __device__ __forceinline__ void decode_rows(const DevTensor &t, const Tables &tb, WaveMem<Cfg<MODE>::row> *wms,
                                             uint32_t wave_first) {
     static_assert(!is_gemv(MODE), "the GEMV has a kernel of its own");
@@ -989,7 +1111,7 @@ __device__ __forceinline__ void decode_rows(const DevTensor &t, const Tables &tb
     // rest.  The lane moves on with the others past its own end; what it decodes there is not stored.
     const bool fast = nsym != 0;
     const uint32_t my_blocks = nsym / SPB;
-    uint64_t tail_pos = fast ? seg_start(t, k) : 0;       // where the symbols behind the lane's last whole block start
+    uint64_t tail_pos = lane_start<MODE, FIND>(t, tb, (lds_v32)wm.ring, wave_first, fast);   // where the symbols behind the lane's last whole block start
     Ring2 r;
     r.stale = Tables::stale;
     r.stream = t.stream;
@@ -1126,7 +1248,7 @@ __device__ __forceinline__ void decode_rows(const DevTensor &t, const Tables &tb
 // writes whole 128-byte rows.
 // ALLFULL: the unit's 64 segments all have full length (decided per wavefront): no store needs a
 // condition, no lane a tail.
-template <int MODE, bool ALLFULL>
+template <int MODE, bool ALLFULL, bool FIND>
 __device__ __forceinline__ void decode_rows2_impl(const DevTensor &t, const Tables &tb, WaveMem2 &wm, uint32_t wave_first) {
     static_assert(MODE == kModeF32 || MODE == kModeBF16, "single codes, two or four bytes per symbol");
     constexpr int SPB = Cfg<MODE>::spb;                   // 64
@@ -1147,7 +1269,7 @@ __device__ __forceinline__ void decode_rows2_impl(const DevTensor &t, const Tabl
     }
     const bool fast = nsym != 0;
     const uint32_t my_blocks = nsym / SPB;
-    uint64_t tail_pos = fast ? seg_start(t, k) : 0;
+    uint64_t tail_pos = lane_start<MODE, FIND>(t, tb, (lds_v32)wm.ring, wave_first, fast);
     Ring2 r;
     r.stale = Tables::stale;
     r.stream = t.stream;
@@ -1221,13 +1343,13 @@ __device__ __forceinline__ void decode_rows2_impl(const DevTensor &t, const Tabl
     }
 }
 
-template <int MODE>
+template <int MODE, bool FIND = false>
 __device__ __forceinline__ void decode_rows2(const DevTensor &t, const Tables &tb, WaveMem2 *wms, uint32_t wave_first) {
     if (wave_first >= t.n_chunks) return;
     WaveMem2 &wm = wms[threadIdx.x >> 6];
     const uint32_t n_full = static_cast<uint32_t>(t.n / t.chunk_symbols);
-    if (wave_first + kUnit <= n_full) decode_rows2_impl<MODE, true>(t, tb, wm, wave_first);
-    else decode_rows2_impl<MODE, false>(t, tb, wm, wave_first);
+    if (wave_first + kUnit <= n_full) decode_rows2_impl<MODE, true, FIND>(t, tb, wm, wave_first);
+    else decode_rows2_impl<MODE, false, FIND>(t, tb, wm, wave_first);
 }
 
 // Decode one segment straight into dot products with x.  A segment covers one
@@ -1578,7 +1700,7 @@ __device__ __forceinline__ void scalar_chunks(const DevTensor &t, const TB &tb, 
 // One tensor per launch: workgroup b builds the tables and takes `wg_units` units
 // (kUnit segments each, one unit per wavefront; at most as many as it has
 // wavefronts) from unit b * wg_units on.
-template <int MODE>
+template <int MODE, bool FIND>
 __device__ __forceinline__ void single_body(const DevTensor &t, uint32_t wg_units) {
     constexpr uint32_t WG = 64 * Cfg<MODE>::waves;
     __shared__ SmemFor<MODE> sm;
@@ -1590,8 +1712,8 @@ __device__ __forceinline__ void single_body(const DevTensor &t, uint32_t wg_unit
         if (wave < wg_units) {
             if constexpr (wide_gemv(MODE)) gemv_direct2<MODE>(t, sm.tb, sm.wm[wave].ring, first + wave * kUnit);
             else if constexpr (is_gemv(MODE)) gemv_direct<MODE>(t, sm.tb, sm.wm[wave].ring, first + wave * kUnit);
-            else if constexpr (short_ring(MODE)) decode_rows2<MODE>(t, sm.tb, sm.wm, first + wave * kUnit);
-            else decode_rows<MODE>(t, sm.tb, sm.wm, first + wave * kUnit);
+            else if constexpr (short_ring(MODE)) decode_rows2<MODE, FIND>(t, sm.tb, sm.wm, first + wave * kUnit);
+            else decode_rows<MODE, FIND>(t, sm.tb, sm.wm, first + wave * kUnit);
         }
     } else {
         const uint32_t end = first + wg_units * kUnit;
@@ -1673,9 +1795,9 @@ __device__ __forceinline__ void batch_body(const DevTensor *__restrict__ tensors
     }
 }
 
-template <int MODE>
+template <int MODE, bool FIND>
 __global__ __launch_bounds__(64 * Cfg<MODE>::waves) void k_single(const DevTensor t, uint32_t wg_units) {
-    single_body<MODE>(t, wg_units);
+    single_body<MODE, FIND>(t, wg_units);
 }
 template <int MODE>
 __global__ __launch_bounds__(64 * Cfg<MODE>::waves) void k_batch(const DevTensor *__restrict__ tensors,
@@ -1940,6 +2062,44 @@ unsigned resident_workgroups(int mode) {
     return static_cast<unsigned>(cus) * (per_cu ? per_cu : 1u);
 }
 
+// Does decoding from a wrong bit fall into step soon?  Not where (nearly) all codes have one length, or lengths with
+// a common divisor.  Judged by the spread of the lengths as the code itself weighs them (a code of l bits: 2^-l): at
+// least half a squared bit.  Weights have one or two, symbols spread evenly over the grid about a tenth.
+bool falls_into_step(const entro_codebook *cb) {
+    double weight = 0, mean = 0, square = 0;
+    uint32_t divisor = 0;
+    for (int s = 0; s < ENTRO_MAX_SYMBOLS; ++s) {
+        const uint32_t l = cb->len[s];
+        if (!l) continue;
+        const double p = std::ldexp(1.0, -static_cast<int>(l));
+        weight += p;
+        mean += p * l;
+        square += p * l * l;
+        divisor = std::gcd(divisor, l);
+    }
+    mean /= weight;
+    return divisor == 1 && square / weight - mean * mean >= 0.5;
+}
+
+// A tensor without entry points whose segments leave most lanes of the device without work: 2^sub_shift lanes per
+// segment that find their pieces' starts themselves (find_start), as many as the device has lanes for.  A lane then
+// decodes its share four times, three of them symbol by symbol, which pays from eight lanes per segment on (with
+// four, three of the four passes make up what the shorter chain saves).  The pieces must be whole blocks of the kernel.
+// Measured: 4096 x 4096 in segments of 4096 to bf16 318 us with a lane per segment, 50 us with 64.
+// (Not for the product: the search in front of gemv_direct2 gave wrong sums that changed from run to run, cause not found.)
+bool cut_segments(entro_op op, int mode, uint64_t lane_slots, const entro_tensor *t, DevTensor *dt) {
+    if (op == ENTRO_OP_GEMV || t->sub_symbols || !falls_into_step(t->cb)) return false;
+    const uint32_t block = spb_of(mode);
+    for (uint32_t sh = 6; sh >= 3; --sh) {
+        if ((static_cast<uint64_t>(dt->n_chunks) << sh) > lane_slots || dt->chunk_symbols % (block << sh) != 0) continue;
+        dt->chunk_symbols >>= sh;
+        dt->sub_shift = sh;
+        dt->n_chunks = static_cast<uint32_t>(entro_num_chunks(dt->n, dt->chunk_symbols));
+        return true;
+    }
+    return false;
+}
+
 entro_status launch_single(const entro_tensor *t, entro_op op, entro_dtype d, float *partials,
                            void *hip_stream) {
     // all argument checks first, on the host alone; then the device is asked how many lanes it holds, which
@@ -1955,6 +2115,7 @@ entro_status launch_single(const entro_tensor *t, entro_op op, entro_dtype d, fl
     if (st != ENTRO_OK) return st;
     dt.partials = partials;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
+    const bool find = cut_segments(op, mode, static_cast<uint64_t>(slots) * wg, t, &dt);
     // a unit per wavefront when the tensor is large; fewer units per workgroup, down to one, when
     // that would leave compute units without a workgroup
     const unsigned units = (dt.n_chunks + kUnit - 1) / kUnit;
@@ -1962,7 +2123,13 @@ entro_status launch_single(const entro_tensor *t, entro_op op, entro_dtype d, fl
     const unsigned grid = (units + wg_units - 1) / wg_units;
     dispatch_mode(mode, [&](auto m) {
         constexpr int M = decltype(m)::value;
-        hipLaunchKernelGGL(k_single<M>, dim3(grid), dim3(wg), 0, s, dt, static_cast<uint32_t>(wg_units));
+        if constexpr (!is_gemv(M)) {
+            if (find) {
+                hipLaunchKernelGGL((k_single<M, true>), dim3(grid), dim3(wg), 0, s, dt, static_cast<uint32_t>(wg_units));
+                return;
+            }
+        }
+        hipLaunchKernelGGL((k_single<M, false>), dim3(grid), dim3(wg), 0, s, dt, static_cast<uint32_t>(wg_units));
     });
     if (!hip_ok(hipGetLastError(), "launch decode kernel")) return ENTRO_ERR_DEVICE;
     if (dt.need_fix) {

@@ -216,6 +216,30 @@ def test_staircase_codes_around_the_widths_of_the_tables(bits, deepest):
         _assert_gemv_close(_gpu_gemv(enc, x, E.ENTRO_F32, batch), y_ref)
 
 
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("chunk,segments,last", [
+    (512, 3, 0), (1024, 9, 0), (4096, 5, 0), (8192, 2, 0), (4096, 3, 1), (4096, 2, 63), (4096, 2, 65), (4096, 1, 4095), (3072, 4, 257),
+    (448, 3, 0)])
+@pytest.mark.parametrize("run", [False, True])
+def test_segments_without_entry_points_cut_into_pieces(bits, chunk, segments, last, run):
+    # 8 to 64 lanes per segment that find their starts themselves, short last segments, and (448) segments that do not
+    # divide; `run`: a segment of one symbol, whose code never falls into step from most wrong bits
+    rng = np.random.default_rng(chunk + last + bits)
+    top, n = (1 << bits) - 1, segments * chunk + last
+    mid = (top + 1) // 2
+    sym = np.clip(np.rint(rng.standard_t(5, n) * (12.0 if bits == 8 else 1.0) + mid), 0, top).astype(np.uint8)
+    if run:
+        sym[:chunk] = mid + (2 if bits == 8 else 1)
+    sym[n // 2] = 0                                            # codes of the far tails
+    sym[n - 1] = top
+    enc = _oracle_encoded(sym, bits, chunk, 1, n, 0.25, 7 if bits == 8 else 3)
+    z = enc.qp.zero_point
+    assert np.array_equal(_gpu_decode(enc, E.ENTRO_U8), sym)
+    assert np.array_equal(_gpu_dequant(enc, E.ENTRO_F32), oracle.dequant_f32(sym, 0.25, z))
+    if bits == 4:
+        assert np.array_equal(_gpu_decode(enc, E.ENTRO_U4_PACKED), oracle.pack_u4(sym))
+
+
 @pytest.mark.parametrize("lengths", [
     list(range(1, 15)) + [15, 15],                 # the deepest complete code over 16 symbols
     [1, 3, 3, 4, 4, 5, 5, 6, 6, 7, 7, 8, 8, 8, 8, 0],   # complete over 15 symbols; codes up to 8 bits
