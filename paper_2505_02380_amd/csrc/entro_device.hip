@@ -2085,12 +2085,15 @@ bool falls_into_step(const entro_codebook *cb) {
 // segment that find their pieces' starts themselves (find_start), as many as the device has lanes for.  A lane then
 // decodes its share four times, three of them symbol by symbol, which pays from eight lanes per segment on (with
 // four, three of the four passes make up what the shorter chain saves).  The pieces must be whole blocks of the kernel.
-// Measured: 4096 x 4096 in segments of 4096 to bf16 318 us with a lane per segment, 50 us with 64.
+// Measured: 4096 x 4096 in segments of 4096 to bf16 318 us with a lane per segment, 50 us with 64; 8192 x 4096 in
+// segments of 1024, which get eight, 102 -> 90 us.  4-bit symbols are decoded two a lookup but searched one at a
+// time: sixteen lanes are the least there (segments of 2048 115 -> 73 us; in segments of 1024 eight take 66.7, one 45.7).
 // (Not for the product: the search in front of gemv_direct2 gave wrong sums that changed from run to run, cause not found.)
 bool cut_segments(entro_op op, int mode, uint64_t lane_slots, const entro_tensor *t, DevTensor *dt) {
     if (op == ENTRO_OP_GEMV || t->sub_symbols || !falls_into_step(t->cb)) return false;
     const uint32_t block = spb_of(mode);
-    for (uint32_t sh = 6; sh >= 3; --sh) {
+    const uint32_t least = dt->bits == 4 ? 4u : 3u;
+    for (uint32_t sh = 6; sh >= least; --sh) {
         if ((static_cast<uint64_t>(dt->n_chunks) << sh) > lane_slots || dt->chunk_symbols % (block << sh) != 0) continue;
         dt->chunk_symbols >>= sh;
         dt->sub_shift = sh;
