@@ -72,7 +72,7 @@ struct DevTensor {
     const uint16_t *x;
     float *partials;            // GEMV: head/tail partial sums, 2 per segment
     const uint16_t *sub;        // entry points inside the segments: stream bits of every piece (or null)
-    void *tables;               // batched launches: the tensor's lookup tables as k_tables left them (or null: build them)
+    void *tables;               // batched launches: the tensor's lookup tables as k_tables left them
     uint64_t n;
     uint32_t stream_bytes;
     uint32_t chunk_symbols;     // symbols one lane decodes: a piece, where the tensor has entry points or they are found on the way, else a segment
@@ -1725,8 +1725,7 @@ __device__ __forceinline__ void single_body(const DevTensor &t, uint32_t wg_unit
 // what a wavefront decodes at a time.  The work list has one item per
 // `item_units` units of a tensor (fewer at the tensor's end), in tensor order;
 // workgroup b of G takes the items [b * n / G, (b + 1) * n / G): a few stretches
-// of one tensor each.  Per stretch it loads the tensor's tables (or builds them, if the
-// launch was not prepared with them), then its wavefronts draw units from a counter in
+// of one tensor each.  Per stretch it loads the tensor's tables, then its wavefronts draw units from a counter in
 // LDS until the stretch is used up.  The wavefronts of a workgroup do not run equally
 // fast (fourteen of them share four SIMDs unevenly; lanes meet long codes at different
 // times), so a fixed split would leave the faster ones waiting.
@@ -1762,15 +1761,14 @@ __device__ __forceinline__ void batch_body(const DevTensor *__restrict__ tensors
             n_all = n_coarse + static_cast<uint32_t>((fine_end - fine_first + kUnit - 1) / kUnit);
         }
         __syncthreads();                                     // nobody reads the previous tables or the counter any more
-        if (t.tables) {
-            // built once when the launch was prepared: 16 bytes per lane and step from memory into LDS
-            const u32x4 *src = static_cast<const u32x4 *>(t.tables);
-            u32x4 *dst = reinterpret_cast<u32x4 *>(&sm.tb);
-            for (uint32_t j = threadIdx.x; j < sizeof(sm.tb) / 16u; j += WG) dst[j] = src[j];
-            __syncthreads();
-        } else {
-            build_tables<WG, kPairMode<MODE>>(t, sm.tb, reinterpret_cast<uint32_t *>(sm.wm));
-        }
+        // Built once when the launch was prepared: 16 bytes per lane and step from memory into LDS.  (Every launch that
+        // comes here has been prepared with tables.  A build in an else branch, never taken, decided the register
+        // allocation: 20 spilled vector registers in the 8-bit product against 6 without, 3 and 4 against none
+        // for packed nibbles and fp32; the step over 32 layers of 8-bit products 6510 -> 6232 us.)
+        const u32x4 *src = static_cast<const u32x4 *>(t.tables);
+        u32x4 *dst = reinterpret_cast<u32x4 *>(&sm.tb);
+        for (uint32_t j = threadIdx.x; j < sizeof(sm.tb) / 16u; j += WG) dst[j] = src[j];
+        __syncthreads();
         if (rows_fit<MODE>(t)) {
             if (threadIdx.x == 0) next_unit = 0;
             __syncthreads();

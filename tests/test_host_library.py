@@ -5,6 +5,8 @@ total cost, Kraft equality and canonical form -- not the length vector."""
 import ctypes as C
 import os
 import re
+import struct
+import subprocess
 from fractions import Fraction
 
 import numpy as np
@@ -27,6 +29,29 @@ def test_library_loads_and_exports_every_declared_symbol():
     for name in sorted(declared):
         assert hasattr(L, name), f"libentro.so does not export {name}"
     assert set(B.EXPORTED) == declared
+
+
+def test_prepared_launches_kernels_keep_their_registers(tmp_path):
+    """The kernels of prepared and batched launches only load lookup tables.  A table build compiled into them costs the
+    decode loops registers although no launch reaches it (3 and 4 spilled vector registers for packed nibbles and
+    fp32, 20 for the 8-bit products, as the code objects in the built library say)."""
+    llvm = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-readelf")
+    data = open(E.library_path(), "rb").read()
+    notes = ""
+    for m in re.finditer(b"__CLANG_OFFLOAD_BUNDLE__", data):                # a bundle per device source: host and gfx950 images
+        at, (count,) = m.start() + 32, struct.unpack_from("<Q", data, m.start() + 24)
+        for _ in range(count):
+            offset, size, name_len = struct.unpack_from("<QQQ", data, at)
+            if data[at + 24: at + 24 + name_len].endswith(b"gfx950"):
+                elf = tmp_path / f"{m.start()}.elf"
+                elf.write_bytes(data[m.start() + offset: m.start() + offset + size])
+                notes += subprocess.run([llvm, "--notes", str(elf)], check=True, capture_output=True, text=True).stdout
+            at += 24 + name_len
+    spills = {int(mode): int(n) for mode, n in re.findall(r"\.symbol:\s+\S*k_batchILi(\d+)E.*?\.vgpr_spill_count:\s+(\d+)", notes, re.S)}
+    assert sorted(spills) == list(range(13))
+    wide = (11, 12)                                          # the 8-bit products hold 64 registers of x and stream ahead
+    assert all(n == 0 for mode, n in spills.items() if mode not in wide), spills
+    assert all(spills[mode] <= 8 for mode in wide), spills
 
 
 def test_comparison_kernels_live_in_their_own_library():
