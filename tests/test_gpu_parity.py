@@ -780,3 +780,39 @@ def test_plain_uint8_gemv_comparison_kernel_matches_the_oracle():
         got = y.cpu().numpy()
         assert np.all(got[rows:] == 9.0)
         _assert_gemv_close(got[:rows].astype(np.float64), y_ref)
+
+
+@pytest.mark.parametrize("y_type", [E.ENTRO_F32, E.ENTRO_BF16])
+def test_few_units_per_workgroup_run_side_by_side(y_type):
+    """A prepared launch with a unit for each SIMD of every compute unit takes as long as one with a single unit per
+    compute unit, whatever the order in which the wavefronts of a workgroup get there: 1.05 times as long (1.21 where
+    two wavefronts of a SIMD may take units while another SIMD has none)."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    cols, sub, us = 8192, 512, []
+    for units in (1, 4):
+        rows = units * cus * 64 * sub // cols
+        rng = np.random.default_rng(units)
+        sym = np.clip(np.rint(rng.laplace(size=rows * cols) * 0.47 + 7), 0, 15).astype(np.uint8)
+        cb = E.entro_build_codebook(sym, 4)
+        stream, off = E.entro_encode(sym, cb, 16 * sub)
+        enc = B.EncodedTensor(stream, off, sym.size, 16 * sub, cb, B.QParams(np.float32(0.25), 7, 4, E.ENTRO_ASYMMETRIC), rows, cols)
+        enc.sub_symbols, enc.sub_bits = sub, E.entro_sub_index(sym, cb, 16 * sub, sub)
+        dt = E.to_device(enc, DEV)
+        x = torch.from_numpy(synth.make_x_bf16(9, units, cols).view(np.int16)).to(DEV).view(torch.bfloat16)
+        y = torch.zeros(rows, dtype=torch.float32 if y_type == E.ENTRO_F32 else torch.bfloat16, device=DEV)
+        ts = [dt.ctensor(y, x)]
+        ws = torch.zeros(E.entro_workspace_bytes(ts, E.ENTRO_OP_GEMV), dtype=torch.uint8, device=DEV)
+        plan = E.entro_plan_init(ts, E.ENTRO_OP_GEMV, y_type, ws)
+        times = []
+        for _ in range(16):
+            a, b = torch.cuda.Event(True), torch.cuda.Event(True)
+            a.record()
+            for _ in range(20):
+                E.entro_plan_run(plan)
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b) * 50)
+        us.append(float(np.median(times)))
+        y_ref, _ = oracle.gemv(sym, rows, cols, 0.25, 7, synth.make_x_bf16(9, units, cols))
+        _assert_gemv_close(y.float().cpu().numpy().astype(np.float64), y_ref, 1e-3 if y_type == E.ENTRO_F32 else 5e-3)
+    assert us[1] <= 1.13 * us[0], us
