@@ -547,11 +547,22 @@ __device__ __forceinline__ uint32_t next_entry(ScalarReader &r, const TB &tb, ui
 // Small launches on a tensor that carries no entry points (k_single with FIND; t.sub is null and t.sub_shift is the
 // log2 of a segment's pieces).  A lane per segment leaves most of the device idle there, and the time is one lane's
 // serial chain of lookups.  So 2^sub_shift lanes share a segment: each takes an equal stretch of its bits and decodes
-// from a guessed bit, Huffman codes falling into step with the true code boundaries within a few codes; then a lane
-// whose neighbour ended elsewhere than it began starts again from there.  Lane 0 of a segment starts at a true boundary,
-// so once all of them agree every start is true, whatever the data (after as many rounds as lanes at the latest;
-// two as a rule).  The lanes' symbol counts then say where each piece of chunk_symbols symbols begins, and the
-// ordinary block path decodes the pieces.
+// from a guessed bit, Huffman codes falling into step with the true code boundaries within a few codes.  Then a lane
+// whose neighbour ended elsewhere than it began goes again from there, up to the first code boundary that it met the
+// first time; from there on nothing changes but the count of its codes.  Lane 0 of a segment starts at a true
+// boundary, so once all of them agree every start is true, whatever the data.  The lanes' symbol counts then say where
+// each piece of chunk_symbols symbols begins, and the ordinary block path decodes the pieces.
+// Data that does not fall into step (a run of one symbol inside a segment), data whose bits are spread too unevenly
+// and offset tables that do not fit the stream show by the number of codes that they take: the wavefront then gives the
+// search up, and the block path decodes its segments with one lane each, as it does without the search.
+constexpr uint32_t kMarkBits = 256;      // stream bits from a lane's guess on in which its first pass marks the codes' starts
+                                         // (of 211 000 lanes on weights 14 met one only behind 128 bits, none behind 192)
+
+// What a wavefront of the decode kernels works on: lane l takes the symbols [(first + l) * symbols, + symbols) of the
+// tensor, as long as first + l < end.
+struct Unit {
+    uint32_t first, end, symbols;
+};
 
 // At least 57 stream bits from absolute bit `pos` on (clamped to the padded stream's last 8 bytes): four lookups.
 __device__ __forceinline__ uint64_t load_bits57(const DevTensor &t, uint64_t pos) {
@@ -578,14 +589,15 @@ __device__ __forceinline__ uint32_t step_code(const DevTensor &t, const TB &tb, 
     return len;
 }
 
-// Stream bit at which the lane's piece wave_first + lane starts; `place` is 64 dwords of the wavefront's LDS.
+// Stream bit at which the lane's piece of the unit starts (0: the lane has none).  Where the search is given up the unit
+// becomes the same stretch of the tensor with a lane per segment.  `ring` is the wavefront's ring memory, not in use yet.
 template <bool PAIR, class TB>
-__device__ __forceinline__ uint64_t find_start(const DevTensor &t, const TB &tb, lds_v32 place, uint32_t wave_first) {
+__device__ __forceinline__ uint64_t find_start(const DevTensor &t, const TB &tb, lds_v32 ring, Unit &u) {
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t sh = t.sub_shift, parts = 1u << sh, part = lane & (parts - 1u);
-    const uint32_t S = t.chunk_symbols;
-    const uint32_t seg = (wave_first + lane) >> sh;              // (a wavefront holds whole segments: parts <= 64)
-    const bool live = (seg << sh) < t.n_chunks;
+    const uint32_t S = u.symbols;
+    const uint32_t seg = (u.first + lane) >> sh;                 // (a wavefront holds whole segments: parts <= 64)
+    const bool live = (seg << sh) < u.end;
     uint64_t base = 0;
     uint32_t nsym = 0, span = 0;                                 // the segment's symbols and bits
     if (live) {
@@ -596,29 +608,75 @@ __device__ __forceinline__ uint64_t find_start(const DevTensor &t, const TB &tb,
         const uint64_t bits = end > base ? end - base : 0;
         span = static_cast<uint32_t>(bits < most ? bits : most);
     }
+    // the lane's stretch, in bits from the segment's start
+    const uint32_t guess = static_cast<uint32_t>((static_cast<uint64_t>(span) * part) >> sh);
     const uint32_t limit = static_cast<uint32_t>((static_cast<uint64_t>(span) * (part + 1u)) >> sh);
-    uint32_t from = static_cast<uint32_t>((static_cast<uint64_t>(span) * part) >> sh);    // bits from the segment's start
-    uint32_t upto = 0, count = 0;
-    bool todo = live;
-    for (;;) {
-        if (todo) {
-            upto = from;
-            count = 0;
-            while (upto < limit) {
-                uint64_t w = load_bits57(t, base + upto);
+    // bit b of dword d: a code of the first pass starts at guess + 32 * d + b
+    const lds_v32 marks = ring + 64 + lane;
+    auto mark_at = [&](uint32_t rel) __attribute__((always_inline)) { return (uint32_t __attribute__((address_space(3))) *)(marks + (rel >> 5) * 64u); };
+#pragma unroll
+    for (uint32_t d = 0; d < kMarkBits / 32u; ++d) marks[d * 64u] = 0;
+    // first pass, four codes a trip: at most an eighth of the segment's symbols, where that is more than a quarter above
+    // a piece's own (weights take up to 1.23 times a piece's symbols, 4-bit ones 1.39 times with 32 and 64 pieces)
+    const uint32_t whole = S << sh, room = S + S / 4u + 16u;
+    uint32_t upto = guess, count = 0;
+    for (uint32_t trips = (whole / 8u > room ? whole / 8u : room) / 4u; trips != 0 && __builtin_amdgcn_ballot_w64(upto < limit) != 0; --trips) {
+        if (upto < limit) {
+            uint64_t w = load_bits57(t, base + upto);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (upto < limit) {
+                    const uint32_t rel = upto - guess;
+                    if (rel < kMarkBits) __hip_atomic_fetch_or(mark_at(rel), 1u << (rel & 31u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                    upto += step_code<PAIR>(t, tb, base + upto, w);
+                    ++count;
+                }
+        }
+    }
+    // rounds until every lane starts where its neighbour ended (one as a rule, as many as lanes at the most): together at
+    // most 64 codes or, in long segments, one of 32 (the slowest lane of a wavefront takes up to 36 on weights)
+    const uint32_t first_upto = upto, first_count = count;
+    uint32_t from = guess, trips = (whole / 32u > 64u ? whole / 32u : 64u) / 4u;
+    bool agreed = __builtin_amdgcn_ballot_w64(upto < limit) == 0;
+    while (agreed) {
+        const uint32_t before = __shfl_up(upto, 1, 64);
+        const uint32_t want = part == 0 ? 0u : before;           // (never in front of the guess: the neighbour passed its limit)
+        const bool todo = live && want != from;
+        from = want;
+        if (__builtin_amdgcn_ballot_w64(todo) == 0) break;
+        uint32_t pos = want, steps = 0;
+        bool on = todo && pos < limit, joined = false;
+        for (; trips != 0 && __builtin_amdgcn_ballot_w64(on) != 0; --trips) {
+            if (on) {
+                uint64_t w = load_bits57(t, base + pos);
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    if (upto < limit) {
-                        upto += step_code<PAIR>(t, tb, base + upto, w);
-                        ++count;
+                    if (on) {
+                        const uint32_t rel = pos - guess;
+                        joined = rel < kMarkBits && ((*(lds_v32)mark_at(rel) >> (rel & 31u)) & 1u) != 0;
+                        if (!joined) {
+                            pos += step_code<PAIR>(t, tb, base + pos, w);
+                            ++steps;
+                        }
+                        on = !joined && pos < limit;
                     }
             }
         }
-        const uint32_t before = __shfl_up(upto, 1, 64);
-        const uint32_t want = part == 0 ? 0u : before;
-        todo = live && want != from;
-        from = want;
-        if (__builtin_amdgcn_ballot_w64(todo) == 0) break;
+        agreed = __builtin_amdgcn_ballot_w64(on) == 0;
+        if (todo) {
+            upto = joined ? first_upto : pos;
+            count = steps;
+            if (joined) {
+                // the first pass's codes from the common start on
+                const uint32_t rel = pos - guess;
+                count += first_count;
+#pragma unroll
+                for (uint32_t d = 0; d < kMarkBits / 32u; ++d) {
+                    const uint32_t below = d < (rel >> 5) ? ~0u : d == (rel >> 5) ? (1u << (rel & 31u)) - 1u : 0u;
+                    count -= static_cast<uint32_t>(__builtin_popcount(marks[d * 64u] & below));
+                }
+            }
+        }
     }
     uint32_t sum = count;                                        // symbols up to the end of the lane's stretch
     for (uint32_t m = 1; m < parts; m <<= 1) {
@@ -626,20 +684,23 @@ __device__ __forceinline__ uint64_t find_start(const DevTensor &t, const TB &tb,
         sum += part >= m ? y : 0u;
     }
     const uint32_t total = __shfl(sum, static_cast<int>(lane | (parts - 1u)), 64);
-    uint32_t idx = sum - count, stop = sum < nsym ? sum : nsym;
-    if (total < nsym) {
-        // an offset table that does not fit the stream: the segment is walked from its start by its first lane
-        idx = 0;
-        from = 0;
-        stop = part == 0 ? nsym : 0u;
+    if (!agreed || __builtin_amdgcn_ballot_w64(total < nsym) != 0) {
+        u.symbols = S << sh;
+        u.first >>= sh;
+        const uint32_t segments = (u.end + parts - 1u) >> sh, mine = u.first + (64u >> sh);
+        u.end = segments < mine ? segments : mine;
+        const uint32_t k = u.first + lane;
+        return k < u.end ? t.offsets[k] : 0;
     }
+    uint32_t idx = sum - count;
+    const uint32_t stop = sum < nsym ? sum : nsym;
     uint32_t slot = (idx + S - 1u) / S;                          // next piece to start at or behind symbol idx
     while (slot * S < stop) {
         uint64_t w = load_bits57(t, base + from);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             if (idx == slot * S && idx < stop) {
-                place[lane - part + slot] = from;
+                ring[lane - part + slot] = from;
                 ++slot;
             }
             from += step_code<PAIR>(t, tb, base + from, w);
@@ -647,20 +708,30 @@ __device__ __forceinline__ uint64_t find_start(const DevTensor &t, const TB &tb,
         }
     }
     wave_sync_lds();
-    const uint64_t start = base + place[lane];
+    const uint64_t start = u.first + lane < u.end ? base + ring[lane] : 0;
     wave_sync_lds();
     return start;
 }
 
-// A wavefront's piece starts, found or looked up.
+// The tensor's lanes of full length as far as the unit goes (which ends early only where a search was given up), and the
+// symbols of the shorter last one, if the unit goes that far.
+template <bool FIND>
+__device__ __forceinline__ uint32_t full_lanes(const DevTensor &t, const Unit &u) {
+    const uint32_t n_full = static_cast<uint32_t>(t.n / u.symbols);
+    return FIND && u.end < n_full ? u.end : n_full;
+}
+template <bool FIND>
+__device__ __forceinline__ uint32_t tail_symbols(const DevTensor &t, const Unit &u, uint32_t n_full) {
+    if (FIND && u.end == n_full) return 0;
+    return static_cast<uint32_t>(t.n - static_cast<uint64_t>(n_full) * u.symbols);
+}
+
+// Where the lane's part of a unit starts in the stream: found, where the tensor has been cut without entry points.
 template <int MODE, bool FIND, class TB>
-__device__ __forceinline__ uint64_t lane_start(const DevTensor &t, const TB &tb, lds_v32 place, uint32_t wave_first, bool fast) {
-    if constexpr (FIND) {
-        const uint64_t start = find_start<kPairMode<MODE>>(t, tb, place, wave_first);
-        return fast ? start : 0;
-    } else {
-        return fast ? seg_start(t, wave_first + (threadIdx.x & 63u)) : 0;
-    }
+__device__ __forceinline__ uint64_t lane_start(const DevTensor &t, const TB &tb, lds_v32 ring, Unit &u) {
+    if constexpr (FIND) return find_start<kPairMode<MODE>>(t, tb, ring, u);
+    const uint32_t k = u.first + (threadIdx.x & 63u);
+    return k < u.end ? seg_start(t, k) : 0;
 }
 
 template <int MODE> struct OutTraits;
@@ -1099,19 +1170,20 @@ __device__ __forceinline__ void decode_rows(const DevTensor &t, const Tables &tb
     const uint32_t wave = threadIdx.x >> 6;
     WaveMem<ROW> &wm = wms[wave];
     if (wave_first >= t.n_chunks) return;
-    const uint32_t C = t.chunk_symbols;
+    Unit u = {wave_first, t.n_chunks, t.chunk_symbols};
+    uint64_t tail_pos = lane_start<MODE, FIND>(t, tb, (lds_v32)wm.ring, u);   // where the symbols behind the lane's last whole block start
+    wave_first = u.first;
+    const uint32_t C = u.symbols;
     const uint32_t blocks_total = C / SPB;
     const uint32_t k = wave_first + lane;
     uint32_t nsym = 0;
-    if (k < t.n_chunks) {
+    if (k < u.end) {
         const uint64_t left = t.n - static_cast<uint64_t>(k) * C;
         nsym = left < C ? static_cast<uint32_t>(left) : C;
     }
-    // A shorter last segment takes the row path for its whole blocks and the scalar path for the
+    // A shorter last lane takes the row path for its whole blocks and the scalar path for the
     // rest.  The lane moves on with the others past its own end; what it decodes there is not stored.
-    const bool fast = nsym != 0;
     const uint32_t my_blocks = nsym / SPB;
-    uint64_t tail_pos = lane_start<MODE, FIND>(t, tb, (lds_v32)wm.ring, wave_first, fast);   // where the symbols behind the lane's last whole block start
     Ring2 r;
     r.stale = Tables::stale;
     r.stream = t.stream;
@@ -1120,9 +1192,9 @@ __device__ __forceinline__ void decode_rows(const DevTensor &t, const Tables &tb
     // a lane without a full segment decodes the start of the stream along with the others; nothing of it is stored
     ring2_fill<false>(r, tail_pos);
     const uint64_t bytes_per_chunk = (static_cast<uint64_t>(C) * EBITS) >> 3;
-    const uint32_t n_full = static_cast<uint32_t>(t.n / C);          // segments of full length
-    // whole blocks of the shorter last segment, if there is one
-    const uint32_t tail_blocks = static_cast<uint32_t>((t.n - static_cast<uint64_t>(n_full) * C) / SPB);
+    // the unit's lanes of full length end here, and whole blocks of the shorter last one, if it is among them
+    const uint32_t n_full = full_lanes<FIND>(t, u);
+    const uint32_t tail_blocks = tail_symbols<FIND>(t, u, n_full) / SPB;
     // a wave that holds only the shorter last segment stops after its blocks
     const uint32_t wave_blocks = wave_first < n_full ? blocks_total : tail_blocks;
     // where the first row this lane serves in a flush pass begins; the passes are RPI rows apart
@@ -1249,27 +1321,26 @@ __device__ __forceinline__ void decode_rows(const DevTensor &t, const Tables &tb
 // ALLFULL: the unit's 64 segments all have full length (decided per wavefront): no store needs a
 // condition, no lane a tail.
 template <int MODE, bool ALLFULL, bool FIND>
-__device__ __forceinline__ void decode_rows2_impl(const DevTensor &t, const Tables &tb, WaveMem2 &wm, uint32_t wave_first) {
+__device__ __forceinline__ void decode_rows2_impl(const DevTensor &t, const Tables &tb, WaveMem2 &wm, const Unit &u, uint64_t tail_pos) {
     static_assert(MODE == kModeF32 || MODE == kModeBF16, "single codes, two or four bytes per symbol");
     constexpr int SPB = Cfg<MODE>::spb;                   // 64
     constexpr uint32_t EBITS = OutTraits<MODE>::ebits;
     constexpr int HALF_GROUPS = 8;                        // groups of four symbols per half block
     static_assert(SPB == 64 && HALF_GROUPS * kGroup * 2 == SPB && HALF_GROUPS % kTripGroups == 0, "two halves of two trips");
     const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t C = t.chunk_symbols;
+    const uint32_t wave_first = u.first;
+    const uint32_t C = u.symbols;
     const uint32_t blocks_total = C / SPB;
     const uint32_t k = wave_first + lane;
     uint32_t nsym = C;
     if (!ALLFULL) {
         nsym = 0;
-        if (k < t.n_chunks) {
+        if (k < u.end) {
             const uint64_t left = t.n - static_cast<uint64_t>(k) * C;
             nsym = left < C ? static_cast<uint32_t>(left) : C;
         }
     }
-    const bool fast = nsym != 0;
     const uint32_t my_blocks = nsym / SPB;
-    uint64_t tail_pos = lane_start<MODE, FIND>(t, tb, (lds_v32)wm.ring, wave_first, fast);
     Ring2 r;
     r.stale = Tables::stale;
     r.stream = t.stream;
@@ -1277,8 +1348,8 @@ __device__ __forceinline__ void decode_rows2_impl(const DevTensor &t, const Tabl
     r.ring = (lds_v32)(wm.ring + lane);
     ring2_fill<false>(r, tail_pos);
     const uint64_t bytes_per_chunk = (static_cast<uint64_t>(C) * EBITS) >> 3;
-    const uint32_t n_full = static_cast<uint32_t>(t.n / C);
-    const uint32_t tail_blocks = static_cast<uint32_t>((t.n - static_cast<uint64_t>(n_full) * C) / SPB);
+    const uint32_t n_full = full_lanes<FIND>(t, u);
+    const uint32_t tail_blocks = tail_symbols<FIND>(t, u, n_full) / SPB;
     const uint32_t wave_blocks = ALLFULL || wave_first < n_full ? blocks_total : tail_blocks;
     // a flush pass serves eight rows, eight lanes each; the passes are eight rows apart
     const uint32_t piece = lane & 7u;
@@ -1347,9 +1418,10 @@ template <int MODE, bool FIND = false>
 __device__ __forceinline__ void decode_rows2(const DevTensor &t, const Tables &tb, WaveMem2 *wms, uint32_t wave_first) {
     if (wave_first >= t.n_chunks) return;
     WaveMem2 &wm = wms[threadIdx.x >> 6];
-    const uint32_t n_full = static_cast<uint32_t>(t.n / t.chunk_symbols);
-    if (wave_first + kUnit <= n_full) decode_rows2_impl<MODE, true, FIND>(t, tb, wm, wave_first);
-    else decode_rows2_impl<MODE, false, FIND>(t, tb, wm, wave_first);
+    Unit u = {wave_first, t.n_chunks, t.chunk_symbols};
+    const uint64_t start = lane_start<MODE, FIND>(t, tb, (lds_v32)wm.ring, u);
+    if (u.first + kUnit <= full_lanes<FIND>(t, u)) decode_rows2_impl<MODE, true, FIND>(t, tb, wm, u, start);
+    else decode_rows2_impl<MODE, false, FIND>(t, tb, wm, u, start);
 }
 
 // Decode one segment straight into dot products with x.  A segment covers one
@@ -2084,11 +2156,14 @@ bool falls_into_step(const entro_codebook *cb) {
 
 // A tensor without entry points whose segments leave most lanes of the device without work: 2^sub_shift lanes per
 // segment that find their pieces' starts themselves (find_start), as many as the device has lanes for.  A lane then
-// decodes its share four times, three of them symbol by symbol, which pays from eight lanes per segment on (with
-// four, three of the four passes make up what the shorter chain saves).  The pieces must be whole blocks of the kernel.
-// Measured: 4096 x 4096 in segments of 4096 to bf16 318 us with a lane per segment, 50 us with 64; 8192 x 4096 in
-// segments of 1024, which get eight, 102 -> 90 us.  4-bit symbols are decoded two a lookup but searched one at a
-// time: sixteen lanes are the least there (segments of 2048 115 -> 73 us; in segments of 1024 eight take 66.7, one 45.7).
+// decodes its share three times, two of them symbol by symbol, which pays from eight lanes per segment on.  The pieces
+// must be whole blocks of the kernel.  Measured: 4096 x 4096 in segments of 4096 to bf16 318 us with a lane per segment,
+// 47 us with 64; 8192 x 4096 in segments of 1024, which get eight, 115 -> 98 us.  4-bit symbols are decoded two a lookup but
+// searched one at a time: sixteen lanes are the least there (4096 x 4096 in segments of 2048 149 -> 93 us; in segments of
+// 1024 eight take 66.7, one 45.7).
+// Where runs of one symbol fill nine tenths of every twentieth segment the search is given up, with a lane per segment
+// after it: segments of 4096 with 64 lanes 395 -> 312 us, of 2048 with 32 lanes 215 -> 183 (fewer active lanes in a wavefront
+// meet fewer bank conflicts), 4-bit ones with 32 lanes 253 -> 204; with the eight of segments of 1024 127 -> 152 us.
 // (Not for the product: the search in front of gemv_direct2 gave wrong sums that changed from run to run, cause not found.)
 bool cut_segments(entro_op op, int mode, uint64_t lane_slots, const entro_tensor *t, DevTensor *dt) {
     if (op == ENTRO_OP_GEMV || t->sub_symbols || !falls_into_step(t->cb)) return false;

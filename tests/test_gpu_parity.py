@@ -222,8 +222,9 @@ def test_staircase_codes_around_the_widths_of_the_tables(bits, deepest):
     (448, 3, 0)])
 @pytest.mark.parametrize("run", [False, True])
 def test_segments_without_entry_points_cut_into_pieces(bits, chunk, segments, last, run):
-    # 8 to 64 lanes per segment that find their starts themselves, short last segments, and (448) segments that do not
-    # divide; `run`: a segment of one symbol, whose code never falls into step from most wrong bits
+    # 8 to 64 lanes per segment that find their starts themselves (4-bit symbols: 32 and 64, the segments of less than
+    # 2048 and of 3072 symbols keep a lane each), short last segments, and (448) segments that do not divide;
+    # `run`: a first segment of one symbol only, where every guess is a true start
     rng = np.random.default_rng(chunk + last + bits)
     top, n = (1 << bits) - 1, segments * chunk + last
     mid = (top + 1) // 2
@@ -238,6 +239,98 @@ def test_segments_without_entry_points_cut_into_pieces(bits, chunk, segments, la
     assert np.array_equal(_gpu_dequant(enc, E.ENTRO_F32), oracle.dequant_f32(sym, 0.25, z))
     if bits == 4:
         assert np.array_equal(_gpu_decode(enc, E.ENTRO_U4_PACKED), oracle.pack_u4(sym))
+
+
+def _with_runs(bits, chunk, segments, last, fraction, every, seed):
+    """Bell-shaped symbols; every `every`-th segment holds a run of one symbol, at an odd place behind codes of other
+    lengths, whose code does not fall into step when it is read from a wrong bit."""
+    rng = np.random.default_rng(seed)
+    top, n = (1 << bits) - 1, segments * chunk + last
+    mid = (top + 1) // 2
+    sym = np.clip(np.rint(rng.standard_t(5, n) * (9.0 if bits == 8 else 1.0) + mid), 0, top).astype(np.uint8)
+    run = int(chunk * fraction)
+    for k in range(seed % every, segments, every):
+        at = k * chunk + 5 + int(rng.integers(0, chunk - run - 5))
+        sym[at: at + run] = mid + (k % 7 if bits == 8 else k % 3)
+    return sym
+
+
+@pytest.mark.parametrize("bits,chunk", [(8, 4096), (8, 2048), (8, 1024), (8, 512), (4, 4096), (4, 2048), (4, 8192)])
+@pytest.mark.parametrize("fraction,every", [(0.5, 3), (0.9, 1), (0.97, 64)])
+def test_runs_inside_segments_without_entry_points(bits, chunk, fraction, every):
+    # the search for starts is given up in the wavefronts that hold the runs, and goes on in the others
+    for segments, last in ((70, 0), (9, chunk // 3 + 1), (1, 0)):
+        sym = _with_runs(bits, chunk, segments, last, fraction, every, segments)
+        enc = _oracle_encoded(sym, bits, chunk, 1, sym.size, 0.25, 7)
+        assert np.array_equal(_gpu_decode(enc, E.ENTRO_U8), sym)
+        assert np.array_equal(_gpu_dequant(enc, E.ENTRO_F32), oracle.dequant_f32(sym, 0.25, 7))
+        assert np.array_equal(_gpu_dequant(enc, E.ENTRO_BF16), oracle.dequant_bf16(sym, 0.25, 7))
+        if bits == 4:
+            assert np.array_equal(_gpu_decode(enc, E.ENTRO_U4_PACKED), oracle.pack_u4(sym))
+
+
+@pytest.mark.parametrize("bits,chunk", [(8, 4096), (8, 512), (4, 4096)])
+def test_segments_without_entry_points_whose_offsets_do_not_fit(bits, chunk):
+    # a segment starts where the table says and holds the symbols that it holds, wherever the table puts its end
+    sym = _with_runs(bits, chunk, 5, chunk // 2 + 3, 0.5, 64, 1)
+    enc = _oracle_encoded(sym, bits, chunk, 1, sym.size, 0.25, 7)
+    true = enc.offsets.copy()
+    for end in (true[-1] - 300, true[-2], true[-2] - 5, np.uint64(0), true[-1] + 900, np.uint64(1) << np.uint64(63)):
+        enc.offsets = true.copy()
+        enc.offsets[-1] = end
+        assert np.array_equal(_gpu_decode(enc, E.ENTRO_U8), sym)
+        assert np.array_equal(_gpu_dequant(enc, E.ENTRO_BF16), oracle.dequant_bf16(sym, 0.25, 7))
+    for shift in (-37, 41):                                    # segment 2 begins inside a neighbour: as one lane decodes it
+        enc.offsets = true.copy()
+        enc.offsets[2] = np.uint64(int(true[2]) + shift)
+        got = _gpu_decode(enc, E.ENTRO_U8)
+        assert np.array_equal(got, _gpu_decode(enc, E.ENTRO_U8, batch=True))
+        assert np.array_equal(got[: 2 * chunk], sym[: 2 * chunk]) and np.array_equal(got[3 * chunk:], sym[3 * chunk:])
+
+
+def _single_and_prepared_us(sym, bits, chunk, out):
+    """Times of the call on one tensor without entry points, which may cut its segments, and of the same tensor's
+    prepared launch, which decodes a segment with a lane and finds its tables built."""
+    cb = E.entro_build_codebook(sym, bits)
+    stream, off = E.entro_encode(sym, cb, chunk)
+    enc = B.EncodedTensor(stream, off, sym.size, chunk, cb, B.QParams(np.float32(0.25), 7, bits, E.ENTRO_ASYMMETRIC), 1, sym.size)
+    op = E.ENTRO_OP_DEQUANT if out == E.ENTRO_BF16 else E.ENTRO_OP_DECODE
+    y = torch.zeros(sym.size, dtype=torch.bfloat16 if out == E.ENTRO_BF16 else torch.uint8, device=DEV)
+    dt = E.to_device(enc, DEV)
+    t = dt.ctensor(y)
+    ws = torch.zeros(E.entro_workspace_bytes([t], op), dtype=torch.uint8, device=DEV)
+    plan = E.entro_plan_init([t], op, out, ws)
+    call = E.entro_decode_dequant if out == E.ENTRO_BF16 else E.entro_decode
+    res = []
+    for f in (lambda: call(t, out), lambda: E.entro_plan_run(plan)):
+        times = []
+        for _ in range(12):
+            a, b = torch.cuda.Event(True), torch.cuda.Event(True)
+            a.record()
+            for _ in range(5):
+                f()
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b) * 200)
+        res.append(float(np.median(times)))
+    return res
+
+
+@pytest.mark.parametrize("bits,chunk,out", [(8, 4096, E.ENTRO_BF16), (8, 2048, E.ENTRO_U8), (4, 4096, E.ENTRO_U4_PACKED)])
+def test_segments_without_entry_points_are_cut(bits, chunk, out):
+    # bell-shaped data in few segments: 0.13, 0.26 and 0.37 of a lane per segment's time
+    sym = _with_runs(bits, chunk, (1 << 23) // chunk, 0, 0.0, 1, 3)
+    single, prepared = _single_and_prepared_us(sym, bits, chunk, out)
+    assert single <= 0.85 * prepared, (single, prepared)
+
+
+@pytest.mark.parametrize("bits,chunk,out,most", [(8, 1024, E.ENTRO_BF16, 1.5), (4, 4096, E.ENTRO_U4_PACKED, 1.9)])
+def test_runs_cost_little_more_than_a_lane_per_segment(bits, chunk, out, most):
+    """Data that does not fall into step: the call gives its search up and takes 1.3 (8 bits) and 0.9 to 1.5 times (4 bits)
+    as long as the prepared launch; 1.73 and 2.15 times at the least where the search goes on until the lanes agree."""
+    segments = (1 << 24) // chunk if chunk > 1024 else 1 << 15
+    single, prepared = _single_and_prepared_us(_with_runs(bits, chunk, segments, 0, 0.9, 20, 3), bits, chunk, out)
+    assert single <= most * prepared, (single, prepared)
 
 
 @pytest.mark.parametrize("lengths", [
