@@ -2139,12 +2139,12 @@ unsigned resident_workgroups(int mode) {
 // a common divisor.  Judged by the spread of the lengths as the code itself weighs them (a code of l bits: 2^-l): at
 // least half a squared bit.  Weights have one or two, symbols spread evenly over the grid about a tenth.
 bool falls_into_step(const entro_codebook *cb) {
+    uint32_t symbols[ENTRO_MAX_CODE_LEN + 1] = {}, divisor = 0;
+    for (int s = 0; s < ENTRO_MAX_SYMBOLS; ++s) ++symbols[cb->len[s]];
     double weight = 0, mean = 0, square = 0;
-    uint32_t divisor = 0;
-    for (int s = 0; s < ENTRO_MAX_SYMBOLS; ++s) {
-        const uint32_t l = cb->len[s];
-        if (!l) continue;
-        const double p = std::ldexp(1.0, -static_cast<int>(l));
+    for (uint32_t l = 1; l <= ENTRO_MAX_CODE_LEN; ++l) {
+        if (!symbols[l]) continue;
+        const double p = std::ldexp(static_cast<double>(symbols[l]), -static_cast<int>(l));
         weight += p;
         mean += p * l;
         square += p * l * l;
@@ -2166,11 +2166,12 @@ bool falls_into_step(const entro_codebook *cb) {
 // meet fewer bank conflicts), 4-bit ones with 32 lanes 253 -> 204; with the eight of segments of 1024 127 -> 152 us.
 // (Not for the product: the search in front of gemv_direct2 gave wrong sums that changed from run to run, cause not found.)
 bool cut_segments(entro_op op, int mode, uint64_t lane_slots, const entro_tensor *t, DevTensor *dt) {
-    if (op == ENTRO_OP_GEMV || t->sub_symbols || !falls_into_step(t->cb)) return false;
+    if (op == ENTRO_OP_GEMV || t->sub_symbols) return false;
     const uint32_t block = spb_of(mode);
     const uint32_t least = dt->bits == 4 ? 4u : 3u;
     for (uint32_t sh = 6; sh >= least; --sh) {
         if ((static_cast<uint64_t>(dt->n_chunks) << sh) > lane_slots || dt->chunk_symbols % (block << sh) != 0) continue;
+        if (!falls_into_step(t->cb)) return false;               // (asked last: a pass over the code's lengths)
         dt->chunk_symbols >>= sh;
         dt->sub_shift = sh;
         dt->n_chunks = static_cast<uint32_t>(entro_num_chunks(dt->n, dt->chunk_symbols));
