@@ -54,6 +54,57 @@ def test_prepared_launches_kernels_keep_their_registers(tmp_path):
     assert all(spills[mode] <= 8 for mode in wide), spills
 
 
+@pytest.fixture(scope="module")
+def host_search(tmp_path_factory):
+    """The device source's search for starts inside segments, built as host code (host_lanes.cpp)."""
+    source = open(os.path.join(ROOT, "paper_2505_02380_amd", "csrc", "entro_device.hip")).read()
+
+    def part(begin, end):
+        at = source.index(begin)
+        return source[at: source.index(end, at)]
+
+    text = "\n".join([
+        part("constexpr int kL1 = 14", "// What the kernels read"), part("struct DevTensor {", "struct WorkItem"),
+        part("struct alignas(16) TablesTail", "// Per-wave LDS"), part("typedef volatile uint32_t", "typedef const uint32_t"),
+        part("__device__ __forceinline__ uint32_t pack_entry", "// The eight 4-bit"),
+        part("// Canonical search over the lengths", "// Pair tables: the single code"),
+        part("constexpr uint32_t kMarkBits", "// The tensor's lanes of full length")])
+    build = tmp_path_factory.mktemp("host_search")
+    (build / "search.inc").write_text(text.replace("__attribute__((address_space(3)))", ""))
+    lib = build / "host_lanes.so"
+    subprocess.run(["g++", "-std=c++20", "-O1", "-shared", "-fPIC", "-pthread", "-I", str(build),
+                    os.path.join(os.path.dirname(__file__), "host_lanes.cpp"), "-o", str(lib)], check=True, capture_output=True)
+    return C.CDLL(str(lib)).host_starts
+
+
+@pytest.mark.parametrize("bits,chunk,shift", [(8, 4096, 6), (8, 2048, 5), (8, 1024, 4), (8, 512, 3), (8, 448, 3),
+                                              (4, 8192, 6), (4, 4096, 5), (4, 2048, 4)])
+@pytest.mark.parametrize("run", [False, True])
+def test_starts_inside_segments_are_the_true_ones(host_search, bits, chunk, shift, run):
+    """Every piece's start bit, as 8 to 64 lanes per segment find it, against the sum of the code lengths in front of it;
+    `run`: the first segment's middle holds one symbol, whose wavefront may give up (the segments' starts remain)."""
+    rng = np.random.default_rng(chunk + run)
+    n, top = chunk * 9 + 3 * chunk // 7, (1 << bits) - 1
+    sym = np.clip(np.rint(rng.standard_t(5, n) * (9.0 if bits == 8 else 1.0) + (top + 1) // 2), 0, top).astype(np.uint8)
+    if run:
+        sym[7: 7 + chunk * 3 // 4] = (top + 1) // 2
+    ln, _, _ = oracle.codebook_from_symbols(sym, bits)
+    stream, offsets = oracle.encode(sym, ln, oracle.canonical_codes(ln), chunk)
+    full = np.zeros(1 << bits, np.uint8)
+    full[: ln.size] = ln
+    before = np.concatenate([[0], np.cumsum(ln[sym].astype(np.uint64))]).astype(np.uint64)
+    true = before[np.arange(0, n, chunk >> shift)]
+    got = np.full(true.size, ~np.uint64(0))
+    ptr = lambda a: a.ctypes.data_as(C.c_void_p)
+    given_up = host_search(ptr(stream), C.c_uint32(stream.size), ptr(offsets), C.c_uint64(n), C.c_uint32(chunk), C.c_uint32(shift),
+                           ptr(full), C.c_int(full.size), C.c_int(int(ln.max())), ptr(got))
+    assert 0 <= given_up <= (1 if run else 0)
+    per_wave = 64
+    for at in range(0, true.size, per_wave):
+        step = 1 << shift if given_up and at == 0 else 1
+        assert np.array_equal(got[at: at + per_wave: step], true[at: at + per_wave: step]), at
+
+
 def test_comparison_kernels_live_in_their_own_library():
     """The memory probe and the plain uint8 GEMV that bench.py times are not part of libentro: they are built
     into bench_kernels/libentro_bench.so, which exports what its header declares."""
