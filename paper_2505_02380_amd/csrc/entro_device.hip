@@ -250,10 +250,11 @@ __device__ __forceinline__ void wave_sync_lds() {
 // Canonical code tables and both lookup levels, built from the 256 (or 16)
 // code lengths by the whole workgroup of WG >= 256 lanes (four waves hold the
 // symbols).  `wcnt` is scratch of 4 * 33 words.
-// A small launch waits for this, so nothing in it is serial: one wavefront turns the
-// counts into the canonical tables with its lanes as the lengths, and the first level is
-// resolved for kSmallBits index bits only, copied to the indexes that end in the same
-// bits, and searched bit by bit for the few indexes that start with a longer code.
+// A small launch waits for this, so little in it is serial: one wavefront turns the counts
+// into the canonical tables with its lanes as the lengths (33 steps in scalar registers), and
+// the first level is resolved for kSmallBits index bits only, copied to the indexes that end in
+// the same bits, and searched bit by bit for the few indexes that start with a longer code.
+// Pair tables resolve every index, with two reads of the small table of single codes.
 // Measured as the whole call: one tensor of 2048 symbols to fp32 33.6 -> 22.0 us, 4 M symbols to
 // bytes 42.6 -> 30.6 us, against a search over all 14 lengths for every index.
 template <int WG, bool PAIR, class TB>
@@ -2164,7 +2165,8 @@ bool falls_into_step(const entro_codebook *cb) {
 // Where runs of one symbol fill nine tenths of every twentieth segment the search is given up, with a lane per segment
 // after it: segments of 4096 with 64 lanes 395 -> 312 us, of 2048 with 32 lanes 215 -> 183 (fewer active lanes in a wavefront
 // meet fewer bank conflicts), 4-bit ones with 32 lanes 253 -> 204; with the eight of segments of 1024 127 -> 152 us.
-// (Not for the product: the search in front of gemv_direct2 gave wrong sums that changed from run to run, cause not found.)
+// (Not for the product: the search in front of gemv_direct2, in a kernel with 11 spilled vector registers, gave wrong sums
+// that changed from run to run.  The cause was not found; the starts that the search finds are checked on their own, as host code.)
 bool cut_segments(entro_op op, int mode, uint64_t lane_slots, const entro_tensor *t, DevTensor *dt) {
     if (op == ENTRO_OP_GEMV || t->sub_symbols) return false;
     const uint32_t block = spb_of(mode);
