@@ -545,8 +545,8 @@ __device__ __forceinline__ uint32_t next_entry(ScalarReader &r, const TB &tb, ui
 }
 
 // ---------------------------------------------------------------- entry points found on the way
-// Small launches on a tensor that carries no entry points (k_single with FIND; t.sub is null and t.sub_shift is the
-// log2 of a segment's pieces).  A lane per segment leaves most of the device idle there, and the time is one lane's
+// Small launches on a tensor in long segments that carries no entry points (k_single with FIND; t.sub is null and
+// t.sub_shift is the log2 of a segment's pieces).  A lane per segment leaves most of the device idle there, and the time is one lane's
 // serial chain of lookups.  So 2^sub_shift lanes share a segment: each takes an equal stretch of its bits and decodes
 // from a guessed bit, Huffman codes falling into step with the true code boundaries within a few codes.  Then a lane
 // whose neighbour ended elsewhere than it began goes again from there, up to the first code boundary that it met the
@@ -1894,6 +1894,387 @@ __global__ __launch_bounds__(64 * Cfg<MODE>::waves) void k_tables(const DevTenso
     for (uint32_t j = threadIdx.x; j < sizeof(sm.tb) / 16u; j += WG) dst[j] = src[j];
 }
 
+// ---------------------------------------------------------------- segments shared by a wavefront's lanes
+// Small calls on one tensor (k_shared).  What bounds them is not the bytes but one lane's serial chain of lookups, so
+// 2^part_shift lanes share a segment, about 64 symbols each, and a lookup answers up to four codes at once.
+//   1. The unit's part of the stream (the segments of a wavefront lie side by side) comes into LDS in whole lines.
+//   2. Each lane takes an equal stretch of its segment's bits and counts the codes that start in it, from a guessed first
+//      bit: Huffman codes fall into step with the true boundaries within a few codes.  Then a lane whose neighbour ended
+//      elsewhere than it began counts its stretch again from there, until all agree.  Lane 0 of a segment begins at a true
+//      boundary and every round settles at least one more lane, so the starts are true whatever the data (one round as a
+//      rule; as many as lanes where a run of one symbol keeps the guesses out of step).
+//   3. The counts say where each lane's symbols belong; it decodes its stretch once more and leaves them there, in LDS.
+//   4. The whole wavefront turns the unit's symbols, now in order, into output: consecutive 16 bytes by consecutive lanes,
+//      or rows of the product.
+// A lane's chain is three times 64 symbols at about 2.9 a lookup instead of a segment's length at one a lookup.
+constexpr int kMulti = 12;               // stream bits that index the table of several codes
+constexpr uint32_t kShareSymbols = 64;   // symbols of a lane, about
+constexpr uint32_t kShareWaves = 16;
+constexpr uint32_t kShareMost = 8192;    // most symbols of a segment: its symbols and its stream have to fit into LDS
+
+// How a launch of k_shared is cut (DevTensor::chunk_symbols is the segment's length there, or the piece's where the tensor
+// has entry points).
+struct Share {
+    uint32_t part_shift;        // log2 of the lanes per segment
+    uint32_t units;             // wavefront's worths of 64 >> part_shift segments
+    uint32_t waves;             // wavefronts of a workgroup that take units
+    uint32_t symbol_bytes;      // a wavefront's memory: the unit's symbols, one byte each and four free bytes behind each 64,
+    uint32_t wave_bytes;        // and the unit's part of the stream
+};
+
+// Entry of the table of several codes: the next codes that kMulti bits hold in full, at most four.
+// x: their symbols, first one lowest.  y: bits 0..5 their lengths' sum, bits 8..10 their number, from bit 12 on, four bits
+// each, the lengths' sums up to the first, second and third code, 15 from the last code on.  All zero: a longer code.
+constexpr uint32_t kLimits = 8;          // longer codes of up to kMulti + kLimits bits are told apart by one look at their limits
+struct alignas(16) ShareMem {
+    u32x2 multi[1 << kMulti];
+    u32x4 limits[kLimits / 4];           // see share_long
+    TablesTail tail;                     // the canonical tables; with what follows, a Tables while the tables are built
+    uint8_t pool[160u * 1024u - (sizeof(u32x2) << kMulti) - 4u * kLimits - sizeof(TablesTail)];
+    __device__ __forceinline__ Tables &building() { return *reinterpret_cast<Tables *>(&tail); }
+};
+static_assert(sizeof(ShareMem) == 160u * 1024u && sizeof(Tables) <= sizeof(TablesTail) + sizeof(ShareMem::pool) &&
+              sizeof(TablesTail) % 16 == 0, "all of a compute unit's LDS");
+
+typedef uint32_t __attribute__((address_space(3))) *lds_w32;
+typedef u32x4 __attribute__((address_space(3))) *lds_128;
+
+// Symbol i of a unit, four a dword: sixteen dwords and one free, or lanes 64 symbols apart would write to four banks only.
+__device__ __forceinline__ uint32_t share_at(uint32_t dword) { return dword + (dword >> 4); }
+
+// Puts the table of several codes together from the first-level table (1024 lanes, four entries each), and the limits of the
+// longer codes: limit j is the first value, of 32 stream bits in code order, that no code of up to kMulti + 1 + j bits has.
+__device__ __forceinline__ void build_multi(ShareMem &sm) {
+    const Tables &tb = sm.building();
+    for (uint32_t i = threadIdx.x; i < (1u << kMulti); i += 64u * kShareWaves) {
+        uint32_t w = i, bits = 0, n = 0, syms = 0, ends = 0xfff000u;
+        bool more = true;
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) {
+            const uint32_t e = tb.lut[w];                        // (zeros behind the index bits: only codes within them count)
+            const uint32_t len = entry_len(e);
+            more = more && len != 0 && bits + len <= static_cast<uint32_t>(kMulti);
+            if (more) {
+                if (j != 0) ends = (ends & ~(15u << (8 + 4 * j))) | (bits << (8 + 4 * j));
+                syms |= entry_sym(e) << (8 * j);
+                bits += len;
+                w >>= len;
+                n = j + 1;
+            }
+        }
+        sm.multi[i] = n ? u32x2{syms, bits | (n << 8) | ends} : u32x2{0u, 0u};
+    }
+    if (threadIdx.x < kLimits) {
+        const uint32_t l = kMulti + 1 + threadIdx.x;
+        const uint64_t v = static_cast<uint64_t>(tb.first[l] + tb.cnt[l]) << (32u - l);
+        reinterpret_cast<uint32_t *>(sm.limits)[threadIdx.x] = v < 0xffffffffu ? static_cast<uint32_t>(v) : 0xffffffffu;
+    }
+}
+
+// Where a lane reads its segment's stream.
+struct ShareReader {
+    uint64_t base;              // absolute bit of the segment's start
+    uint32_t lds_bit;           // and its bit in the wavefront's copy
+    bool in_lds;                // the copy holds the whole unit (else: straight from memory)
+    lds_p32 words;
+};
+
+// At least 57 stream bits from bit `rel` of the segment on.
+__device__ __forceinline__ uint64_t share_window(const DevTensor &t, const ShareReader &r, uint32_t rel) {
+    if (__builtin_expect(!r.in_lds, 0)) return load_bits57(t, r.base + rel);
+    const uint32_t p = r.lds_bit + rel;
+    const lds_p32 src = r.words + (p >> 5);
+    const uint32_t w0 = src[0], w1 = src[1], w2 = src[2];
+    return static_cast<uint64_t>(__builtin_amdgcn_alignbit(w1, w0, p)) | (static_cast<uint64_t>(__builtin_amdgcn_alignbit(w2, w1, p)) << 32);
+}
+
+// The code at bit `rel`, longer than kMulti bits.  Canonical codes grow with their length, so the number of limits that its
+// bits have reached is its length; one in 64 to 500 codes comes here (one in two groups of a wavefront has such a lane).
+__device__ __forceinline__ uint32_t share_long(const DevTensor &t, const ShareMem &sm, const ShareReader &r, uint32_t rel) {
+    const uint32_t window = static_cast<uint32_t>(share_window(t, r, rel)), v = __brev(window);
+    uint32_t l = kMulti + 1;
+#pragma unroll
+    for (uint32_t j = 0; j < kLimits; ++j) l += v >= sm.limits[j / 4][j % 4] ? 1u : 0u;
+    if (__builtin_expect(l > kMulti + kLimits && t.max_len > kMulti + kLimits, 0))
+        return decode_canonical(sm.tail, window, kMulti + kLimits + 1, t.max_len);
+    l = l < t.max_len ? l : t.max_len;                           // (the last limit of a full code is one too low)
+    const uint32_t d = (v >> (32u - l)) - sm.tail.first[l];
+    return d < sm.tail.cnt[l] ? pack_entry(sm.tail.sorted[sm.tail.offs[l] + d], l) : pack_entry(0, 1);   // not a code: keep moving
+}
+
+// A lane's symbols on their way into the unit's, which are zero at first: whole dwords, to which lanes that share one add
+// their bytes.
+struct ShareWriter {
+    lds_w32 out;
+    uint32_t dword;             // next one to write
+    uint32_t fill;              // bytes of it that have passed, 0..3
+    uint64_t held;
+    __device__ __forceinline__ void begin(lds_w32 o, uint32_t i) { out = o; dword = i >> 2; fill = i & 3u; held = 0; }
+    __device__ __forceinline__ void flush() {
+        __hip_atomic_fetch_or(out + share_at(dword), static_cast<uint32_t>(held), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    }
+    // n <= 4 symbols (the bytes behind them are zero)
+    __device__ __forceinline__ void put(uint32_t syms, uint32_t n) {
+        held |= static_cast<uint64_t>(syms) << (8u * fill);
+        fill += n;
+        if (fill >= 4u) {
+            flush();
+            held >>= 32;
+            ++dword;
+            fill -= 4u;
+        }
+    }
+};
+
+// The codes that start in [rel, limit): four lookups a window while the lane has kMulti bits to go, then, for the end of the
+// stretch, one a window of which only the codes that start in front of the limit count.  Moves rel behind the last of them
+// and adds their number to `count`.  WRITE: their symbols go to `out`.
+template <bool WRITE>
+__device__ __forceinline__ void share_pass(const DevTensor &t, const ShareMem &sm, const ShareReader &r, uint32_t &rel, uint32_t limit,
+                                           uint32_t &count, ShareWriter &out) {
+    int32_t room = static_cast<int32_t>(limit - rel);            // (negative: the lane begins behind its limit)
+    while (__builtin_amdgcn_ballot_w64(room >= kMulti) != 0) {
+        uint64_t w = share_window(t, r, limit - static_cast<uint32_t>(room));
+        bool miss = false;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const u32x2 e = sm.multi[static_cast<uint32_t>(w) & ((1u << kMulti) - 1u)];
+            const bool on = room >= kMulti;
+            const uint32_t y = on ? e.y : 0u;
+            if (WRITE) out.put(on ? e.x : 0u, (y >> 8) & 7u);
+            w >>= y & 63u;
+            room -= static_cast<int32_t>(y & 63u);
+            count += (y >> 8) & 7u;
+            miss = on && y == 0;                                 // (a lane that meets a longer code does not move any more)
+        }
+        if (__builtin_amdgcn_ballot_w64(miss) != 0) {
+            if (miss) {
+                const uint32_t e = share_long(t, sm, r, limit - static_cast<uint32_t>(room));
+                if (WRITE) out.put(entry_sym(e), 1u);
+                room -= static_cast<int32_t>(entry_len(e));
+                ++count;
+            }
+        }
+    }
+    while (__builtin_amdgcn_ballot_w64(room > 0) != 0) {
+        if (room > 0) {
+            const uint32_t at = limit - static_cast<uint32_t>(room);
+            const u32x2 e = sm.multi[static_cast<uint32_t>(share_window(t, r, at)) & ((1u << kMulti) - 1u)];
+            uint32_t syms = e.x, len = e.y & 63u, n = (e.y >> 8) & 7u;
+            if (__builtin_expect(n == 0, 0)) {
+                const uint32_t l = share_long(t, sm, r, at);
+                syms = entry_sym(l);
+                len = entry_len(l);
+                n = 1;
+            } else {
+                const uint32_t left = static_cast<uint32_t>(room), c1 = (e.y >> 12) & 15u, c2 = (e.y >> 16) & 15u, c3 = (e.y >> 20) & 15u;
+                const uint32_t k = left <= c1 ? 1u : left <= c2 ? 2u : left <= c3 ? 3u : 4u;
+                const uint32_t upto = left <= c1 ? c1 : left <= c2 ? c2 : left <= c3 ? c3 : len;
+                n = k < n ? k : n;
+                len = upto < len ? upto : len;
+                syms &= ~0u >> (32u - 8u * n);
+            }
+            if (WRITE) out.put(syms, n);
+            room -= static_cast<int32_t>(len);
+            count += n;
+        }
+    }
+    rel = limit - static_cast<uint32_t>(room);
+}
+
+// m symbols in LDS, the tensor's from u0 (a multiple of 128) on, to the output: 16 bytes a lane and step.
+template <int MODE>
+__device__ __forceinline__ void share_store(const DevTensor &t, lds_w32 sym, uint64_t u0, uint32_t m) {
+    constexpr uint32_t SYMS = MODE == kModeF32 ? 4u : MODE == kModeBF16 ? 8u : MODE == kModeU8 ? 16u : 32u;   // per 16 bytes
+    const uint32_t lane = threadIdx.x & 63u;
+    uint8_t *const out = static_cast<uint8_t *>(t.out) + ((u0 * OutTraits<MODE>::ebits) >> 3);
+    const float zf = static_cast<float>(t.zero_point), scale = t.scale;
+    const uint32_t whole = m / SYMS;
+    for (uint32_t j = lane; j < whole; j += 64u) {
+        uint32_t src[SYMS / 4];                                  // (they lie within one run of sixteen dwords)
+#pragma unroll
+        for (uint32_t i = 0; i < SYMS / 4; ++i) src[i] = sym[share_at(j * (SYMS / 4)) + i];
+        u32x4 v;
+        if constexpr (MODE == kModeU8) {
+            v = u32x4{src[0], src[1], src[2], src[3]};
+        } else if constexpr (MODE == kModeU4) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t a = src[2 * i], b = src[2 * i + 1];
+                const uint32_t pa = (a & 0x000f000fu) | ((a >> 4) & 0x00f000f0u), pb = (b & 0x000f000fu) | ((b >> 4) & 0x00f000f0u);
+                v[i] = __builtin_amdgcn_perm(pb, pa, 0x06040200u);
+            }
+        } else {
+            float f[SYMS];
+#pragma unroll
+            for (uint32_t i = 0; i < SYMS; ++i) f[i] = (static_cast<float>((src[i / 4] >> (8 * (i % 4))) & 0xffu) - zf) * scale;
+            if constexpr (MODE == kModeF32) {
+                v = u32x4{__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]), __float_as_uint(f[3])};
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const f32x2 pr = {f[2 * i], f[2 * i + 1]};
+                    v[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pr, bf16x2));   // round to nearest even
+                }
+            }
+        }
+        *(global_u4_wptr)(out + j * 16u) = v;
+    }
+    // the tensor's end
+    for (uint32_t i = whole * SYMS + lane; i < m; i += 64u) {
+        const uint32_t q = (sym[share_at(i >> 2)] >> (8u * (i & 3u))) & 0xffu;
+        if constexpr (MODE == kModeU8) out[i] = static_cast<uint8_t>(q);
+        if constexpr (MODE == kModeU4)
+            if ((i & 1u) == 0) out[i >> 1] = static_cast<uint8_t>((q & 0xfu) | (i + 1u < m ? (sym[share_at(i >> 2)] >> (8u * (i & 3u) + 4u)) & 0xf0u : 0u));
+        if constexpr (MODE == kModeF32) reinterpret_cast<float *>(out)[i] = dequant(q, t.zero_point, scale);
+        if constexpr (MODE == kModeBF16) reinterpret_cast<uint16_t *>(out)[i] = static_cast<uint16_t>(bf16_bits(dequant(q, t.zero_point, scale)));
+    }
+}
+
+// The rows of the product that m symbols in LDS, the tensor's from u0 on, hold in full or in part.  As many
+// lanes take a row as have eight columns each of it (a power of two, at most all), several rows at a time where rows are short.
+// cols and m are multiples of 8, u0 of 128: eight columns lie side by side, and their activations on 16 bytes.
+// A row that does not lie in the unit as a whole leaves a partial sum, as k_fix_* reads it (chunk_symbols: the unit's).
+template <int MODE>
+__device__ __forceinline__ void share_rows(const DevTensor &t, lds_w32 sym, uint32_t unit, uint64_t u0, uint32_t m) {
+    const uint32_t lane = threadIdx.x & 63u, cols = t.cols;
+    uint32_t per = 1;
+    while (per < 64u && per * 8u < cols) per <<= 1;
+    const uint32_t r0 = static_cast<uint32_t>(u0 / cols), r1 = static_cast<uint32_t>((u0 + m - 1u) / cols);
+    const uint32_t head = static_cast<uint32_t>(u0 - static_cast<uint64_t>(r0) * cols);      // columns of row r0 in front of the unit
+    const float zf = static_cast<float>(t.zero_point);
+    for (uint32_t r = r0 + lane / per; r <= r1; r += 64u / per) {
+        // the row's columns [c0, c1) are the unit's symbols from s0 on
+        const uint64_t before = static_cast<uint64_t>(r - r0) * cols;
+        const uint32_t c0 = r == r0 ? head : 0u;
+        const uint32_t s0 = r == r0 ? 0u : static_cast<uint32_t>(before - head);
+        const uint32_t c1 = cols - c0 < m - s0 ? cols : c0 + (m - s0);
+        float acc = 0.0f;
+#pragma unroll 4
+        for (uint32_t i = 8u * (lane & (per - 1u)); i < c1 - c0; i += 8u * per) {
+            const u32x4 xv = *(global_u4_ptr)(t.x + c0 + i);
+            const uint32_t at = share_at((s0 + i) >> 2);
+            const uint32_t q[2] = {sym[at], sym[at + 1u]};           // (an even dword and the next: within one run)
+#pragma unroll
+            for (uint32_t j = 0; j < 8; ++j) {
+                const float d = static_cast<float>((q[j / 4] >> (8 * (j % 4))) & 0xffu) - zf;
+                const float x = __uint_as_float((j & 1u) ? xv[j / 2] & 0xffff0000u : xv[j / 2] << 16);
+                acc = __builtin_fmaf(d, x, acc);
+            }
+        }
+        for (uint32_t d = 1; d < per; d <<= 1) acc += __shfl_xor(acc, d, 64);
+        if ((lane & (per - 1u)) == 0) {
+            if (c0 == 0 && c1 == cols) {
+                const float y = acc * t.scale;
+                if (gemv_f32(MODE)) reinterpret_cast<float *>(t.out)[r] = y;
+                else reinterpret_cast<uint16_t *>(t.out)[r] = static_cast<uint16_t>(bf16_bits(y));
+            } else {
+                t.partials[2 * static_cast<uint64_t>(unit) + (r == r0 ? 0 : 1)] = acc;
+            }
+        }
+    }
+}
+
+// One tensor per launch: every workgroup builds the tables, its wavefronts take units.
+template <int MODE>
+__global__ __launch_bounds__(64 * kShareWaves) void k_shared(const DevTensor t, const Share c) {
+    __shared__ ShareMem sm;
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    const uint32_t sh = c.part_shift, parts = 1u << sh, part = lane & (parts - 1u), S = t.chunk_symbols;
+    const uint32_t unit_symbols = S << (6u - sh);
+    const lds_w32 sym = (lds_w32)(sm.pool + wave * c.wave_bytes);
+    const lds_w32 copy = sym + c.symbol_bytes / 4u;
+    const uint32_t copy_bytes = c.wave_bytes - c.symbol_bytes;
+    ShareReader r;
+    r.words = (lds_p32)copy;
+    // the lane's segment of a unit: its symbols, and its bits in the stream
+    uint32_t nsym, span;
+    auto look_up = [&](uint32_t unit) __attribute__((always_inline)) {
+        const uint32_t k = (unit << (6u - sh)) + (lane >> sh);
+        nsym = span = 0;
+        r.base = 0;
+        if (k < t.n_chunks) {
+            const uint64_t left = t.n - static_cast<uint64_t>(k) * S;
+            nsym = left < S ? static_cast<uint32_t>(left) : S;
+            r.base = t.offsets[k];
+            const uint64_t end = t.offsets[k + 1], bits = end > r.base ? end - r.base : 0;
+            const uint64_t most = static_cast<uint64_t>(nsym) * ENTRO_MAX_CODE_LEN;
+            span = static_cast<uint32_t>(bits < most ? bits : most);
+        }
+    };
+    uint32_t unit = blockIdx.x * c.waves + wave;
+    const bool works = wave < c.waves && unit < c.units;
+    if (works) look_up(unit);                                    // (on its way while the tables are built)
+    build_tables<64 * kShareWaves, false>(t, sm.building(), reinterpret_cast<uint32_t *>(sm.multi));   // (scratch: not in use yet)
+    build_multi(sm);
+    __syncthreads();
+    if (!works) return;
+    for (;;) {
+        {
+            // the unit's part of the stream, and zeros for its symbols (its first segment is always there: no unit is empty)
+            const uint64_t lo = (static_cast<uint64_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(r.base >> 32))) << 32 |
+                                 __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(r.base))) & ~uint64_t{127};
+            const uint32_t room = 8u * (copy_bytes - 32u);       // (a window reaches some bytes behind a segment's end)
+            const bool held = nsym == 0 || (r.base - lo <= room && r.base - lo + span <= room);   // (also in front of lo: not held)
+            r.in_lds = __builtin_amdgcn_ballot_w64(!held) == 0;
+            r.lds_bit = nsym != 0 ? static_cast<uint32_t>(r.base - lo) : 0u;
+            const uint32_t from = static_cast<uint32_t>(lo >> 3);
+            if (r.in_lds)
+                for (uint32_t b = lane; b < copy_bytes / 16u; b += 64u)
+                    *(lds_128)(copy + b * 4u) = load_block(t.stream, from + b * 16u, t.stream_bytes - 16u);
+            for (uint32_t b = lane; b < c.symbol_bytes / 16u; b += 64u) *(lds_128)(sym + b * 4u) = u32x4{0u, 0u, 0u, 0u};
+        }
+        wave_sync_lds();
+        const uint32_t guess = static_cast<uint32_t>((static_cast<uint64_t>(span) * part) >> sh);
+        const uint32_t limit = static_cast<uint32_t>((static_cast<uint64_t>(span) * (part + 1u)) >> sh);
+        ShareWriter out;
+        uint32_t from = guess, upto = guess, count = 0;
+        share_pass<false>(t, sm, r, upto, limit, count, out);
+        for (;;) {
+            const uint32_t before = __shfl_up(upto, 1, 64);
+            const uint32_t want = part == 0 ? 0u : before;       // (never in front of the guess: the neighbour passed its limit)
+            const bool todo = want != from;
+            if (__builtin_amdgcn_ballot_w64(todo) == 0) break;
+            uint32_t rel = todo ? want : limit, n = 0;
+            share_pass<false>(t, sm, r, rel, limit, n, out);
+            upto = todo ? rel : upto;
+            count = todo ? n : count;
+            from = want;
+        }
+        uint32_t sum = count;
+        for (uint32_t d = 1; d < parts; d <<= 1) {
+            const uint32_t y = __shfl_up(sum, d, 64);
+            sum += part >= d ? y : 0u;
+        }
+        // an offset table that does not fit the stream: the segment's first lane decodes it from its start
+        const bool bad = __shfl(sum, static_cast<int>(lane | (parts - 1u)), 64) != nsym;
+        const uint32_t first = (lane >> sh) * S;
+        out.begin(sym, first + (bad ? 0u : sum - count));
+        uint32_t rel = bad ? limit : from, n = 0;
+        share_pass<true>(t, sm, r, rel, limit, n, out);
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(bad) != 0, 0)) {
+            if (bad && part == 0) {
+                uint64_t pos = r.base;
+                for (uint32_t i = 0; i < nsym; ++i) {
+                    const uint32_t e = decode_canonical(sm.tail, static_cast<uint32_t>(load_bits57(t, pos)), 1u, t.max_len);
+                    out.put(entry_sym(e), 1u);
+                    pos += entry_len(e);
+                }
+            }
+        }
+        if (out.fill != 0) out.flush();                          // (never behind the unit's symbols: fill is 0 at their end)
+        wave_sync_lds();
+        const uint64_t u0 = static_cast<uint64_t>(unit) * unit_symbols, left = t.n - u0;
+        const uint32_t m = left < unit_symbols ? static_cast<uint32_t>(left) : unit_symbols;
+        if constexpr (is_gemv(MODE)) share_rows<MODE>(t, sym, unit, u0, m);
+        else share_store<MODE>(t, sym, u0, m);
+        unit += gridDim.x * c.waves;
+        if (unit >= c.units) break;
+        wave_sync_lds();
+        look_up(unit);
+    }
+}
+
 // Second stage of the GEMV: the partial sums of a row that straddles lanes are added up by sixteen lanes,
 // lane j taking every sixteenth of them in segment order, then the sixteen in a fixed tree (the same sum
 // in the same order on every run).
@@ -2155,20 +2536,14 @@ bool falls_into_step(const entro_codebook *cb) {
     return divisor == 1 && square / weight - mean * mean >= 0.5;
 }
 
-// A tensor without entry points whose segments leave most lanes of the device without work: 2^sub_shift lanes per
-// segment that find their pieces' starts themselves (find_start), as many as the device has lanes for.  A lane then
-// decodes its share three times, two of them symbol by symbol, which pays from eight lanes per segment on.  The pieces
-// must be whole blocks of the kernel.  Measured: 4096 x 4096 in segments of 4096 to bf16 318 us with a lane per segment,
-// 47 us with 64; 8192 x 4096 in segments of 1024, which get eight, 115 -> 98 us.  4-bit symbols are decoded two a lookup but
-// searched one at a time: sixteen lanes are the least there (4096 x 4096 in segments of 2048 149 -> 93 us; in segments of
-// 1024 eight take 66.7, one 45.7).
-// Where runs of one symbol fill nine tenths of every twentieth segment the search is given up, with a lane per segment
-// after it: segments of 4096 with 64 lanes 395 -> 312 us, of 2048 with 32 lanes 215 -> 183 (fewer active lanes in a wavefront
-// meet fewer bank conflicts), 4-bit ones with 32 lanes 253 -> 204; with the eight of segments of 1024 127 -> 152 us.
-// (Not for the product: the search in front of gemv_direct2, in a kernel with 11 spilled vector registers, gave wrong sums
-// that changed from run to run.  The cause was not found; the starts that the search finds are checked on their own, as host code.)
+// Segments longer than k_shared holds (kShareMost), without entry points, that leave most lanes of the device without work:
+// 2^sub_shift lanes per segment that find their pieces' starts themselves (find_start), as many as the device has lanes for.
+// A lane then decodes its share three times, two of them symbol by symbol, which pays from eight lanes per segment on (4-bit
+// symbols, decoded two a lookup but searched one at a time: sixteen).  The pieces must be whole blocks of the kernel.
+// Measured when shorter segments came here too: 4096 x 4096 in segments of 4096 to bf16 318 us with a lane per segment, 47 us
+// with 64; 8192 x 4096 in segments of 1024, which got eight, 115 -> 98 us.
 bool cut_segments(entro_op op, int mode, uint64_t lane_slots, const entro_tensor *t, DevTensor *dt) {
-    if (op == ENTRO_OP_GEMV || t->sub_symbols) return false;
+    if (op == ENTRO_OP_GEMV || t->sub_symbols || dt->chunk_symbols <= kShareMost) return false;
     const uint32_t block = spb_of(mode);
     const uint32_t least = dt->bits == 4 ? 4u : 3u;
     for (uint32_t sh = 6; sh >= least; --sh) {
@@ -2180,6 +2555,54 @@ bool cut_segments(entro_op op, int mode, uint64_t lane_slots, const entro_tensor
         return true;
     }
     return false;
+}
+
+entro_status launch_fix_single(entro_dtype d, const DevTensor &dt, hipStream_t s) {
+    const unsigned grid = (dt.rows + kFixRows - 1) / kFixRows;
+    if (d == ENTRO_F32) hipLaunchKernelGGL(k_fix_single<kModeGemvF32>, dim3(grid), dim3(kFixWG), 0, s, dt);
+    else hipLaunchKernelGGL(k_fix_single<kModeGemvBF16>, dim3(grid), dim3(kFixWG), 0, s, dt);
+    return hip_ok(hipGetLastError(), "launch row-sum kernel") ? ENTRO_OK : ENTRO_ERR_DEVICE;
+}
+
+// A tensor without entry points in few segments: 8 to 64 lanes share one (k_shared), at about 64 symbols a lane.  A
+// wavefront's share of LDS is what its unit's symbols take, and its part of the stream at the tensor's mean rate and a
+// thirty-second more (a unit with more is read straight from memory).
+// A lane per segment takes 0.036 (4-bit) to 0.072 us (8-bit) for each of a segment's symbols, however many segments there
+// are until the device is full; k_shared 13.5 to 17.5 us for each 2^24 symbols of the tensor.  They meet at 50 to 65
+// thousand segments: three sixteenths of the lanes is a little less (and less again where LDS holds fewer than sixteen units).
+// Measured, whole calls, before -> now.  8 bits, 4096 x 4096: to bf16 47.2 -> 34.0 us, bytes 65.1 -> 31.0, product 295.9
+// -> 32.5; segments of 1024 49.1 -> 33.8, 64.8 -> 31.8, 84.8 -> 32.8; of 512, 32768 of them, 47.7 -> 33.9, 50.1 -> 31.4, 48.9
+// -> 32.2, and 131072 of them, which the rule leaves with a lane each, 57 against 86.  4 bits: bf16 62.4 -> 25.0, product
+// 159.4 -> 24.3; segments of 1024, 16384 x 4096 (65536, left with a lane each), 59 against 63.
+bool share_segments(entro_op op, uint64_t lane_slots, unsigned cus, const entro_tensor *t, const DevTensor &dt, Share *c) {
+    const uint32_t S = dt.chunk_symbols;
+    if (t->sub_symbols || S % 128u != 0 || S < 8u * kShareSymbols || S > kShareMost) return false;
+    if (op == ENTRO_OP_GEMV && dt.cols % 8u != 0) return false;
+    c->part_shift = 3;
+    while (c->part_shift < 6u && (kShareSymbols << (c->part_shift + 1u)) <= S) ++c->part_shift;
+    const uint32_t per = 64u >> c->part_shift, unit = S * per;
+    c->units = (dt.n_chunks + per - 1u) / per;
+    const double rate = std::min(static_cast<double>(dt.bits), 8.0 * dt.stream_bytes / static_cast<double>(dt.n));
+    const uint32_t copy = static_cast<uint32_t>(unit * rate / 8.0 * 33.0 / 32.0) + 16u;
+    c->symbol_bytes = (unit / 16u * 17u + 15u) / 16u * 16u;
+    c->wave_bytes = c->symbol_bytes + (copy + 15u) / 16u * 16u + 32u;
+    const uint32_t most = std::min<uint32_t>(kShareWaves, sizeof(ShareMem::pool) / c->wave_bytes);
+    c->waves = std::min<uint32_t>(most, (c->units + cus - 1u) / cus);
+    return static_cast<uint64_t>(dt.n_chunks) * 16u * kShareWaves <= lane_slots * 3u * most && falls_into_step(t->cb);
+}
+
+entro_status launch_shared(entro_op op, entro_dtype d, DevTensor &dt, const Share &c, unsigned cus, hipStream_t s) {
+    const unsigned grid = std::min<unsigned>(cus, (c.units + c.waves - 1u) / c.waves);
+    dispatch_mode(mode_of(op, d, false), [&](auto m) {
+        constexpr int M = decltype(m)::value;
+        if constexpr (M <= kModeGemvBF16)
+            hipLaunchKernelGGL(k_shared<M>, dim3(grid), dim3(64u * kShareWaves), 0, s, dt, c);
+    });
+    if (!hip_ok(hipGetLastError(), "launch decode kernel")) return ENTRO_ERR_DEVICE;
+    const uint32_t unit = dt.chunk_symbols * (64u >> c.part_shift);
+    if (op != ENTRO_OP_GEMV || unit % dt.cols == 0) return ENTRO_OK;
+    dt.chunk_symbols = unit;                                     // rows that straddle units
+    return launch_fix_single(d, dt, s);
 }
 
 entro_status launch_single(const entro_tensor *t, entro_op op, entro_dtype d, float *partials,
@@ -2197,6 +2620,8 @@ entro_status launch_single(const entro_tensor *t, entro_op op, entro_dtype d, fl
     if (st != ENTRO_OK) return st;
     dt.partials = partials;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
+    Share c;
+    if (share_segments(op, static_cast<uint64_t>(slots) * wg, slots, t, dt, &c)) return launch_shared(op, d, dt, c, slots, s);
     const bool find = cut_segments(op, mode, static_cast<uint64_t>(slots) * wg, t, &dt);
     // a unit per wavefront when the tensor is large; fewer units per workgroup, down to one, when
     // that would leave compute units without a workgroup
@@ -2214,13 +2639,7 @@ entro_status launch_single(const entro_tensor *t, entro_op op, entro_dtype d, fl
         hipLaunchKernelGGL((k_single<M, false>), dim3(grid), dim3(wg), 0, s, dt, static_cast<uint32_t>(wg_units));
     });
     if (!hip_ok(hipGetLastError(), "launch decode kernel")) return ENTRO_ERR_DEVICE;
-    if (dt.need_fix) {
-        const unsigned g2 = (dt.rows + kFixRows - 1) / kFixRows;
-        if (gemv_f32(mode)) hipLaunchKernelGGL(k_fix_single<kModeGemvF32>, dim3(g2), dim3(kFixWG), 0, s, dt);
-        else hipLaunchKernelGGL(k_fix_single<kModeGemvBF16>, dim3(g2), dim3(kFixWG), 0, s, dt);
-        if (!hip_ok(hipGetLastError(), "launch row-sum kernel")) return ENTRO_ERR_DEVICE;
-    }
-    return ENTRO_OK;
+    return dt.need_fix ? launch_fix_single(d, dt, s) : ENTRO_OK;
 }
 
 // Device address of `scratch` on the current device, looked up once per device; nullptr if the

@@ -269,6 +269,44 @@ def test_runs_inside_segments_without_entry_points(bits, chunk, fraction, every)
             assert np.array_equal(_gpu_decode(enc, E.ENTRO_U4_PACKED), oracle.pack_u4(sym))
 
 
+@pytest.mark.parametrize("bits,chunk,cols", [(8, 512, 64), (8, 640, 72), (8, 1152, 4104), (8, 3968, 14336), (8, 8192, 3072), (4, 512, 200),
+                                             (4, 4096, 8), (4, 8192, 5000)])
+def test_segments_shared_by_lanes_every_output_and_product(bits, chunk, cols):
+    """Rows shorter and longer than a wavefront's unit, segments of odd lengths, a run that keeps guesses out of step, codes
+    longer than the tables, and a stretch of rare symbols whose stream is longer than the unit's copy holds."""
+    rows = -(-(11 * chunk + 300) // cols)
+    n, top = rows * cols, (1 << bits) - 1
+    rng = np.random.default_rng(chunk + cols)
+    sym = np.clip(np.rint(rng.standard_t(3, n) * (9.0 if bits == 8 else 0.8) + (top + 1) // 2), 0, top).astype(np.uint8)
+    sym[chunk + 7: chunk + 7 + chunk // 2] = (top + 1) // 2
+    sym[5 * chunk + 3: 6 * chunk + 9] = rng.integers(0, top + 1, chunk + 6)
+    z = 100 if bits == 8 else 6
+    enc = _oracle_encoded(sym, bits, chunk, rows, cols, 0.25, z)
+    assert np.array_equal(_gpu_decode(enc, E.ENTRO_U8), sym)
+    assert np.array_equal(_gpu_dequant(enc, E.ENTRO_F32), oracle.dequant_f32(sym, 0.25, z))
+    assert np.array_equal(_gpu_dequant(enc, E.ENTRO_BF16), oracle.dequant_bf16(sym, 0.25, z))
+    if bits == 4:
+        assert np.array_equal(_gpu_decode(enc, E.ENTRO_U4_PACKED), oracle.pack_u4(sym))
+    xb = synth.make_x_bf16(0, 3, cols)
+    y_ref, _ = oracle.gemv(sym, rows, cols, 0.25, z, xb)
+    # fp32 sums of exact products: at most cols roundings of half an ulp, relative to the terms' magnitudes
+    terms = np.abs((sym.astype(np.float64).reshape(rows, cols) - z) * 0.25) @ np.abs((xb.astype(np.uint32) << 16).view(np.float32).astype(np.float64))
+    assert np.all(np.abs(_gpu_gemv(enc, xb, E.ENTRO_F32) - y_ref) <= (cols + 2) * 2.0 ** -24 * terms)
+    assert np.all(np.abs(_gpu_gemv(enc, xb, E.ENTRO_BF16) - y_ref) <= 2.0 ** -8 * np.abs(y_ref) + (cols + 2) * 2.0 ** -24 * terms)
+
+
+@pytest.mark.parametrize("bits,chunk,segments", [(8, 8192, 2700), (8, 1024, 17000), (4, 512, 41000), (8, 512, 49152), (8, 512, 49153)])
+def test_more_shared_segments_than_wavefronts_and_the_line_to_a_lane_each(bits, chunk, segments):
+    # (the prepared launch of the same tensor gives every segment a lane)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(segments)
+    w = torch.randn(segments * chunk, device=DEV, generator=gen)
+    d, q = E.compress_on_device(w, bits, E.ENTRO_ASYMMETRIC, chunk, return_q=True)
+    out = torch.zeros(q.numel(), dtype=torch.uint8, device=DEV)
+    E.entro_decode(d.ctensor(out), E.ENTRO_U8)
+    assert torch.equal(out, q)
+
+
 @pytest.mark.parametrize("bits,chunk", [(8, 4096), (8, 512), (4, 4096)])
 def test_segments_without_entry_points_whose_offsets_do_not_fit(bits, chunk):
     # a segment starts where the table says and holds the symbols that it holds, wherever the table puts its end
