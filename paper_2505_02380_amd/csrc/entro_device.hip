@@ -2196,8 +2196,14 @@ __global__ __launch_bounds__(64 * kShareWaves) void k_shared(const DevTensor t, 
         if (k < t.n_chunks) {
             const uint64_t left = t.n - static_cast<uint64_t>(k) * S;
             nsym = left < S ? static_cast<uint32_t>(left) : S;
-            r.base = t.offsets[k];
-            const uint64_t end = t.offsets[k + 1], bits = end > r.base ? end - r.base : 0;
+            r.base = seg_start(t, k);
+            uint64_t bits;
+            if (t.sub_shift) {
+                bits = t.sub[k];
+            } else {
+                const uint64_t end = t.offsets[k + 1];
+                bits = end > r.base ? end - r.base : 0;
+            }
             const uint64_t most = static_cast<uint64_t>(nsym) * ENTRO_MAX_CODE_LEN;
             span = static_cast<uint32_t>(bits < most ? bits : most);
         }
@@ -2564,9 +2570,9 @@ entro_status launch_fix_single(entro_dtype d, const DevTensor &dt, hipStream_t s
     return hip_ok(hipGetLastError(), "launch row-sum kernel") ? ENTRO_OK : ENTRO_ERR_DEVICE;
 }
 
-// A tensor without entry points in few segments: 8 to 64 lanes share one (k_shared), at about 64 symbols a lane.  A
-// wavefront's share of LDS is what its unit's symbols take, and its part of the stream at the tensor's mean rate and a
-// thirty-second more (a unit with more is read straight from memory).
+// A tensor in few segments, or few pieces between entry points: 4 to 64 lanes share one (k_shared), at about 64 symbols a
+// lane.  A wavefront's share of LDS is what its unit's symbols take, and its part of the stream at the tensor's mean rate and
+// a thirty-second more (a unit with more is read straight from memory).
 // A lane per segment takes 0.036 (4-bit) to 0.072 us (8-bit) for each of a segment's symbols, however many segments there
 // are until the device is full; k_shared 13.5 to 17.5 us for each 2^24 symbols of the tensor.  They meet at 50 to 65
 // thousand segments: three sixteenths of the lanes is a little less (and less again where LDS holds fewer than sixteen units).
@@ -2574,15 +2580,20 @@ entro_status launch_fix_single(entro_dtype d, const DevTensor &dt, hipStream_t s
 // -> 32.5; segments of 1024 49.1 -> 33.8, 64.8 -> 31.8, 84.8 -> 32.8; of 512, 32768 of them, 47.7 -> 33.9, 50.1 -> 31.4, 48.9
 // -> 32.2, and 131072 of them, which the rule leaves with a lane each, 57 against 86.  4 bits: bf16 62.4 -> 25.0, product
 // 159.4 -> 24.3; segments of 1024, 16384 x 4096 (65536, left with a lane each), 59 against 63.
+// Pieces between entry points, 2048 x 4096: of 512 symbols, 8 bits, to bf16 54.7 -> 28.4 us, bytes 53.5 -> 27.4, product 53.5
+// -> 27.9, 4 bits 36.4 -> 22.1; of 256 33.7 -> 28.4 and 26.7 -> 21.8, but the more bits a symbol takes, the fewer a lookup
+// answers: at 5.0 bits 35.6 -> 36.1 (and the product 34.2 -> 36.1), so they come here up to 4 bits.  Pieces of 128 do not:
+// 20.9 against 26.2 (256 x 4096).
 bool share_segments(entro_op op, uint64_t lane_slots, unsigned cus, const entro_tensor *t, const DevTensor &dt, Share *c) {
     const uint32_t S = dt.chunk_symbols;
-    if (t->sub_symbols || S % 128u != 0 || S < 8u * kShareSymbols || S > kShareMost) return false;
+    if (dt.sub_merge != 0 || S % 128u != 0 || S < (t->sub_symbols ? 4u : 8u) * kShareSymbols || S > kShareMost) return false;
     if (op == ENTRO_OP_GEMV && dt.cols % 8u != 0) return false;
-    c->part_shift = 3;
+    c->part_shift = 1;
     while (c->part_shift < 6u && (kShareSymbols << (c->part_shift + 1u)) <= S) ++c->part_shift;
     const uint32_t per = 64u >> c->part_shift, unit = S * per;
     c->units = (dt.n_chunks + per - 1u) / per;
     const double rate = std::min(static_cast<double>(dt.bits), 8.0 * dt.stream_bytes / static_cast<double>(dt.n));
+    if (t->sub_symbols && S < 8u * kShareSymbols && rate > 4.0) return false;
     const uint32_t copy = static_cast<uint32_t>(unit * rate / 8.0 * 33.0 / 32.0) + 16u;
     c->symbol_bytes = (unit / 16u * 17u + 15u) / 16u * 16u;
     c->wave_bytes = c->symbol_bytes + (copy + 15u) / 16u * 16u + 32u;

@@ -269,9 +269,11 @@ def test_runs_inside_segments_without_entry_points(bits, chunk, fraction, every)
             assert np.array_equal(_gpu_decode(enc, E.ENTRO_U4_PACKED), oracle.pack_u4(sym))
 
 
-@pytest.mark.parametrize("bits,chunk,cols", [(8, 512, 64), (8, 640, 72), (8, 1152, 4104), (8, 3968, 14336), (8, 8192, 3072), (4, 512, 200),
-                                             (4, 4096, 8), (4, 8192, 5000)])
-def test_segments_shared_by_lanes_every_output_and_product(bits, chunk, cols):
+@pytest.mark.parametrize("bits,chunk,cols,sub", [
+    (8, 512, 64, 0), (8, 640, 72, 0), (8, 1152, 4104, 0), (8, 3968, 14336, 0), (8, 8192, 3072, 0), (4, 512, 200, 0), (4, 4096, 8, 0),
+    (4, 8192, 5000, 0), (8, 4096, 4096, 256), (8, 1536, 72, 384), (8, 8192, 14336, 512), (8, 1024, 2048, 1024), (4, 4096, 3072, 256),
+    (4, 8192, 200, 1024)])
+def test_segments_shared_by_lanes_every_output_and_product(bits, chunk, cols, sub):
     """Rows shorter and longer than a wavefront's unit, segments of odd lengths, a run that keeps guesses out of step, codes
     longer than the tables, and a stretch of rare symbols whose stream is longer than the unit's copy holds."""
     rows = -(-(11 * chunk + 300) // cols)
@@ -281,7 +283,7 @@ def test_segments_shared_by_lanes_every_output_and_product(bits, chunk, cols):
     sym[chunk + 7: chunk + 7 + chunk // 2] = (top + 1) // 2
     sym[5 * chunk + 3: 6 * chunk + 9] = rng.integers(0, top + 1, chunk + 6)
     z = 100 if bits == 8 else 6
-    enc = _oracle_encoded(sym, bits, chunk, rows, cols, 0.25, z)
+    enc = _oracle_encoded(sym, bits, chunk, rows, cols, 0.25, z, sub)
     assert np.array_equal(_gpu_decode(enc, E.ENTRO_U8), sym)
     assert np.array_equal(_gpu_dequant(enc, E.ENTRO_F32), oracle.dequant_f32(sym, 0.25, z))
     assert np.array_equal(_gpu_dequant(enc, E.ENTRO_BF16), oracle.dequant_bf16(sym, 0.25, z))
