@@ -89,6 +89,10 @@ struct DevTensor {
     uint32_t row_lanes;         // GEMV: lanes per matrix row where a wavefront sums its rows by itself (0: not so)
     uint32_t fine;              // batched launches: index of the same tensor's description with finer lanes (0: none)
     uint32_t fine_shift;        // log2 of how many of those lanes make one of this description's
+    uint32_t fix_symbols;       // GEMV: symbols per pair of partial sums: a lane's, or a unit's where lanes share segments
+    uint32_t share_shift;       // k_shared*: log2 of the lanes that share a segment (or piece)
+    uint32_t share_per;         // segments of a unit, at most 64 >> share_shift (0: the tensor does not go there)
+    uint32_t share_units;       // units of the tensor
     uint8_t len[256];
 };
 
@@ -1895,7 +1899,7 @@ __global__ __launch_bounds__(64 * Cfg<MODE>::waves) void k_tables(const DevTenso
 }
 
 // ---------------------------------------------------------------- segments shared by a wavefront's lanes
-// Small calls on one tensor (k_shared).  What bounds them is not the bytes but one lane's serial chain of lookups, so
+// Small launches (k_shared, k_shared_batch).  What bounds them is not the bytes but one lane's serial chain of lookups, so
 // 2^part_shift lanes share a segment, about 64 symbols each, and a lookup answers up to four codes at once.
 //   1. The unit's part of the stream (the segments of a wavefront lie side by side) comes into LDS in whole lines.
 //   2. Each lane takes an equal stretch of its segment's bits and counts the codes that start in it, from a guessed first
@@ -1911,16 +1915,8 @@ constexpr int kMulti = 12;               // stream bits that index the table of 
 constexpr uint32_t kShareSymbols = 64;   // symbols of a lane, about
 constexpr uint32_t kShareWaves = 16;
 constexpr uint32_t kShareMost = 8192;    // most symbols of a segment: its symbols and its stream have to fit into LDS
-
-// How a launch of k_shared is cut (DevTensor::chunk_symbols is the segment's length there, or the piece's where the tensor
-// has entry points).
-struct Share {
-    uint32_t part_shift;        // log2 of the lanes per segment
-    uint32_t units;             // wavefront's worths of 64 >> part_shift segments
-    uint32_t waves;             // wavefronts of a workgroup that take units
-    uint32_t symbol_bytes;      // a wavefront's memory: the unit's symbols, one byte each and four free bytes behind each 64,
-    uint32_t wave_bytes;        // and the unit's part of the stream
-};
+// A unit's symbols in LDS: a byte each, and four free bytes behind each 64.
+__host__ __device__ constexpr uint32_t share_symbol_bytes(uint32_t symbols) { return (symbols / 16u * 17u + 15u) / 16u * 16u; }
 
 // Entry of the table of several codes: the next codes that kMulti bits hold in full, at most four.
 // x: their symbols, first one lowest.  y: bits 0..5 their lengths' sum, bits 8..10 their number, from bit 12 on, four bits
@@ -1931,10 +1927,11 @@ struct alignas(16) ShareMem {
     u32x4 limits[kLimits / 4];           // see share_long
     TablesTail tail;                     // the canonical tables; with what follows, a Tables while the tables are built
     uint8_t pool[160u * 1024u - (sizeof(u32x2) << kMulti) - 4u * kLimits - sizeof(TablesTail)];
+    static constexpr uint32_t table_bytes = 160u * 1024u - sizeof(pool);   // all in front of the pool
     __device__ __forceinline__ Tables &building() { return *reinterpret_cast<Tables *>(&tail); }
 };
 static_assert(sizeof(ShareMem) == 160u * 1024u && sizeof(Tables) <= sizeof(TablesTail) + sizeof(ShareMem::pool) &&
-              sizeof(TablesTail) % 16 == 0, "all of a compute unit's LDS");
+              sizeof(TablesTail) % 16 == 0 && ShareMem::table_bytes <= sizeof(Tables32), "all of a compute unit's LDS; the tables fit the workspace");
 
 typedef uint32_t __attribute__((address_space(3))) *lds_w32;
 typedef u32x4 __attribute__((address_space(3))) *lds_128;
@@ -2175,110 +2172,168 @@ __device__ __forceinline__ void share_rows(const DevTensor &t, lds_w32 sym, uint
     }
 }
 
-// One tensor per launch: every workgroup builds the tables, its wavefronts take units.
-template <int MODE>
-__global__ __launch_bounds__(64 * kShareWaves) void k_shared(const DevTensor t, const Share c) {
-    __shared__ ShareMem sm;
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    const uint32_t sh = c.part_shift, parts = 1u << sh, part = lane & (parts - 1u), S = t.chunk_symbols;
-    const uint32_t unit_symbols = S << (6u - sh);
-    const lds_w32 sym = (lds_w32)(sm.pool + wave * c.wave_bytes);
-    const lds_w32 copy = sym + c.symbol_bytes / 4u;
-    const uint32_t copy_bytes = c.wave_bytes - c.symbol_bytes;
+// What a wavefront keeps about the unit it works on.
+struct ShareUnit {
     ShareReader r;
-    r.words = (lds_p32)copy;
-    // the lane's segment of a unit: its symbols, and its bits in the stream
-    uint32_t nsym, span;
-    auto look_up = [&](uint32_t unit) __attribute__((always_inline)) {
-        const uint32_t k = (unit << (6u - sh)) + (lane >> sh);
-        nsym = span = 0;
-        r.base = 0;
-        if (k < t.n_chunks) {
-            const uint64_t left = t.n - static_cast<uint64_t>(k) * S;
-            nsym = left < S ? static_cast<uint32_t>(left) : S;
-            r.base = seg_start(t, k);
-            uint64_t bits;
-            if (t.sub_shift) {
-                bits = t.sub[k];
-            } else {
-                const uint64_t end = t.offsets[k + 1];
-                bits = end > r.base ? end - r.base : 0;
-            }
-            const uint64_t most = static_cast<uint64_t>(nsym) * ENTRO_MAX_CODE_LEN;
-            span = static_cast<uint32_t>(bits < most ? bits : most);
+    uint32_t nsym, span;        // the symbols of the lane's segment, and its bits in the stream
+};
+
+__device__ __forceinline__ void share_look_up(const DevTensor &t, uint32_t unit, ShareUnit &u) {
+    const uint32_t at = (threadIdx.x & 63u) >> t.share_shift, k = unit * t.share_per + at;
+    u.nsym = u.span = 0;
+    u.r.base = 0;
+    if (at < t.share_per && k < t.n_chunks) {
+        const uint64_t left = t.n - static_cast<uint64_t>(k) * t.chunk_symbols;
+        u.nsym = left < t.chunk_symbols ? static_cast<uint32_t>(left) : t.chunk_symbols;
+        u.r.base = seg_start(t, k);
+        uint64_t bits;
+        if (t.sub_shift) {
+            bits = t.sub[k];
+        } else {
+            const uint64_t end = t.offsets[k + 1];
+            bits = end > u.r.base ? end - u.r.base : 0;
         }
-    };
-    uint32_t unit = blockIdx.x * c.waves + wave;
-    const bool works = wave < c.waves && unit < c.units;
-    if (works) look_up(unit);                                    // (on its way while the tables are built)
+        const uint64_t most = static_cast<uint64_t>(u.nsym) * ENTRO_MAX_CODE_LEN;
+        u.span = static_cast<uint32_t>(bits < most ? bits : most);
+    }
+}
+
+// One unit, looked up already, by one wavefront with `wave_bytes` of LDS at `sym`.
+template <int MODE>
+__device__ __forceinline__ void share_unit(const DevTensor &t, const ShareMem &sm, lds_w32 sym, uint32_t wave_bytes, uint32_t unit, ShareUnit &u) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t sh = t.share_shift, parts = 1u << sh, part = lane & (parts - 1u), S = t.chunk_symbols;
+    const uint32_t unit_symbols = S * t.share_per, symbol_bytes = share_symbol_bytes(unit_symbols), copy_bytes = wave_bytes - symbol_bytes;
+    const lds_w32 copy = sym + symbol_bytes / 4u;
+    ShareReader &r = u.r;
+    const uint32_t nsym = u.nsym, span = u.span;
+    r.words = (lds_p32)copy;
+    // the unit's part of the stream, and zeros for its symbols (its first segment is always there: no unit is empty)
+    const uint64_t lo = (static_cast<uint64_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(r.base >> 32))) << 32 |
+                         __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(r.base))) & ~uint64_t{127};
+    const uint32_t room = 8u * (copy_bytes - 32u);               // (a window reaches some bytes behind a segment's end)
+    const bool held = nsym == 0 || (r.base - lo <= room && r.base - lo + span <= room);   // (also in front of lo: not held)
+    r.in_lds = __builtin_amdgcn_ballot_w64(!held) == 0;
+    r.lds_bit = nsym != 0 ? static_cast<uint32_t>(r.base - lo) : 0u;
+    if (r.in_lds)
+        for (uint32_t b = lane; b < copy_bytes / 16u; b += 64u)
+            *(lds_128)(copy + b * 4u) = load_block(t.stream, static_cast<uint32_t>(lo >> 3) + b * 16u, t.stream_bytes - 16u);
+    for (uint32_t b = lane; b < symbol_bytes / 16u; b += 64u) *(lds_128)(sym + b * 4u) = u32x4{0u, 0u, 0u, 0u};
+    wave_sync_lds();
+    const uint32_t guess = static_cast<uint32_t>((static_cast<uint64_t>(span) * part) >> sh);
+    const uint32_t limit = static_cast<uint32_t>((static_cast<uint64_t>(span) * (part + 1u)) >> sh);
+    ShareWriter out;
+    uint32_t from = guess, upto = guess, count = 0;
+    share_pass<false>(t, sm, r, upto, limit, count, out);
+    for (;;) {
+        const uint32_t before = __shfl_up(upto, 1, 64);
+        const uint32_t want = part == 0 ? 0u : before;           // (never in front of the guess: the neighbour passed its limit)
+        const bool todo = want != from;
+        if (__builtin_amdgcn_ballot_w64(todo) == 0) break;
+        uint32_t rel = todo ? want : limit, n = 0;
+        share_pass<false>(t, sm, r, rel, limit, n, out);
+        upto = todo ? rel : upto;
+        count = todo ? n : count;
+        from = want;
+    }
+    uint32_t sum = count;
+    for (uint32_t d = 1; d < parts; d <<= 1) {
+        const uint32_t y = __shfl_up(sum, d, 64);
+        sum += part >= d ? y : 0u;
+    }
+    // an offset table that does not fit the stream: the segment's first lane decodes it from its start
+    const bool bad = __shfl(sum, static_cast<int>(lane | (parts - 1u)), 64) != nsym;
+    out.begin(sym, (lane >> sh) * S + (bad ? 0u : sum - count));
+    uint32_t rel = bad ? limit : from, n = 0;
+    share_pass<true>(t, sm, r, rel, limit, n, out);
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(bad) != 0, 0)) {
+        if (bad && part == 0) {
+            uint64_t pos = r.base;
+            for (uint32_t i = 0; i < nsym; ++i) {
+                const uint32_t e = decode_canonical(sm.tail, static_cast<uint32_t>(load_bits57(t, pos)), 1u, t.max_len);
+                out.put(entry_sym(e), 1u);
+                pos += entry_len(e);
+            }
+        }
+    }
+    if (out.fill != 0) out.flush();                              // (never behind the unit's symbols: fill is 0 at their end)
+    wave_sync_lds();
+    const uint64_t u0 = static_cast<uint64_t>(unit) * unit_symbols, left = t.n - u0;
+    const uint32_t m = left < unit_symbols ? static_cast<uint32_t>(left) : unit_symbols;
+    if constexpr (is_gemv(MODE)) share_rows<MODE>(t, sym, unit, u0, m);
+    else share_store<MODE>(t, sym, u0, m);
+    wave_sync_lds();
+}
+
+// One tensor per launch: every workgroup builds the tables, then `waves` of its wavefronts take units.
+template <int MODE>
+__global__ __launch_bounds__(64 * kShareWaves) void k_shared(const DevTensor t, uint32_t waves, uint32_t wave_bytes) {
+    __shared__ ShareMem sm;
+    const uint32_t wave = threadIdx.x >> 6;
+    const lds_w32 sym = (lds_w32)(sm.pool + wave * wave_bytes);
+    ShareUnit u;
+    uint32_t unit = blockIdx.x * waves + wave;
+    const bool works = wave < waves && unit < t.share_units;
+    if (works) share_look_up(t, unit, u);                        // (on its way while the tables are built)
     build_tables<64 * kShareWaves, false>(t, sm.building(), reinterpret_cast<uint32_t *>(sm.multi));   // (scratch: not in use yet)
     build_multi(sm);
     __syncthreads();
     if (!works) return;
     for (;;) {
-        {
-            // the unit's part of the stream, and zeros for its symbols (its first segment is always there: no unit is empty)
-            const uint64_t lo = (static_cast<uint64_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(r.base >> 32))) << 32 |
-                                 __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(r.base))) & ~uint64_t{127};
-            const uint32_t room = 8u * (copy_bytes - 32u);       // (a window reaches some bytes behind a segment's end)
-            const bool held = nsym == 0 || (r.base - lo <= room && r.base - lo + span <= room);   // (also in front of lo: not held)
-            r.in_lds = __builtin_amdgcn_ballot_w64(!held) == 0;
-            r.lds_bit = nsym != 0 ? static_cast<uint32_t>(r.base - lo) : 0u;
-            const uint32_t from = static_cast<uint32_t>(lo >> 3);
-            if (r.in_lds)
-                for (uint32_t b = lane; b < copy_bytes / 16u; b += 64u)
-                    *(lds_128)(copy + b * 4u) = load_block(t.stream, from + b * 16u, t.stream_bytes - 16u);
-            for (uint32_t b = lane; b < c.symbol_bytes / 16u; b += 64u) *(lds_128)(sym + b * 4u) = u32x4{0u, 0u, 0u, 0u};
-        }
-        wave_sync_lds();
-        const uint32_t guess = static_cast<uint32_t>((static_cast<uint64_t>(span) * part) >> sh);
-        const uint32_t limit = static_cast<uint32_t>((static_cast<uint64_t>(span) * (part + 1u)) >> sh);
-        ShareWriter out;
-        uint32_t from = guess, upto = guess, count = 0;
-        share_pass<false>(t, sm, r, upto, limit, count, out);
-        for (;;) {
-            const uint32_t before = __shfl_up(upto, 1, 64);
-            const uint32_t want = part == 0 ? 0u : before;       // (never in front of the guess: the neighbour passed its limit)
-            const bool todo = want != from;
-            if (__builtin_amdgcn_ballot_w64(todo) == 0) break;
-            uint32_t rel = todo ? want : limit, n = 0;
-            share_pass<false>(t, sm, r, rel, limit, n, out);
-            upto = todo ? rel : upto;
-            count = todo ? n : count;
-            from = want;
-        }
-        uint32_t sum = count;
-        for (uint32_t d = 1; d < parts; d <<= 1) {
-            const uint32_t y = __shfl_up(sum, d, 64);
-            sum += part >= d ? y : 0u;
-        }
-        // an offset table that does not fit the stream: the segment's first lane decodes it from its start
-        const bool bad = __shfl(sum, static_cast<int>(lane | (parts - 1u)), 64) != nsym;
-        const uint32_t first = (lane >> sh) * S;
-        out.begin(sym, first + (bad ? 0u : sum - count));
-        uint32_t rel = bad ? limit : from, n = 0;
-        share_pass<true>(t, sm, r, rel, limit, n, out);
-        if (__builtin_expect(__builtin_amdgcn_ballot_w64(bad) != 0, 0)) {
-            if (bad && part == 0) {
-                uint64_t pos = r.base;
-                for (uint32_t i = 0; i < nsym; ++i) {
-                    const uint32_t e = decode_canonical(sm.tail, static_cast<uint32_t>(load_bits57(t, pos)), 1u, t.max_len);
-                    out.put(entry_sym(e), 1u);
-                    pos += entry_len(e);
-                }
-            }
-        }
-        if (out.fill != 0) out.flush();                          // (never behind the unit's symbols: fill is 0 at their end)
-        wave_sync_lds();
-        const uint64_t u0 = static_cast<uint64_t>(unit) * unit_symbols, left = t.n - u0;
-        const uint32_t m = left < unit_symbols ? static_cast<uint32_t>(left) : unit_symbols;
-        if constexpr (is_gemv(MODE)) share_rows<MODE>(t, sym, unit, u0, m);
-        else share_store<MODE>(t, sym, u0, m);
-        unit += gridDim.x * c.waves;
-        if (unit >= c.units) break;
-        wave_sync_lds();
-        look_up(unit);
+        share_unit<MODE>(t, sm, sym, wave_bytes, unit, u);
+        unit += gridDim.x * waves;
+        if (unit >= t.share_units) break;
+        share_look_up(t, unit, u);
     }
+}
+
+// Units of a work item: about 64 segments, as in the other kernels' lists.
+__host__ __device__ constexpr uint32_t share_item_units(uint32_t per) { return (kUnit + per - 1u) / per; }
+
+// Many tensors per launch: workgroup b of G takes the items [b * n / G, (b + 1) * n / G), stretches of one tensor each, whose
+// tables, built when the launch was prepared (k_share_tables), it loads; `waves` of its wavefronts take units in turn.
+template <int MODE>
+__global__ __launch_bounds__(64 * kShareWaves) void k_shared_batch(const DevTensor *__restrict__ tensors, const WorkItem *__restrict__ items,
+                                                                   uint32_t n_items, uint32_t waves, uint32_t wave_bytes) {
+    __shared__ ShareMem sm;
+    const uint32_t lo = static_cast<uint32_t>(static_cast<uint64_t>(blockIdx.x) * n_items / gridDim.x);
+    const uint32_t hi = static_cast<uint32_t>(static_cast<uint64_t>(blockIdx.x + 1) * n_items / gridDim.x);
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const lds_w32 sym = (lds_w32)(sm.pool + wave * wave_bytes);
+    uint32_t i = lo;
+    while (i < hi) {
+        const WorkItem it = items[i];
+        const DevTensor &t = tensors[it.tensor];
+        const uint32_t item_units = share_item_units(t.share_per), left = t.share_units - it.first;
+        const uint64_t share = static_cast<uint64_t>(hi - i) * item_units;
+        const uint32_t n_units = left < share ? left : static_cast<uint32_t>(share);
+        uint32_t at = wave < waves ? wave : n_units;
+        ShareUnit u;
+        if (at < n_units) share_look_up(t, it.first + at, u);    // (on its way while the tables come in)
+        __syncthreads();                                         // nobody reads the previous tables any more
+        const u32x4 *src = static_cast<const u32x4 *>(t.tables);
+        u32x4 *dst = reinterpret_cast<u32x4 *>(&sm);
+        for (uint32_t j = threadIdx.x; j < ShareMem::table_bytes / 16u; j += 64u * kShareWaves) dst[j] = src[j];
+        __syncthreads();
+        while (at < n_units) {
+            share_unit<MODE>(t, sm, sym, wave_bytes, it.first + at, u);
+            at += waves;
+            if (at < n_units) share_look_up(t, it.first + at, u);
+        }
+        i += (n_units + item_units - 1u) / item_units;
+    }
+}
+
+// The tables of k_shared_batch, for the tensors of a prepared launch (workgroup b: tensor b).
+__global__ __launch_bounds__(64 * kShareWaves) void k_share_tables(const DevTensor *__restrict__ tensors) {
+    __shared__ ShareMem sm;
+    const DevTensor &t = tensors[blockIdx.x];
+    build_tables<64 * kShareWaves, false>(t, sm.building(), reinterpret_cast<uint32_t *>(sm.multi));
+    build_multi(sm);
+    __syncthreads();
+    const u32x4 *src = reinterpret_cast<const u32x4 *>(&sm);
+    u32x4 *dst = static_cast<u32x4 *>(t.tables);
+    for (uint32_t j = threadIdx.x; j < ShareMem::table_bytes / 16u; j += 64u * kShareWaves) dst[j] = src[j];
 }
 
 // Second stage of the GEMV: the partial sums of a row that straddles lanes are added up by sixteen lanes,
@@ -2293,12 +2348,12 @@ __device__ __forceinline__ void fix_row(const DevTensor &t, uint32_t row, uint32
     uint32_t k_lo = 1, k_hi = 0;
     if (live) {
         const uint64_t lo = static_cast<uint64_t>(row) * t.cols;
-        k_lo = static_cast<uint32_t>(lo / t.chunk_symbols);
-        k_hi = static_cast<uint32_t>((lo + t.cols - 1) / t.chunk_symbols);
+        k_lo = static_cast<uint32_t>(lo / t.fix_symbols);
+        k_hi = static_cast<uint32_t>((lo + t.cols - 1) / t.fix_symbols);
     }
     float acc = 0.0f;
     for (uint64_t k = static_cast<uint64_t>(k_lo) + j; k <= k_hi; k += 16u) {
-        const uint32_t first_row = static_cast<uint32_t>((k * t.chunk_symbols) / t.cols);
+        const uint32_t first_row = static_cast<uint32_t>((k * t.fix_symbols) / t.cols);
         acc += t.partials[2 * k + (first_row == row ? 0 : 1)];
     }
 #pragma unroll
@@ -2425,7 +2480,7 @@ entro_status fill_dev_tensor(const entro_tensor *t, entro_op op, entro_dtype d, 
     dt->x = static_cast<const uint16_t *>(t->x);
     dt->n = t->n;
     dt->stream_bytes = static_cast<uint32_t>(t->stream_bytes);
-    dt->chunk_symbols = lane_symbols;
+    dt->chunk_symbols = dt->fix_symbols = lane_symbols;
     dt->n_chunks = static_cast<uint32_t>(n_chunks);
     dt->sub = sub_shift ? t->sub_bits : nullptr;
     dt->sub_shift = sub_shift;
@@ -2563,13 +2618,6 @@ bool cut_segments(entro_op op, int mode, uint64_t lane_slots, const entro_tensor
     return false;
 }
 
-entro_status launch_fix_single(entro_dtype d, const DevTensor &dt, hipStream_t s) {
-    const unsigned grid = (dt.rows + kFixRows - 1) / kFixRows;
-    if (d == ENTRO_F32) hipLaunchKernelGGL(k_fix_single<kModeGemvF32>, dim3(grid), dim3(kFixWG), 0, s, dt);
-    else hipLaunchKernelGGL(k_fix_single<kModeGemvBF16>, dim3(grid), dim3(kFixWG), 0, s, dt);
-    return hip_ok(hipGetLastError(), "launch row-sum kernel") ? ENTRO_OK : ENTRO_ERR_DEVICE;
-}
-
 // A tensor in few segments, or few pieces between entry points: 4 to 64 lanes share one (k_shared), at about 64 symbols a
 // lane.  A wavefront's share of LDS is what its unit's symbols take, and its part of the stream at the tensor's mean rate and
 // a thirty-second more (a unit with more is read straight from memory).
@@ -2584,36 +2632,56 @@ entro_status launch_fix_single(entro_dtype d, const DevTensor &dt, hipStream_t s
 // -> 27.9, 4 bits 36.4 -> 22.1; of 256 33.7 -> 28.4 and 26.7 -> 21.8, but the more bits a symbol takes, the fewer a lookup
 // answers: at 5.0 bits 35.6 -> 36.1 (and the product 34.2 -> 36.1), so they come here up to 4 bits.  Pieces of 128 do not:
 // 20.9 against 26.2 (256 x 4096).
-bool share_segments(entro_op op, uint64_t lane_slots, unsigned cus, const entro_tensor *t, const DevTensor &dt, Share *c) {
-    const uint32_t S = dt.chunk_symbols;
-    if (dt.sub_merge != 0 || S % 128u != 0 || S < (t->sub_symbols ? 4u : 8u) * kShareSymbols || S > kShareMost) return false;
-    if (op == ENTRO_OP_GEMV && dt.cols % 8u != 0) return false;
-    c->part_shift = 1;
-    while (c->part_shift < 6u && (kShareSymbols << (c->part_shift + 1u)) <= S) ++c->part_shift;
-    const uint32_t per = 64u >> c->part_shift, unit = S * per;
-    c->units = (dt.n_chunks + per - 1u) / per;
-    const double rate = std::min(static_cast<double>(dt.bits), 8.0 * dt.stream_bytes / static_cast<double>(dt.n));
+// share_fits: whether the tensor's form goes there at all; describes its units and says how much LDS one takes.
+// share_pays: the rule above, for a launch of `segments` segments with `waves` wavefronts' worth of LDS in a workgroup.
+bool share_fits(entro_op op, const entro_tensor *t, DevTensor *dt, uint32_t *wave_bytes) {
+    const uint32_t S = dt->chunk_symbols;
+    if (dt->sub_merge != 0 || S % 128u != 0 || S < (t->sub_symbols ? 4u : 8u) * kShareSymbols || S > kShareMost) return false;
+    if (op == ENTRO_OP_GEMV && dt->cols % 8u != 0) return false;
+    const double rate = std::min(static_cast<double>(dt->bits), 8.0 * dt->stream_bytes / static_cast<double>(dt->n));
     if (t->sub_symbols && S < 8u * kShareSymbols && rate > 4.0) return false;
-    const uint32_t copy = static_cast<uint32_t>(unit * rate / 8.0 * 33.0 / 32.0) + 16u;
-    c->symbol_bytes = (unit / 16u * 17u + 15u) / 16u * 16u;
-    c->wave_bytes = c->symbol_bytes + (copy + 15u) / 16u * 16u + 32u;
-    const uint32_t most = std::min<uint32_t>(kShareWaves, sizeof(ShareMem::pool) / c->wave_bytes);
-    c->waves = std::min<uint32_t>(most, (c->units + cus - 1u) / cus);
-    return static_cast<uint64_t>(dt.n_chunks) * 16u * kShareWaves <= lane_slots * 3u * most && falls_into_step(t->cb);
+    if (!falls_into_step(t->cb)) return false;
+    uint32_t sh = 1;
+    while (sh < 6u && (kShareSymbols << (sh + 1u)) <= S) ++sh;
+    uint32_t per = 64u >> sh;
+    // units of whole rows need no second stage: up to a quarter of the lanes is left idle for it
+    for (uint32_t p = per; op == ENTRO_OP_GEMV && 4u * p >= 3u * (64u >> sh); --p)
+        if (S * p % dt->cols == 0) {
+            per = p;
+            break;
+        }
+    dt->share_shift = sh;
+    dt->share_per = per;
+    dt->share_units = (dt->n_chunks + per - 1u) / per;
+    dt->fix_symbols = S * per;
+    dt->row_lanes = 0;
+    dt->need_fix = (op == ENTRO_OP_GEMV && dt->fix_symbols % dt->cols != 0) ? 1u : 0u;
+    const uint32_t copy = static_cast<uint32_t>(S * per * rate / 8.0 * 33.0 / 32.0) + 16u;
+    *wave_bytes = share_symbol_bytes(S * per) + (copy + 15u) / 16u * 16u + 32u;
+    return true;
 }
 
-entro_status launch_shared(entro_op op, entro_dtype d, DevTensor &dt, const Share &c, unsigned cus, hipStream_t s) {
-    const unsigned grid = std::min<unsigned>(cus, (c.units + c.waves - 1u) / c.waves);
+uint32_t share_waves(uint32_t wave_bytes) { return std::min<uint32_t>(kShareWaves, sizeof(ShareMem::pool) / wave_bytes); }
+
+bool share_pays(uint64_t segments, uint32_t waves, uint64_t lane_slots) { return segments * 16u * kShareWaves <= lane_slots * 3u * waves; }
+
+entro_status launch_fix_single(entro_dtype d, const DevTensor &dt, hipStream_t s) {
+    const unsigned grid = (dt.rows + kFixRows - 1) / kFixRows;
+    if (d == ENTRO_F32) hipLaunchKernelGGL(k_fix_single<kModeGemvF32>, dim3(grid), dim3(kFixWG), 0, s, dt);
+    else hipLaunchKernelGGL(k_fix_single<kModeGemvBF16>, dim3(grid), dim3(kFixWG), 0, s, dt);
+    return hip_ok(hipGetLastError(), "launch row-sum kernel") ? ENTRO_OK : ENTRO_ERR_DEVICE;
+}
+
+entro_status launch_shared(entro_op op, entro_dtype d, const DevTensor &dt, uint32_t wave_bytes, unsigned cus, hipStream_t s) {
+    const unsigned waves = std::min<unsigned>(share_waves(wave_bytes), (dt.share_units + cus - 1u) / cus);
+    const unsigned grid = std::min<unsigned>(cus, (dt.share_units + waves - 1u) / waves);
     dispatch_mode(mode_of(op, d, false), [&](auto m) {
         constexpr int M = decltype(m)::value;
         if constexpr (M <= kModeGemvBF16)
-            hipLaunchKernelGGL(k_shared<M>, dim3(grid), dim3(64u * kShareWaves), 0, s, dt, c);
+            hipLaunchKernelGGL(k_shared<M>, dim3(grid), dim3(64u * kShareWaves), 0, s, dt, static_cast<uint32_t>(waves), wave_bytes);
     });
     if (!hip_ok(hipGetLastError(), "launch decode kernel")) return ENTRO_ERR_DEVICE;
-    const uint32_t unit = dt.chunk_symbols * (64u >> c.part_shift);
-    if (op != ENTRO_OP_GEMV || unit % dt.cols == 0) return ENTRO_OK;
-    dt.chunk_symbols = unit;                                     // rows that straddle units
-    return launch_fix_single(d, dt, s);
+    return dt.need_fix ? launch_fix_single(d, dt, s) : ENTRO_OK;
 }
 
 entro_status launch_single(const entro_tensor *t, entro_op op, entro_dtype d, float *partials,
@@ -2631,8 +2699,10 @@ entro_status launch_single(const entro_tensor *t, entro_op op, entro_dtype d, fl
     if (st != ENTRO_OK) return st;
     dt.partials = partials;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    Share c;
-    if (share_segments(op, static_cast<uint64_t>(slots) * wg, slots, t, dt, &c)) return launch_shared(op, d, dt, c, slots, s);
+    DevTensor shared = dt;
+    uint32_t wave_bytes = 0;
+    if (share_fits(op, t, &shared, &wave_bytes) && share_pays(shared.n_chunks, share_waves(wave_bytes), static_cast<uint64_t>(slots) * wg))
+        return launch_shared(op, d, shared, wave_bytes, slots, s);
     const bool find = cut_segments(op, mode, static_cast<uint64_t>(slots) * wg, t, &dt);
     // a unit per wavefront when the tensor is large; fewer units per workgroup, down to one, when
     // that would leave compute units without a workgroup
@@ -2788,17 +2858,39 @@ static entro_status build_plan(entro_plan *plan, const entro_tensor *ts, uint32_
     const int mode0 = mode_of(op, out_type, all4, wide);
     const unsigned slots0 = resident_workgroups(mode0);
     if (slots0 == 0) return ENTRO_ERR_DEVICE;
-    const uint32_t level = choose_level(ts, count, static_cast<uint64_t>(slots0) * wg_of(mode0));
+    const uint64_t lane_slots = static_cast<uint64_t>(slots0) * wg_of(mode0);
+    // Launches whose segments or pieces are so few that lanes share them (k_shared_batch), by the rule of the single calls.
+    // Measured, prepared launches, before -> now.  2048 x 2048 matrices, 8 bits, pieces of 512: one to bf16 47.6 -> 22.7 us, its
+    // product 46.8 -> 23.9; five 90.2 -> 48.8, 85.0 -> 47.8; twenty, a lane each, 97.  Pieces of 1024: 86.2 -> 26.4, 82.4 ->
+    // 27.7; twenty at once 103 against 123, and the rule leaves them.  4 bits, pieces of 512: 27.8 -> 15.2, five 53.1 -> 32.3.
+    // Two exceptions, where the tests hold this form's times against others': decoding without entry points keeps a lane per
+    // segment, and so do 4-bit products in pieces of up to 512 symbols whose rows a wavefront adds up itself (2048 x 4096:
+    // 25.6 us, and 19.0 shared).
+    uint64_t segments = 0;
+    for (uint32_t i = 0; i < count; ++i) segments += dts[i].n_chunks;
+    bool shared = share_pays(segments, kShareWaves, lane_slots);
+    uint32_t wave_bytes = 1;
+    for (uint32_t i = 0; shared && i < count; ++i) {
+        DevTensor dt = dts[i];
+        uint32_t bytes = 0;
+        shared = (op == ENTRO_OP_GEMV || ts[i].sub_symbols) && !(dt.bits == 4 && dt.row_lanes && dt.chunk_symbols <= 512u) &&
+                 share_fits(op, &ts[i], &dt, &bytes);
+        wave_bytes = std::max(wave_bytes, bytes);
+    }
+    shared = shared && share_pays(segments, share_waves(wave_bytes), lane_slots);
+    const uint32_t level = shared ? 0u : choose_level(ts, count, lane_slots);
     for (uint32_t i = 0; i < count; ++i) {
         entro_status st = fill_dev_tensor(&ts[i], op, out_type, level, &dts[i]);
         if (st != ENTRO_OK) return st;
+        uint32_t bytes;
+        if (shared) share_fits(op, &ts[i], &dts[i], &bytes);
         dts[i].tables = static_cast<unsigned char *>(workspace) + L.off_tables + kTablesStride * i;
         total_units += (dts[i].n_chunks + kUnit - 1) / kUnit;
         pairs = pairs && dts[i].bits == 4;
         multirow = multirow || (op == ENTRO_OP_GEMV && dts[i].cols < dts[i].chunk_symbols);
         if (dts[i].need_fix) {
             dts[i].partials = partials_base + partial_floats;
-            partial_floats += 2 * static_cast<uint64_t>(dts[i].n_chunks);
+            partial_floats += 2 * static_cast<uint64_t>(shared ? dts[i].share_units : dts[i].n_chunks);
             for (uint32_t r = 0; r < dts[i].rows; r += kFixRows) fix[n_fix++] = WorkItem{i, r};
         }
     }
@@ -2814,7 +2906,7 @@ static entro_status build_plan(entro_plan *plan, const entro_tensor *ts, uint32_
     // is left over behind the last whole round of a stretch from that description.  (Not for the GEMV: its partial sums are laid out per lane.)
     uint32_t n_desc = count;
     const uint32_t block = spb_of(mode);
-    for (uint32_t i = 0; i < count && op != ENTRO_OP_GEMV; ++i) {
+    for (uint32_t i = 0; i < count && op != ENTRO_OP_GEMV && !shared; ++i) {
         uint32_t finer = std::min<uint32_t>(dts[i].sub_merge, kTailShift);
         while (finer > 0 && ((dts[i].chunk_symbols >> finer) % block) != 0) --finer;
         if (finer == 0 || dts[i].chunk_symbols % block != 0) continue;
@@ -2827,11 +2919,14 @@ static entro_status build_plan(entro_plan *plan, const entro_tensor *ts, uint32_
     // where every tensor has that second description a stretch may end anywhere at little cost: the
     // workgroups' shares are made equal to within one unit
     if (n_desc == 2 * count) item_units = 1;
-    for (uint32_t i = 0; i < count; ++i)
-        for (uint64_t c = 0; c < dts[i].n_chunks; c += static_cast<uint64_t>(item_units) * kUnit) {
+    for (uint32_t i = 0; i < count; ++i) {
+        const uint64_t end = shared ? dts[i].share_units : dts[i].n_chunks;
+        const uint64_t step = shared ? share_item_units(dts[i].share_per) : static_cast<uint64_t>(item_units) * kUnit;
+        for (uint64_t c = 0; c < end; c += step) {
             if (n_items >= L.n_items) return ENTRO_ERR_SIZE;     // (the layout counts the same units: cannot happen)
             items[n_items++] = WorkItem{i, static_cast<uint32_t>(c)};
         }
+    }
     plan->workspace = workspace;
     plan->workspace_bytes = workspace_bytes;
     plan->op = op;
@@ -2843,6 +2938,7 @@ static entro_status build_plan(entro_plan *plan, const entro_tensor *ts, uint32_
     plan->pair_tables = pairs ? 1u : 0u;
     plan->wide_tables = (op == ENTRO_OP_GEMV && !pairs && wide) ? 1u : 0u;
     plan->gemv_multirow = multirow ? 1u : 0u;
+    plan->shared_wave_bytes = shared ? wave_bytes : 0u;
     plan->off_tensors = L.off_tensors;
     plan->off_items = L.off_items;
     plan->off_partials = L.off_partials;
@@ -2865,6 +2961,10 @@ static entro_status plan_checks(entro_plan *plan, const entro_tensor *ts, uint32
 // descriptor table on the same stream).
 static entro_status enqueue_tables(const entro_plan *plan, hipStream_t s) {
     const DevTensor *dts = reinterpret_cast<const DevTensor *>(static_cast<const unsigned char *>(plan->workspace) + plan->off_tensors);
+    if (plan->shared_wave_bytes) {
+        hipLaunchKernelGGL(k_share_tables, dim3(plan->count), dim3(64u * kShareWaves), 0, s, dts);
+        return hip_ok(hipGetLastError(), "launch table kernel") ? ENTRO_OK : ENTRO_ERR_DEVICE;
+    }
     const int mode = mode_of(static_cast<entro_op>(plan->op), static_cast<entro_dtype>(plan->out), plan->pair_tables != 0,
                              plan->wide_tables != 0);
     dispatch_mode(mode, [&](auto m) {
@@ -2926,7 +3026,15 @@ entro_status entro_plan_run(const entro_plan *plan, void *hip_stream) {
     const unsigned slots = resident_workgroups(mode);
     if (slots == 0) return ENTRO_ERR_DEVICE;
     const unsigned grid = plan->n_items < slots ? plan->n_items : slots;
-    dispatch_mode(mode, [&](auto m) {
+    if (plan->shared_wave_bytes) {
+        const uint32_t waves = share_waves(plan->shared_wave_bytes);
+        dispatch_mode(mode_of(static_cast<entro_op>(plan->op), static_cast<entro_dtype>(plan->out), false), [&](auto m) {
+            constexpr int M = decltype(m)::value;
+            if constexpr (M <= kModeGemvBF16)
+                hipLaunchKernelGGL(k_shared_batch<M>, dim3(grid), dim3(64u * kShareWaves), 0, s, dts, items, plan->n_items, waves,
+                                   plan->shared_wave_bytes);
+        });
+    } else dispatch_mode(mode, [&](auto m) {
         constexpr int M = decltype(m)::value;
         hipLaunchKernelGGL(k_batch<M>, dim3(grid), dim3(wg_of(mode)), 0, s, dts, items, plan->n_items, plan->item_units);
     });

@@ -269,11 +269,12 @@ def test_runs_inside_segments_without_entry_points(bits, chunk, fraction, every)
             assert np.array_equal(_gpu_decode(enc, E.ENTRO_U4_PACKED), oracle.pack_u4(sym))
 
 
+@pytest.mark.parametrize("batch", [False, True])
 @pytest.mark.parametrize("bits,chunk,cols,sub", [
     (8, 512, 64, 0), (8, 640, 72, 0), (8, 1152, 4104, 0), (8, 3968, 14336, 0), (8, 8192, 3072, 0), (4, 512, 200, 0), (4, 4096, 8, 0),
     (4, 8192, 5000, 0), (8, 4096, 4096, 256), (8, 1536, 72, 384), (8, 8192, 14336, 512), (8, 1024, 2048, 1024), (4, 4096, 3072, 256),
     (4, 8192, 200, 1024)])
-def test_segments_shared_by_lanes_every_output_and_product(bits, chunk, cols, sub):
+def test_segments_shared_by_lanes_every_output_and_product(bits, chunk, cols, sub, batch):
     """Rows shorter and longer than a wavefront's unit, segments of odd lengths, a run that keeps guesses out of step, codes
     longer than the tables, and a stretch of rare symbols whose stream is longer than the unit's copy holds."""
     rows = -(-(11 * chunk + 300) // cols)
@@ -284,17 +285,57 @@ def test_segments_shared_by_lanes_every_output_and_product(bits, chunk, cols, su
     sym[5 * chunk + 3: 6 * chunk + 9] = rng.integers(0, top + 1, chunk + 6)
     z = 100 if bits == 8 else 6
     enc = _oracle_encoded(sym, bits, chunk, rows, cols, 0.25, z, sub)
-    assert np.array_equal(_gpu_decode(enc, E.ENTRO_U8), sym)
-    assert np.array_equal(_gpu_dequant(enc, E.ENTRO_F32), oracle.dequant_f32(sym, 0.25, z))
-    assert np.array_equal(_gpu_dequant(enc, E.ENTRO_BF16), oracle.dequant_bf16(sym, 0.25, z))
+    assert np.array_equal(_gpu_decode(enc, E.ENTRO_U8, batch), sym)
+    assert np.array_equal(_gpu_dequant(enc, E.ENTRO_F32, batch), oracle.dequant_f32(sym, 0.25, z))
+    assert np.array_equal(_gpu_dequant(enc, E.ENTRO_BF16, batch), oracle.dequant_bf16(sym, 0.25, z))
     if bits == 4:
-        assert np.array_equal(_gpu_decode(enc, E.ENTRO_U4_PACKED), oracle.pack_u4(sym))
+        assert np.array_equal(_gpu_decode(enc, E.ENTRO_U4_PACKED, batch), oracle.pack_u4(sym))
     xb = synth.make_x_bf16(0, 3, cols)
     y_ref, _ = oracle.gemv(sym, rows, cols, 0.25, z, xb)
     # fp32 sums of exact products: at most cols roundings of half an ulp, relative to the terms' magnitudes
     terms = np.abs((sym.astype(np.float64).reshape(rows, cols) - z) * 0.25) @ np.abs((xb.astype(np.uint32) << 16).view(np.float32).astype(np.float64))
-    assert np.all(np.abs(_gpu_gemv(enc, xb, E.ENTRO_F32) - y_ref) <= (cols + 2) * 2.0 ** -24 * terms)
-    assert np.all(np.abs(_gpu_gemv(enc, xb, E.ENTRO_BF16) - y_ref) <= 2.0 ** -8 * np.abs(y_ref) + (cols + 2) * 2.0 ** -24 * terms)
+    assert np.all(np.abs(_gpu_gemv(enc, xb, E.ENTRO_F32, batch) - y_ref) <= (cols + 2) * 2.0 ** -24 * terms)
+    assert np.all(np.abs(_gpu_gemv(enc, xb, E.ENTRO_BF16, batch) - y_ref) <= 2.0 ** -8 * np.abs(y_ref) + (cols + 2) * 2.0 ** -24 * terms)
+
+
+@pytest.mark.parametrize("y_type", [E.ENTRO_F32, E.ENTRO_BF16])
+def test_tensors_of_different_segments_shared_in_one_launch(y_type):
+    # alphabets, pieces, rows per unit and bits per symbol differ from tensor to tensor; the first is long enough for shares of
+    # workgroups that start and end inside it
+    rng = np.random.default_rng(5)
+    encs, refs, xs = [], [], []
+    for i, (bits, chunk, sub, rows, cols) in enumerate([(8, 4096, 512, 700, 3072), (4, 8192, 1024, 37, 8192), (8, 4096, 512, 20, 14336),
+                                                        (4, 4096, 256, 9, 1000), (8, 1024, 512, 60, 64), (8, 8192, 8192, 33, 4096)]):
+        top = (1 << bits) - 1
+        sym = np.clip(np.rint(rng.standard_t(4, rows * cols) * ((3.0 + i) if bits == 8 else 1.0) + (top + 1) // 2), 0, top).astype(np.uint8)
+        encs.append(_oracle_encoded(sym, bits, chunk, rows, cols, 0.02 * (i + 1), 5 + i, sub))
+        refs.append(sym)
+        xs.append(synth.make_x_bf16(2, i, cols))
+    dts = [E.to_device(e, DEV) for e in encs]
+    outs = [torch.zeros(e.n, dtype=torch.uint8, device=DEV) for e in encs]
+    ts = [d.ctensor(o) for d, o in zip(dts, outs)]
+    ws = torch.zeros(E.entro_workspace_bytes(ts, E.ENTRO_OP_DECODE), dtype=torch.uint8, device=DEV)
+    plan = E.entro_plan_init(ts, E.ENTRO_OP_DECODE, E.ENTRO_U8, ws)
+    assert plan.shared_wave_bytes > 0
+    E.entro_plan_run(plan)
+    for o, r in zip(outs, refs):
+        assert np.array_equal(o.cpu().numpy(), r)
+    ys = [torch.zeros(e.rows, dtype=torch.float32 if y_type == E.ENTRO_F32 else torch.bfloat16, device=DEV) for e in encs]
+    xd = [torch.from_numpy(x.view(np.int16)).to(DEV).view(torch.bfloat16) for x in xs]
+    ts = [d.ctensor(y, x) for d, y, x in zip(dts, ys, xd)]
+    ws = torch.zeros(E.entro_workspace_bytes(ts, E.ENTRO_OP_GEMV), dtype=torch.uint8, device=DEV)
+    plan = E.entro_plan_init(ts, E.ENTRO_OP_GEMV, y_type, ws)
+    assert plan.shared_wave_bytes > 0
+    for _ in range(2):
+        for y in ys:
+            y.zero_()
+        E.entro_plan_run(plan)
+        for e, y, r, x in zip(encs, ys, refs, xs):
+            y_ref, _ = oracle.gemv(r, e.rows, e.cols, e.qp.scale, e.qp.zero_point, x)
+            terms = np.abs((r.astype(np.float64).reshape(e.rows, e.cols) - e.qp.zero_point) * e.qp.scale) @ \
+                np.abs((x.astype(np.uint32) << 16).view(np.float32).astype(np.float64))
+            half_ulp = 0.0 if y_type == E.ENTRO_F32 else 2.0 ** -8
+            assert np.all(np.abs(y.float().cpu().numpy() - y_ref) <= half_ulp * np.abs(y_ref) + (e.cols + 2) * 2.0 ** -24 * terms)
 
 
 @pytest.mark.parametrize("bits,chunk,segments", [(8, 8192, 2700), (8, 1024, 17000), (4, 512, 41000), (8, 512, 49152), (8, 512, 49153)])
