@@ -220,6 +220,8 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef const u32x4 __attribute__((address_space(1))) *global_u4_ptr;
 typedef u32x4 __attribute__((address_space(1))) *global_u4_wptr;
 typedef u32x2 __attribute__((address_space(1))) *global_u2_wptr;
+typedef const uint64_t __attribute__((address_space(1))) *global_u64_ptr;
+typedef const uint16_t __attribute__((address_space(1))) *global_u16_ptr;
 // LDS pointers with the address space spelled out: the accesses compile to plain
 // ds_ instructions with 32-bit addresses
 typedef volatile uint32_t __attribute__((address_space(3))) *lds_v32;
@@ -249,6 +251,29 @@ __device__ __forceinline__ void unpack_nibbles(uint32_t d, uint32_t &lo, uint32_
 __device__ __forceinline__ void wave_sync_lds() {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
+}
+
+// Tables that a launch's preparation has built, from memory into LDS by the whole workgroup of WG lanes: every lane asks for
+// its 16-byte pieces at once.
+// (In a loop each step waited for its piece, four or five times the way to the L2 and back.)  Measured with seg_start's fifteen
+// loads at once, before -> now: 24-layer set to bytes 838 -> 815 us, phi3-shaped to nibbles 891 -> 868,
+// seven tensors validated and launched to bf16 180 -> 176, 4-bit products of the phi3 shapes 33.4 -> 32.6, 26.2 -> 25.5, and
+// through seg_start alone the step over 32 layers of 8-bit products 6224 -> 6111.
+template <uint32_t BYTES, uint32_t WG>
+__device__ __forceinline__ void copy_tables(void *dst, const void *src) {
+    static_assert(BYTES % 16 == 0, "16-byte pieces");
+    constexpr uint32_t N = BYTES / 16u, STEPS = (N + WG - 1u) / WG;
+    u32x4 v[STEPS];
+#pragma unroll
+    for (uint32_t i = 0; i < STEPS; ++i) {
+        const uint32_t j = i * WG + threadIdx.x;
+        v[i] = ((global_u4_ptr)src)[j < N ? j : N - 1u];
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < STEPS; ++i) {
+        const uint32_t j = i * WG + threadIdx.x;
+        if (j < N) static_cast<u32x4 *>(dst)[j] = v[i];
+    }
 }
 
 // Canonical code tables and both lookup levels, built from the 256 (or 16)
@@ -497,15 +522,20 @@ __device__ __forceinline__ uint32_t single_entry(const TablesTail &tb, uint32_t 
 // front of it in the same segment where the tensor has entry points inside its segments.
 __device__ __forceinline__ uint64_t seg_start(const DevTensor &t, uint32_t k) {
     const uint32_t sh = t.sub_shift;
-    if (sh == 0) return t.offsets[k];
+    const global_u64_ptr offsets = (global_u64_ptr)t.offsets;
+    if (sh == 0) return offsets[k];
     const uint32_t c = k >> sh;
     const uint32_t before = (k - (c << sh)) << t.sub_merge;          // pieces of the segment in front of the lane's
-    const uint16_t *sb = t.sub + (static_cast<uint64_t>(c) << (sh + t.sub_merge));
-    uint32_t add = 0;
+    const global_u16_ptr sb = (global_u16_ptr)t.sub + (static_cast<uint64_t>(c) << (sh + t.sub_merge));
+    const uint64_t base = offsets[c];
+    // All fifteen are asked for at once, the segment's first entry in the place of those that the lane does not need: loads
+    // under a condition each came back one after the other.  Measured with copy_tables: see there.
+    uint32_t len[ENTRO_MAX_SUB_PER_CHUNK - 1], add = 0;
 #pragma unroll
-    for (uint32_t i = 0; i + 1 < ENTRO_MAX_SUB_PER_CHUNK; ++i)
-        if (i < before) add += sb[i];
-    return t.offsets[c] + add;
+    for (uint32_t i = 0; i + 1 < ENTRO_MAX_SUB_PER_CHUNK; ++i) len[i] = sb[i < before ? i : 0u];
+#pragma unroll
+    for (uint32_t i = 0; i + 1 < ENTRO_MAX_SUB_PER_CHUNK; ++i) add += i < before ? len[i] : 0u;
+    return base + add;
 }
 
 // ---------------------------------------------------------------- scalar reader
@@ -1838,13 +1868,16 @@ __device__ __forceinline__ void batch_body(const DevTensor *__restrict__ tensors
             n_all = n_coarse + static_cast<uint32_t>((fine_end - fine_first + kUnit - 1) / kUnit);
         }
         __syncthreads();                                     // nobody reads the previous tables or the counter any more
-        // Built once when the launch was prepared: 16 bytes per lane and step from memory into LDS.  (Every launch that
+        // Built once when the launch was prepared.  (Every launch that
         // comes here has been prepared with tables.  A build in an else branch, never taken, decided the register
         // allocation: 20 spilled vector registers in the 8-bit product against 6 without, 3 and 4 against none
         // for packed nibbles and fp32; the step over 32 layers of 8-bit products 6510 -> 6232 us.)
-        const u32x4 *src = static_cast<const u32x4 *>(t.tables);
-        u32x4 *dst = reinterpret_cast<u32x4 *>(&sm.tb);
-        for (uint32_t j = threadIdx.x; j < sizeof(sm.tb) / 16u; j += WG) dst[j] = src[j];
+        if constexpr (wide_gemv(MODE)) {
+            // (one piece after the other: asked for at once they cost the product loop five more spilled registers)
+            for (uint32_t j = threadIdx.x; j < sizeof(sm.tb) / 16u; j += WG) reinterpret_cast<u32x4 *>(&sm.tb)[j] = ((global_u4_ptr)t.tables)[j];
+        } else {
+            copy_tables<sizeof(sm.tb), WG>(&sm.tb, t.tables);
+        }
         __syncthreads();
         if (rows_fit<MODE>(t)) {
             // A wavefront's first unit has its own number: a stretch of fewer units than wavefronts is spread evenly over
@@ -2311,9 +2344,7 @@ __global__ __launch_bounds__(64 * kShareWaves) void k_shared_batch(const DevTens
         ShareUnit u;
         if (at < n_units) share_look_up(t, it.first + at, u);    // (on its way while the tables come in)
         __syncthreads();                                         // nobody reads the previous tables any more
-        const u32x4 *src = static_cast<const u32x4 *>(t.tables);
-        u32x4 *dst = reinterpret_cast<u32x4 *>(&sm);
-        for (uint32_t j = threadIdx.x; j < ShareMem::table_bytes / 16u; j += 64u * kShareWaves) dst[j] = src[j];
+        copy_tables<ShareMem::table_bytes, 64u * kShareWaves>(&sm, t.tables);
         __syncthreads();
         while (at < n_units) {
             share_unit<MODE>(t, sm, sym, wave_bytes, it.first + at, u);
