@@ -200,7 +200,7 @@ entro_status entro_encode(const uint8_t *q, uint64_t n, const entro_codebook *cb
  * segment's offset plus the entries of the pieces before it in the same segment.  The
  * stream and the offset table are those of entro_encode, unchanged.  With sub_bits and
  * sub_symbols in an entro_tensor the device calls give a lane a piece instead of a
- * segment; results are identical.  ENTRO_ERR_CODE_TOO_LONG if a piece exceeds 65535 bits
+ * segment (or, in small launches, several lanes a piece); results are identical.  ENTRO_ERR_CODE_TOO_LONG if a piece exceeds 65535 bits
  * (cannot happen for sub_symbols <= 2047), ENTRO_ERR_SYMBOL for a symbol without a code. */
 entro_status entro_sub_index(const uint8_t *q, uint64_t n, const entro_codebook *cb, uint32_t chunk_symbols,
                              uint32_t sub_symbols, uint16_t *sub_bits);
@@ -276,11 +276,12 @@ uint64_t entro_workspace_bytes(const entro_tensor *ts, uint32_t count, entro_op 
  * The work list is cut for the current device (its number of compute units
  * decides how many units a work item holds and, for tensors with entry points
  * inside their segments, how many pieces a lane takes: as coarse as still gives
- * the device's lanes work): run the plan on the device it was prepared on.  The
+ * the device's lanes work; launches too small for that let several lanes share a
+ * piece or segment, see shared_wave_bytes): run the plan on the device it was prepared on.  The
  * launch is one workgroup per compute unit at most; inside a workgroup the
  * wavefronts draw their segments from a counter, so which wavefront decodes which
  * segment differs from run to run, the result does not.  (A GEMV's sums are taken
- * in an order that depends on how rows are cut into lanes, i.e. on the launch, never
+ * in an order that depends on how rows are cut into lanes or units, i.e. on the launch, never
  * on the run.) */
 entro_status entro_plan_init(entro_plan *plan, const entro_tensor *ts, uint32_t count, entro_op op,
                              entro_dtype out_type, void *workspace, uint64_t workspace_bytes,

@@ -6,6 +6,7 @@
 // them independently; here a segment is a fixed number of symbols and one
 // GPU lane owns one segment, so a workgroup of W lanes decodes W consecutive
 // segments of one tensor with one shared set of lookup tables in LDS.
+// Launches over few segments let several lanes share one (k_shared, below).
 //
 // Data flow of the decode / dequant kernels, per lane:
 //   HBM --128-byte lines (GEMV: 64)--> registers --between output blocks--> 128-byte ring in LDS

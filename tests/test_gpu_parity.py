@@ -222,8 +222,8 @@ def test_staircase_codes_around_the_widths_of_the_tables(bits, deepest):
     (448, 3, 0)])
 @pytest.mark.parametrize("run", [False, True])
 def test_segments_without_entry_points_cut_into_pieces(bits, chunk, segments, last, run):
-    # 8 to 64 lanes per segment that find their starts themselves (4-bit symbols: 32 and 64, the segments of less than
-    # 2048 and of 3072 symbols keep a lane each), short last segments, and (448) segments that do not divide;
+    # 8 to 64 lanes per segment that find their starts themselves, short last segments, and (448) segments that are too
+    # short for that;
     # `run`: a first segment of one symbol only, where every guess is a true start
     rng = np.random.default_rng(chunk + last + bits)
     top, n = (1 << bits) - 1, segments * chunk + last
@@ -258,7 +258,7 @@ def _with_runs(bits, chunk, segments, last, fraction, every, seed):
 @pytest.mark.parametrize("bits,chunk", [(8, 4096), (8, 2048), (8, 1024), (8, 512), (4, 4096), (4, 2048), (4, 8192)])
 @pytest.mark.parametrize("fraction,every", [(0.5, 3), (0.9, 1), (0.97, 64)])
 def test_runs_inside_segments_without_entry_points(bits, chunk, fraction, every):
-    # the search for starts is given up in the wavefronts that hold the runs, and goes on in the others
+    # lanes in a run agree on their starts one after the other, those beside it at once
     for segments, last in ((70, 0), (9, chunk // 3 + 1), (1, 0)):
         sym = _with_runs(bits, chunk, segments, last, fraction, every, segments)
         enc = _oracle_encoded(sym, bits, chunk, 1, sym.size, 0.25, 7)
@@ -407,8 +407,8 @@ def test_segments_without_entry_points_are_cut(bits, chunk, out):
 
 @pytest.mark.parametrize("bits,chunk,out,most", [(8, 1024, E.ENTRO_BF16, 1.5), (4, 4096, E.ENTRO_U4_PACKED, 1.9)])
 def test_runs_cost_little_more_than_a_lane_per_segment(bits, chunk, out, most):
-    """Data that does not fall into step: the call gives its search up and takes 1.3 (8 bits) and 0.9 to 1.5 times (4 bits)
-    as long as the prepared launch; 1.73 and 2.15 times at the least where the search goes on until the lanes agree."""
+    """Data that does not fall into step takes rounds until the lanes agree: so many times the prepared launch, which decodes
+    a segment with a lane, at the most."""
     segments = (1 << 24) // chunk if chunk > 1024 else 1 << 15
     single, prepared = _single_and_prepared_us(_with_runs(bits, chunk, segments, 0, 0.9, 20, 3), bits, chunk, out)
     assert single <= most * prepared, (single, prepared)
