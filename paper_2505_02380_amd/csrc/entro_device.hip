@@ -285,9 +285,11 @@ __device__ __forceinline__ void copy_tables(void *dst, const void *src) {
 // the first level is resolved for kSmallBits index bits only, copied to the indexes that end in
 // the same bits, and searched bit by bit for the few indexes that start with a longer code.
 // Pair tables resolve every index, with two reads of the small table of single codes.
+// L2 false: without the second level (k_shared goes to the canonical tables for the codes that its table does not hold).
+// 4096 x 4096 without entry points to bf16 32.8 -> 31.9 us, its product 31.3 -> 30.5, 2048 x 2048 to bytes 24.5 -> 23.8.
 // Measured as the whole call: one tensor of 2048 symbols to fp32 33.6 -> 22.0 us, 4 M symbols to
 // bytes 42.6 -> 30.6 us, against a search over all 14 lengths for every index.
-template <int WG, bool PAIR, class TB>
+template <int WG, bool PAIR, bool L2 = true, class TB>
 __device__ __forceinline__ void build_tables(const DevTensor &t, TB &tb, uint32_t *wcnt) {
     static_assert(WG >= 256, "one lane per symbol");
     constexpr uint32_t kLens = ENTRO_MAX_CODE_LEN + 1;
@@ -296,8 +298,10 @@ __device__ __forceinline__ void build_tables(const DevTensor &t, TB &tb, uint32_
     const uint32_t wave = tid >> 6;
     const uint32_t max_len = t.max_len;
     const uint32_t l = tid < 256 ? t.len[tid] : 0u;
-    if (tid < kL2MaxPrefixes) tb.pdepth[tid] = 0;
-    for (uint32_t i = tid; i < kL2Cap; i += WG) tb.lut2[i] = 0;
+    if constexpr (L2) {
+        if (tid < kL2MaxPrefixes) tb.pdepth[tid] = 0;
+        for (uint32_t i = tid; i < kL2Cap; i += WG) tb.lut2[i] = 0;
+    }
     // symbols of each length per wave, and every symbol's place among those of its length in its wave
     uint32_t rank = 0;
     if (tid < 256) {
@@ -342,7 +346,7 @@ __device__ __forceinline__ void build_tables(const DevTensor &t, TB &tb, uint32_
     __syncthreads();
     uint32_t code = 0;
     const uint32_t first_prefix = tb.first_prefix;
-    const bool have_l2 = !PAIR && first_prefix < (1u << kL1);
+    const bool have_l2 = L2 && !PAIR && first_prefix < (1u << kL1);
     if (l) {
         for (uint32_t w = 0; w < wave; ++w) rank += wcnt[w * kLens + l];
         code = tb.first[l] + rank;
@@ -476,7 +480,7 @@ __device__ __forceinline__ void build_tables(const DevTensor &t, TB &tb, uint32_
             uint32_t e = pack_entry(0, 1);
             if (v >= long_start) {
                 e = 7u << 8;
-                if (v >= first_prefix) e = (tb.pdepth[v - first_prefix] << 8) | ((tb.pbase[v - first_prefix] >> 4) << 11);
+                if (L2 && v >= first_prefix) e = (tb.pdepth[v - first_prefix] << 8) | ((tb.pbase[v - first_prefix] >> 4) << 11);
             }
             if (len) e = entry_of(idx, len);
             tb.lut[__brev(v) >> (32 - kL1)] = static_cast<Entry>(e);
@@ -2309,7 +2313,7 @@ __global__ __launch_bounds__(64 * kShareWaves) void k_shared(const DevTensor t, 
     uint32_t unit = blockIdx.x * waves + wave;
     const bool works = wave < waves && unit < t.share_units;
     if (works) share_look_up(t, unit, u);                        // (on its way while the tables are built)
-    build_tables<64 * kShareWaves, false>(t, sm.building(), reinterpret_cast<uint32_t *>(sm.multi));   // (scratch: not in use yet)
+    build_tables<64 * kShareWaves, false, false>(t, sm.building(), reinterpret_cast<uint32_t *>(sm.multi));   // (scratch: not in use yet)
     build_multi(sm);
     __syncthreads();
     if (!works) return;
@@ -2360,7 +2364,7 @@ __global__ __launch_bounds__(64 * kShareWaves) void k_shared_batch(const DevTens
 __global__ __launch_bounds__(64 * kShareWaves) void k_share_tables(const DevTensor *__restrict__ tensors) {
     __shared__ ShareMem sm;
     const DevTensor &t = tensors[blockIdx.x];
-    build_tables<64 * kShareWaves, false>(t, sm.building(), reinterpret_cast<uint32_t *>(sm.multi));
+    build_tables<64 * kShareWaves, false, false>(t, sm.building(), reinterpret_cast<uint32_t *>(sm.multi));
     build_multi(sm);
     __syncthreads();
     const u32x4 *src = reinterpret_cast<const u32x4 *>(&sm);
