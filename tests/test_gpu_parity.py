@@ -369,49 +369,71 @@ def test_segments_without_entry_points_whose_offsets_do_not_fit(bits, chunk):
         assert np.array_equal(got[: 2 * chunk], sym[: 2 * chunk]) and np.array_equal(got[3 * chunk:], sym[3 * chunk:])
 
 
-def _single_and_prepared_us(sym, bits, chunk, out):
-    """Times of the call on one tensor without entry points, which may cut its segments, and of the same tensor's
-    prepared launch, which decodes a segment with a lane and finds its tables built."""
+def _times_us(calls, inner=5):
+    """Times of the calls, taken in turn."""
+    times = [[] for _ in calls]
+    for f in calls:
+        f()
+    for _ in range(12):
+        for f, t in zip(calls, times):
+            a, b = torch.cuda.Event(True), torch.cuda.Event(True)
+            a.record()
+            for _ in range(inner):
+                f()
+            b.record()
+            b.synchronize()
+            t.append(a.elapsed_time(b) * 1000 / inner)
+    return [float(np.median(t)) for t in times]
+
+
+# Codes whose lengths have a common divisor: reading from a wrong bit does not fall into step, so lanes never share a segment.
+EVEN_LENGTHS = {8: [2, 2, 2, 4, 4, 4, 6, 6, 6, 6], 4: [2, 2, 2, 4, 4, 4, 4]}
+
+
+def _out_of_step(bits, chunk, n, rows=1, cols=0, sub=0):
+    """n symbols under such a code."""
+    lengths = np.array(EVEN_LENGTHS[bits])
+    sym = np.random.default_rng(n).choice(lengths.size, n, p=0.5 ** lengths).astype(np.uint8)
+    cb = E.entro_codebook_from_lengths(np.pad(lengths, (0, (1 << bits) - lengths.size)).astype(np.uint8), bits)
+    stream, off = E.entro_encode(sym, cb, chunk)
+    enc = B.EncodedTensor(stream, off, n, chunk, cb, B.QParams(np.float32(0.25), 7, bits, E.ENTRO_ASYMMETRIC), rows, cols or n)
+    if sub:
+        enc.sub_symbols, enc.sub_bits = sub, E.entro_sub_index(sym, cb, chunk, sub)
+    return enc, sym
+
+
+def _single_and_lane_per_segment_us(sym, bits, chunk, out):
+    """Times of the call on one tensor without entry points, and of a prepared launch over as many segments of as many symbols
+    under a code that does not fall into step: it decodes a segment with a lane, and finds its tables built."""
     cb = E.entro_build_codebook(sym, bits)
     stream, off = E.entro_encode(sym, cb, chunk)
     enc = B.EncodedTensor(stream, off, sym.size, chunk, cb, B.QParams(np.float32(0.25), 7, bits, E.ENTRO_ASYMMETRIC), 1, sym.size)
     op = E.ENTRO_OP_DEQUANT if out == E.ENTRO_BF16 else E.ENTRO_OP_DECODE
     y = torch.zeros(sym.size, dtype=torch.bfloat16 if out == E.ENTRO_BF16 else torch.uint8, device=DEV)
-    dt = E.to_device(enc, DEV)
-    t = dt.ctensor(y)
-    ws = torch.zeros(E.entro_workspace_bytes([t], op), dtype=torch.uint8, device=DEV)
-    plan = E.entro_plan_init([t], op, out, ws)
+    dt, lane = E.to_device(enc, DEV), E.to_device(_out_of_step(bits, chunk, sym.size)[0], DEV)
+    t, tl = dt.ctensor(y), lane.ctensor(y)
+    ws = torch.zeros(E.entro_workspace_bytes([tl], op), dtype=torch.uint8, device=DEV)
+    plan = E.entro_plan_init([tl], op, out, ws)
+    assert plan.shared_wave_bytes == 0
     call = E.entro_decode_dequant if out == E.ENTRO_BF16 else E.entro_decode
-    res = []
-    for f in (lambda: call(t, out), lambda: E.entro_plan_run(plan)):
-        times = []
-        for _ in range(12):
-            a, b = torch.cuda.Event(True), torch.cuda.Event(True)
-            a.record()
-            for _ in range(5):
-                f()
-            b.record()
-            b.synchronize()
-            times.append(a.elapsed_time(b) * 200)
-        res.append(float(np.median(times)))
-    return res
+    return _times_us([lambda: call(t, out), lambda: E.entro_plan_run(plan)])
 
 
 @pytest.mark.parametrize("bits,chunk,out", [(8, 4096, E.ENTRO_BF16), (8, 2048, E.ENTRO_U8), (4, 4096, E.ENTRO_U4_PACKED)])
 def test_segments_without_entry_points_are_cut(bits, chunk, out):
-    # bell-shaped data in few segments: 0.13, 0.26 and 0.37 of a lane per segment's time
+    # bell-shaped data in few segments
     sym = _with_runs(bits, chunk, (1 << 23) // chunk, 0, 0.0, 1, 3)
-    single, prepared = _single_and_prepared_us(sym, bits, chunk, out)
-    assert single <= 0.85 * prepared, (single, prepared)
+    single, lane = _single_and_lane_per_segment_us(sym, bits, chunk, out)
+    assert single <= 0.85 * lane, (single, lane)
 
 
 @pytest.mark.parametrize("bits,chunk,out,most", [(8, 1024, E.ENTRO_BF16, 1.5), (4, 4096, E.ENTRO_U4_PACKED, 1.9)])
 def test_runs_cost_little_more_than_a_lane_per_segment(bits, chunk, out, most):
-    """Data that does not fall into step takes rounds until the lanes agree: so many times the prepared launch, which decodes
-    a segment with a lane, at the most."""
+    """Data that does not fall into step takes rounds until the lanes agree: so many times a launch that decodes a segment with
+    a lane, at the most."""
     segments = (1 << 24) // chunk if chunk > 1024 else 1 << 15
-    single, prepared = _single_and_prepared_us(_with_runs(bits, chunk, segments, 0, 0.9, 20, 3), bits, chunk, out)
-    assert single <= most * prepared, (single, prepared)
+    single, lane = _single_and_lane_per_segment_us(_with_runs(bits, chunk, segments, 0, 0.9, 20, 3), bits, chunk, out)
+    assert single <= most * lane, (single, lane)
 
 
 @pytest.mark.parametrize("lengths", [
@@ -965,28 +987,15 @@ def test_few_units_per_workgroup_run_side_by_side(y_type):
     cols, sub, us = 8192, 512, []
     for units in (1, 4):
         rows = units * cus * 64 * sub // cols
-        rng = np.random.default_rng(units)
-        sym = np.clip(np.rint(rng.laplace(size=rows * cols) * 0.47 + 7), 0, 15).astype(np.uint8)
-        cb = E.entro_build_codebook(sym, 4)
-        stream, off = E.entro_encode(sym, cb, 16 * sub)
-        enc = B.EncodedTensor(stream, off, sym.size, 16 * sub, cb, B.QParams(np.float32(0.25), 7, 4, E.ENTRO_ASYMMETRIC), rows, cols)
-        enc.sub_symbols, enc.sub_bits = sub, E.entro_sub_index(sym, cb, 16 * sub, sub)
+        enc, sym = _out_of_step(4, 16 * sub, rows * cols, rows, cols, sub)   # (a code that lanes do not share pieces of)
         dt = E.to_device(enc, DEV)
         x = torch.from_numpy(synth.make_x_bf16(9, units, cols).view(np.int16)).to(DEV).view(torch.bfloat16)
         y = torch.zeros(rows, dtype=torch.float32 if y_type == E.ENTRO_F32 else torch.bfloat16, device=DEV)
         ts = [dt.ctensor(y, x)]
         ws = torch.zeros(E.entro_workspace_bytes(ts, E.ENTRO_OP_GEMV), dtype=torch.uint8, device=DEV)
         plan = E.entro_plan_init(ts, E.ENTRO_OP_GEMV, y_type, ws)
-        times = []
-        for _ in range(16):
-            a, b = torch.cuda.Event(True), torch.cuda.Event(True)
-            a.record()
-            for _ in range(20):
-                E.entro_plan_run(plan)
-            b.record()
-            b.synchronize()
-            times.append(a.elapsed_time(b) * 50)
-        us.append(float(np.median(times)))
+        assert plan.shared_wave_bytes == 0
+        us.append(_times_us([lambda: E.entro_plan_run(plan)], 20)[0])
         y_ref, _ = oracle.gemv(sym, rows, cols, 0.25, 7, synth.make_x_bf16(9, units, cols))
         _assert_gemv_close(y.float().cpu().numpy().astype(np.float64), y_ref, 1e-3 if y_type == E.ENTRO_F32 else 5e-3)
     assert us[1] <= 1.13 * us[0], us
