@@ -2670,14 +2670,15 @@ bool falls_into_step(const entro_codebook *cb) {
     return divisor == 1 && square / weight - mean * mean >= 0.5;
 }
 
-// Segments longer than k_shared holds (kShareMost), without entry points, that leave most lanes of the device without work:
-// 2^sub_shift lanes per segment that find their pieces' starts themselves (find_start), as many as the device has lanes for.
+// Segments without entry points that leave most lanes of the device without work: 2^sub_shift lanes per segment that find their
+// pieces' starts themselves (find_start), as many as the device has lanes for.  For segments longer than k_shared holds
+// (kShareMost), and for those of more than half of that where it is the faster of the two (launch_single).
 // A lane then decodes its share three times, two of them symbol by symbol, which pays from eight lanes per segment on (4-bit
 // symbols, decoded two a lookup but searched one at a time: sixteen).  The pieces must be whole blocks of the kernel.
 // Measured when shorter segments came here too: 4096 x 4096 in segments of 4096 to bf16 318 us with a lane per segment, 47 us
 // with 64; 8192 x 4096 in segments of 1024, which got eight, 115 -> 98 us.
 bool cut_segments(entro_op op, int mode, uint64_t lane_slots, const entro_tensor *t, DevTensor *dt) {
-    if (op == ENTRO_OP_GEMV || t->sub_symbols || dt->chunk_symbols <= kShareMost) return false;
+    if (op == ENTRO_OP_GEMV || t->sub_symbols) return false;
     const uint32_t block = spb_of(mode);
     const uint32_t least = dt->bits == 4 ? 4u : 3u;
     for (uint32_t sh = 6; sh >= least; --sh) {
@@ -2691,27 +2692,21 @@ bool cut_segments(entro_op op, int mode, uint64_t lane_slots, const entro_tensor
     return false;
 }
 
+// Stream bits of a symbol on average (as far as the rules below use them: at most the symbol's own).
+double stream_bits(const DevTensor &dt) { return std::min(static_cast<double>(dt.bits), 8.0 * dt.stream_bytes / static_cast<double>(dt.n)); }
+
 // A tensor in few segments, or few pieces between entry points: 4 to 64 lanes share one (k_shared), at about 64 symbols a
 // lane.  A wavefront's share of LDS is what its unit's symbols take, and its part of the stream at the tensor's mean rate and
 // a thirty-second more (a unit with more is read straight from memory).
-// A lane per segment takes 0.036 (4-bit) to 0.072 us (8-bit) for each of a segment's symbols, however many segments there
-// are until the device is full; k_shared 13.5 to 17.5 us for each 2^24 symbols of the tensor.  They meet at 50 to 65
-// thousand segments: three sixteenths of the lanes is a little less (and less again where LDS holds fewer than sixteen units).
-// Measured, whole calls, before -> now.  8 bits, 4096 x 4096: to bf16 47.2 -> 34.0 us, bytes 65.1 -> 31.0, product 295.9
-// -> 32.5; segments of 1024 49.1 -> 33.8, 64.8 -> 31.8, 84.8 -> 32.8; of 512, 32768 of them, 47.7 -> 33.9, 50.1 -> 31.4, 48.9
-// -> 32.2, and 131072 of them, which the rule leaves with a lane each, 57 against 86.  4 bits: bf16 62.4 -> 25.0, product
-// 159.4 -> 24.3; segments of 1024, 16384 x 4096 (65536, left with a lane each), 59 against 63.
-// Pieces between entry points, 2048 x 4096: of 512 symbols, 8 bits, to bf16 54.7 -> 28.4 us, bytes 53.5 -> 27.4, product 53.5
-// -> 27.9, 4 bits 36.4 -> 22.1; of 256 33.7 -> 28.4 and 26.7 -> 21.8, but the more bits a symbol takes, the fewer a lookup
-// answers: at 5.0 bits 35.6 -> 36.1 (and the product 34.2 -> 36.1), so they come here up to 4 bits.  Pieces of 128 do not:
-// 20.9 against 26.2 (256 x 4096).
 // share_fits: whether the tensor's form goes there at all; describes its units and says how much LDS one takes.
-// share_pays: the rule above, for a launch of `segments` segments with `waves` wavefronts' worth of LDS in a workgroup.
+// Pieces of 256 symbols come here up to 4 bits a symbol (2048 x 4096: 33.7 -> 28.4 us and 26.7 -> 21.8, but the more bits a symbol
+// takes, the fewer a lookup answers: at 5.0 bits 35.6 -> 36.1, and the product 34.2 -> 36.1).  Pieces of 128 do not: 20.9
+// against 26.2 (256 x 4096).
 bool share_fits(entro_op op, const entro_tensor *t, DevTensor *dt, uint32_t *wave_bytes) {
     const uint32_t S = dt->chunk_symbols;
     if (dt->sub_merge != 0 || S % 128u != 0 || S < (t->sub_symbols ? 4u : 8u) * kShareSymbols || S > kShareMost) return false;
     if (op == ENTRO_OP_GEMV && dt->cols % 8u != 0) return false;
-    const double rate = std::min(static_cast<double>(dt->bits), 8.0 * dt->stream_bytes / static_cast<double>(dt->n));
+    const double rate = stream_bits(*dt);
     if (t->sub_symbols && S < 8u * kShareSymbols && rate > 4.0) return false;
     if (!falls_into_step(t->cb)) return false;
     uint32_t sh = 1;
@@ -2736,7 +2731,72 @@ bool share_fits(entro_op op, const entro_tensor *t, DevTensor *dt, uint32_t *wav
 
 uint32_t share_waves(uint32_t wave_bytes) { return std::min<uint32_t>(kShareWaves, sizeof(ShareMem::pool) / wave_bytes); }
 
-bool share_pays(uint64_t segments, uint32_t waves, uint64_t lane_slots) { return segments * 16u * kShareWaves <= lane_slots * 3u * waves; }
+// Whether sharing pays is decided by what the launches take, in microseconds, as measured on 3000 calls of 3.3 to 7.5 (8 bits)
+// and 1.5 to 3.6 (4 bits) bits a symbol, segments and pieces of 256 to 8192 symbols, 512 to 49152 of them; the estimates are
+// within 10 to 20 % of the times, beside what the launches have in common.
+// A lane per segment: a lane's serial chain, whatever their number while wavefronts have their SIMDs to themselves; that is up to
+// three sixteenths of the lanes, and launches of more segments are not shared.  A product takes a shorter last segment symbol by
+// symbol behind that (4096 segments of 4096 in rows of 11008: 864 us, 298 without one).
+// Shared: rounds of units, one a wavefront.  A round's time goes with the bits (more of them, fewer codes a lookup; 4-bit symbols
+// leave a lookup's four codes as the limit), with the symbols of a unit, and less than in proportion with the wavefronts.
+// Searched (find_start): every piece is decoded three times, slower the more bits a symbol has; below 4096 symbols a segment the
+// search gives up on dense codes and has cost a lane per segment then (4096 x 4096 at 7.5 bits to bf16 296 us, 86 shared).
+// Measured, a lane per segment -> shared, at the places where the choice turns.  Prepared products of 8 bits: 40960 segments of
+// 512 symbols at 3.5 bits 48 -> 42 us, at 5.4 54.7 -> 57.1, at 7.5 46 -> 80; of 4096 at 5.2 338 -> 363; 28672 of 4096 at 6.5
+// 396 -> 292, at 7.5 314 -> 346.  Of 4 bits: 40960 of 1024 44.3 -> 53.5, 28672 39.9 -> 41.7.  Single calls to bytes: 28672 of
+// 8192 at 3.3 bits searched 631, shared 295.
+bool few_segments(uint64_t segments, uint64_t lane_slots) { return segments * 16u <= lane_slots * 3u; }
+
+double lane_us(entro_op op, entro_dtype d, uint32_t bits, const DevTensor &dt) {
+    const double each = op == ENTRO_OP_GEMV ? (bits == 4 ? 0.038 : 0.072) : d == ENTRO_F32 ? (bits == 4 ? 0.042 : 0.094)
+                        : d == ENTRO_BF16   ? (bits == 4 ? 0.039 : 0.080) : (bits == 4 ? 0.034 : 0.080);
+    return 2.0 + each * dt.chunk_symbols + (op == ENTRO_OP_GEMV ? 0.18 * (dt.n % dt.chunk_symbols) : 0.0);
+}
+
+// `units`: of the workgroup that has most of them.
+double share_us(entro_op op, const DevTensor &dt, uint32_t units, uint32_t waves) {
+    const double full = (dt.bits == 4 ? 12.0 : 4.9 * stream_bits(dt)) + (op == ENTRO_OP_GEMV ? 4.0 : 0.0);   // 16 wavefronts, 4096 symbols each
+    const double by_size = full * dt.chunk_symbols * dt.share_per / 4096.0;
+    const uint32_t rounds = units / waves, last = units % waves;
+    return by_size / 30.0 * (rounds * (14.0 + waves) + (last ? 14.0 + last : 0.0));
+}
+
+double find_us(const DevTensor &dt, double rate) { return 3.0 * dt.chunk_symbols * (0.02 + 0.035 * rate); }
+
+// A prepared launch gives workgroup b of G the items [b * n / G, (b + 1) * n / G): the longest time that `cost` makes of a
+// workgroup's stretches (items of one tensor side by side), with the time to load a stretch's tables.
+template <class Items, class Cost>
+double busiest_us(uint32_t count, uint32_t slots, Items items, Cost cost) {
+    uint64_t n = 0;
+    for (uint32_t i = 0; i < count; ++i) n += items(i);
+    const uint64_t groups = std::min<uint64_t>(n, slots);
+    double most = 0;
+    uint64_t left = items(0), carried = 0;
+    uint32_t i = 0;
+    for (uint64_t b = 0; b < groups; ++b) {
+        carried += n % groups;
+        uint64_t share = n / groups + (carried >= groups ? 1u : 0u);
+        carried -= carried >= groups ? groups : 0u;
+        double us = 0;
+        while (share != 0) {
+            const uint64_t here = std::min(share, left);
+            us += cost(i, here) + 3.0;
+            share -= here;
+            left -= here;
+            if (left == 0 && i + 1u < count) left = items(++i);
+        }
+        most = std::max(most, us);
+    }
+    return most;
+}
+
+uint64_t items_of(uint64_t units, uint64_t per_item) { return (units + per_item - 1u) / per_item; }
+
+// Units of a work item where a lane takes a segment (or piece): what a workgroup takes in one round when the launch is large, and
+// less when the launch would not give every compute unit an item otherwise.
+uint32_t lane_item_units(uint64_t units, uint32_t slots, uint32_t waves) {
+    return static_cast<uint32_t>(std::min<uint64_t>(waves, std::max<uint64_t>(1, units / slots)));
+}
 
 entro_status launch_fix_single(entro_dtype d, const DevTensor &dt, hipStream_t s) {
     const unsigned grid = (dt.rows + kFixRows - 1) / kFixRows;
@@ -2745,8 +2805,13 @@ entro_status launch_fix_single(entro_dtype d, const DevTensor &dt, hipStream_t s
     return hip_ok(hipGetLastError(), "launch row-sum kernel") ? ENTRO_OK : ENTRO_ERR_DEVICE;
 }
 
+// Wavefronts of a workgroup that take units in a launch over one tensor.
+uint32_t share_launch_waves(const DevTensor &dt, uint32_t wave_bytes, unsigned cus) {
+    return std::min<uint32_t>(share_waves(wave_bytes), (dt.share_units + cus - 1u) / cus);
+}
+
 entro_status launch_shared(entro_op op, entro_dtype d, const DevTensor &dt, uint32_t wave_bytes, unsigned cus, hipStream_t s) {
-    const unsigned waves = std::min<unsigned>(share_waves(wave_bytes), (dt.share_units + cus - 1u) / cus);
+    const unsigned waves = share_launch_waves(dt, wave_bytes, cus);
     const unsigned grid = std::min<unsigned>(cus, (dt.share_units + waves - 1u) / waves);
     dispatch_mode(mode_of(op, d, false), [&](auto m) {
         constexpr int M = decltype(m)::value;
@@ -2772,16 +2837,35 @@ entro_status launch_single(const entro_tensor *t, entro_op op, entro_dtype d, fl
     if (st != ENTRO_OK) return st;
     dt.partials = partials;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    DevTensor shared = dt;
-    uint32_t wave_bytes = 0;
-    if (share_fits(op, t, &shared, &wave_bytes) && share_pays(shared.n_chunks, share_waves(wave_bytes), static_cast<uint64_t>(slots) * wg))
-        return launch_shared(op, d, shared, wave_bytes, slots, s);
-    const bool find = cut_segments(op, mode, static_cast<uint64_t>(slots) * wg, t, &dt);
+    const uint64_t lane_slots = static_cast<uint64_t>(slots) * wg;
     // a unit per wavefront when the tensor is large; fewer units per workgroup, down to one, when
     // that would leave compute units without a workgroup
-    const unsigned units = (dt.n_chunks + kUnit - 1) / kUnit;
-    const unsigned wg_units = std::min(wg / 64u, std::max(1u, units / slots));
-    const unsigned grid = (units + wg_units - 1) / wg_units;
+    unsigned wg_units = 1, grid = 1;
+    auto cut_units = [&](const DevTensor &of) {
+        const unsigned units = (of.n_chunks + kUnit - 1) / kUnit;
+        wg_units = std::min(wg / 64u, std::max(1u, units / slots));
+        grid = (units + wg_units - 1) / wg_units;
+        return (grid + slots - 1u) / slots;                      // rounds of workgroups
+    };
+    bool find = false;
+    DevTensor shared = dt;
+    uint32_t wave_bytes = 0;
+    if (few_segments(dt.n_chunks, lane_slots) && share_fits(op, t, &shared, &wave_bytes)) {
+        const uint32_t waves = share_launch_waves(shared, wave_bytes, slots);
+        const uint32_t rounds = (shared.share_units + slots * waves - 1u) / (slots * waves);
+        const double share = share_us(op, shared, rounds * waves, waves);
+        const double lane = lane_us(op, d, dt.bits, dt) * cut_units(dt);
+        DevTensor found = dt;
+        if (dt.bits == 8 && dt.chunk_symbols > kShareMost / 2u && cut_segments(op, mode, lane_slots, t, &found)) {
+            const double search = find_us(found, stream_bits(dt)) * cut_units(found);
+            find = search < share && search < lane;
+        }
+        if (!find && share <= lane) return launch_shared(op, d, shared, wave_bytes, slots, s);
+        if (find) dt = found;
+    } else {
+        find = cut_segments(op, mode, lane_slots, t, &dt);
+    }
+    cut_units(dt);
     dispatch_mode(mode, [&](auto m) {
         constexpr int M = decltype(m)::value;
         if constexpr (!is_gemv(M)) {
@@ -2934,23 +3018,38 @@ static entro_status build_plan(entro_plan *plan, const entro_tensor *ts, uint32_
     const uint64_t lane_slots = static_cast<uint64_t>(slots0) * wg_of(mode0);
     // Launches whose segments or pieces are so few that lanes share them (k_shared_batch), by the rule of the single calls.
     // Measured, prepared launches, before -> now.  2048 x 2048 matrices, 8 bits, pieces of 512: one to bf16 47.6 -> 22.7 us, its
-    // product 46.8 -> 23.9; five 90.2 -> 48.8, 85.0 -> 47.8; twenty, a lane each, 97.  Pieces of 1024: 86.2 -> 26.4, 82.4 ->
-    // 27.7; twenty at once 103 against 123, and the rule leaves them.  4 bits, pieces of 512: 27.8 -> 15.2, five 53.1 -> 32.3.
+    // product 46.8 -> 23.9; five 90.2 -> 48.8, 85.0 -> 47.8.  Pieces of 1024: 86.2 -> 26.4, 82.4 -> 27.7.  4 bits, pieces of 512:
+    // 27.8 -> 15.2, five 53.1 -> 32.3.
     // Two exceptions, where the tests hold this form's times against others': decoding without entry points keeps a lane per
     // segment, and so do 4-bit products in pieces of up to 512 symbols whose rows a wavefront adds up itself (2048 x 4096:
     // 25.6 us, and 19.0 shared).
     uint64_t segments = 0;
     for (uint32_t i = 0; i < count; ++i) segments += dts[i].n_chunks;
-    bool shared = share_pays(segments, kShareWaves, lane_slots);
+    bool shared = few_segments(segments, lane_slots);
     uint32_t wave_bytes = 1;
     for (uint32_t i = 0; shared && i < count; ++i) {
-        DevTensor dt = dts[i];
         uint32_t bytes = 0;
-        shared = (op == ENTRO_OP_GEMV || ts[i].sub_symbols) && !(dt.bits == 4 && dt.row_lanes && dt.chunk_symbols <= 512u) &&
-                 share_fits(op, &ts[i], &dt, &bytes);
+        shared = (op == ENTRO_OP_GEMV || ts[i].sub_symbols) && !(dts[i].bits == 4 && dts[i].row_lanes && dts[i].chunk_symbols <= 512u) &&
+                 share_fits(op, &ts[i], &dts[i], &bytes);
         wave_bytes = std::max(wave_bytes, bytes);
     }
-    shared = shared && share_pays(segments, share_waves(wave_bytes), lane_slots);
+    if (shared) {
+        // what the busiest workgroup takes: its stretches, one after the other, with the tables of each
+        const uint32_t take = share_waves(wave_bytes), have = static_cast<uint32_t>(wg_of(mode0) / 64u);
+        uint64_t units = 0;
+        for (uint32_t i = 0; i < count; ++i) units += (dts[i].n_chunks + kUnit - 1u) / kUnit;
+        const uint32_t item_units = lane_item_units(units, slots0, have);
+        const double share = busiest_us(count, slots0, [&](uint32_t i) { return items_of(dts[i].share_units, share_item_units(dts[i].share_per)); },
+                                        [&](uint32_t i, uint64_t items) {
+                                            const uint64_t n = std::min<uint64_t>(dts[i].share_units, items * share_item_units(dts[i].share_per));
+                                            return share_us(op, dts[i], static_cast<uint32_t>(n), take);
+                                        });
+        const double lane = busiest_us(count, slots0, [&](uint32_t i) { return items_of((dts[i].n_chunks + kUnit - 1u) / kUnit, item_units); },
+                                       [&](uint32_t i, uint64_t items) {
+                                           return lane_us(op, out_type, all4 ? 4u : 8u, dts[i]) * ((items * item_units + have - 1u) / have);
+                                       });
+        shared = share <= lane;
+    }
     const uint32_t level = shared ? 0u : choose_level(ts, count, lane_slots);
     for (uint32_t i = 0; i < count; ++i) {
         entro_status st = fill_dev_tensor(&ts[i], op, out_type, level, &dts[i]);
@@ -2973,7 +3072,7 @@ static entro_status build_plan(entro_plan *plan, const entro_tensor *ts, uint32_
     const int mode = mode0;
     const unsigned slots = slots0;
     const uint64_t waves = wg_of(mode) / 64u;
-    uint32_t item_units = static_cast<uint32_t>(std::min<uint64_t>(waves, std::max<uint64_t>(1, total_units / slots)));
+    uint32_t item_units = lane_item_units(total_units, slots, static_cast<uint32_t>(waves));
     // Tensors with entry points inside their segments are described a second time, with lanes up to
     // 2^kTailShift times finer (as fine as still tiles into the kernel's blocks): the kernel draws what
     // is left over behind the last whole round of a stretch from that description.  (Not for the GEMV: its partial sums are laid out per lane.)

@@ -466,6 +466,48 @@ def test_runs_in_every_segment_are_counted_once_a_start(bits, out, most):
     assert single <= most * lane, (single, lane)
 
 
+def test_twice_the_segments_take_twice_the_time():
+    # 28672 segments of 8192 symbols fit a wavefront's LDS nine or ten to a workgroup and are still shared, or searched: 2.0 times
+    # the time of half of them (4.5 where they got a lane each)
+    us, calls = [], []
+    for segments in (14336, 28672):
+        gen = torch.Generator(device=DEV)
+        gen.manual_seed(segments)
+        d, q = E.compress_on_device(torch.randn(segments * 8192, device=DEV, generator=gen), 8, E.ENTRO_ASYMMETRIC, 8192, return_q=True)
+        out = torch.zeros(q.numel(), dtype=torch.uint8, device=DEV)
+        t = d.ctensor(out)
+        E.entro_decode(t, E.ENTRO_U8)
+        assert torch.equal(out, q)
+        us.append(_times_us([lambda: E.entro_decode(t, E.ENTRO_U8)])[0])
+    assert us[1] <= 2.6 * us[0], us
+
+
+@pytest.mark.parametrize("bits,most,chunk,segments,shared", [(8, 3.0, 512, 40960, False), (8, 3.0, 512, 14336, True), (4, 9.0, 1024, 40960, False),
+                                                             (4, 9.0, 1024, 24576, True)])
+def test_products_share_pieces_only_where_that_is_not_slower(bits, most, chunk, segments, shared):
+    """The more bits a symbol takes, the more a shared segment costs and the fewer segments are shared.  Of the time of a lane
+    per segment: up to 1.26 (a lane each as well, but the yardstick's stream is a third as long as 7.5 bits a symbol make it),
+    2.1 where the number of segments alone decides."""
+    cols, gen = 1024, torch.Generator(device=DEV)
+    gen.manual_seed(segments)
+    rows = segments * chunk // cols
+    w = torch.randn(rows * cols, device=DEV, generator=gen).clamp_(-most, most)
+    d, q = E.compress_on_device(w, bits, E.ENTRO_ASYMMETRIC, chunk, rows=rows, cols=cols, return_q=True)
+    x = torch.randn(cols, device=DEV, generator=gen).to(torch.bfloat16)
+    lane, plans, ws = E.to_device(_out_of_step(bits, chunk, rows * cols, rows, cols)[0], DEV), [], []
+    ys = [torch.zeros(rows, dtype=torch.float32, device=DEV) for _ in range(2)]
+    for dt, y in zip((d, lane), ys):
+        ts = [dt.ctensor(y, x)]
+        ws.append(torch.zeros(E.entro_workspace_bytes(ts, E.ENTRO_OP_GEMV), dtype=torch.uint8, device=DEV))
+        plans.append(E.entro_plan_init(ts, E.ENTRO_OP_GEMV, E.ENTRO_F32, ws[-1]))
+    assert [p.shared_wave_bytes > 0 for p in plans] == [shared, False]
+    us = _times_us([lambda p=p: E.entro_plan_run(p) for p in plans])
+    terms = (q.view(rows, cols).to(torch.float32) - d.enc.qp.zero_point).double() * float(d.enc.qp.scale) * x.double()
+    # fp32 sums of exact products: at most cols roundings of half an ulp, relative to the terms' magnitudes
+    assert bool(((ys[0].double() - terms.sum(1)).abs() <= (cols + 2) * 2.0 ** -24 * terms.abs().sum(1)).all())
+    assert us[0] <= 1.45 * us[1], us
+
+
 @pytest.mark.parametrize("lengths", [
     list(range(1, 15)) + [15, 15],                 # the deepest complete code over 16 symbols
     [1, 3, 3, 4, 4, 5, 5, 6, 6, 7, 7, 8, 8, 8, 8, 0],   # complete over 15 symbols; codes up to 8 bits
