@@ -2748,20 +2748,21 @@ uint32_t share_waves(uint32_t wave_bytes) { return std::min<uint32_t>(kShareWave
 bool few_segments(uint64_t segments, uint64_t lane_slots) { return segments * 16u <= lane_slots * 3u; }
 
 double lane_us(entro_op op, entro_dtype d, uint32_t bits, const DevTensor &dt) {
-    const double each = op == ENTRO_OP_GEMV ? (bits == 4 ? 0.038 : 0.072) : d == ENTRO_F32 ? (bits == 4 ? 0.042 : 0.094)
+    const double each = op == ENTRO_OP_GEMV ? (bits == 4 ? 0.038 : 0.072) : d == ENTRO_F32 ? (bits == 4 ? 0.045 : 0.098)
                         : d == ENTRO_BF16   ? (bits == 4 ? 0.039 : 0.080) : (bits == 4 ? 0.034 : 0.080);
     return 2.0 + each * dt.chunk_symbols + (op == ENTRO_OP_GEMV ? 0.18 * (dt.n % dt.chunk_symbols) : 0.0);
 }
 
 // `units`: of the workgroup that has most of them.
-double share_us(entro_op op, const DevTensor &dt, uint32_t units, uint32_t waves) {
-    const double full = (dt.bits == 4 ? 12.0 : 4.9 * stream_bits(dt)) + (op == ENTRO_OP_GEMV ? 4.0 : 0.0);   // 16 wavefronts, 4096 symbols each
+double share_us(entro_op op, entro_dtype d, const DevTensor &dt, uint32_t units, uint32_t waves) {
+    const double out = op == ENTRO_OP_GEMV ? 4.0 : d == ENTRO_F32 ? 1.5 : 0.0;
+    const double full = (dt.bits == 4 ? 12.0 : 4.9 * stream_bits(dt)) + out;      // 16 wavefronts, 4096 symbols each
     const double by_size = full * dt.chunk_symbols * dt.share_per / 4096.0;
     const uint32_t rounds = units / waves, last = units % waves;
     return by_size / 30.0 * (rounds * (14.0 + waves) + (last ? 14.0 + last : 0.0));
 }
 
-double find_us(const DevTensor &dt, double rate) { return 3.0 * dt.chunk_symbols * (0.02 + 0.035 * rate); }
+double find_us(const DevTensor &dt, double rate) { return 3.0 * dt.chunk_symbols * (0.04 + 0.04 * rate); }
 
 // A prepared launch gives workgroup b of G the items [b * n / G, (b + 1) * n / G): the longest time that `cost` makes of a
 // workgroup's stretches (items of one tensor side by side), with the time to load a stretch's tables.
@@ -2853,7 +2854,7 @@ entro_status launch_single(const entro_tensor *t, entro_op op, entro_dtype d, fl
     if (few_segments(dt.n_chunks, lane_slots) && share_fits(op, t, &shared, &wave_bytes)) {
         const uint32_t waves = share_launch_waves(shared, wave_bytes, slots);
         const uint32_t rounds = (shared.share_units + slots * waves - 1u) / (slots * waves);
-        const double share = share_us(op, shared, rounds * waves, waves);
+        const double share = share_us(op, d, shared, rounds * waves, waves);
         const double lane = lane_us(op, d, dt.bits, dt) * cut_units(dt);
         DevTensor found = dt;
         if (dt.bits == 8 && dt.chunk_symbols > kShareMost / 2u && cut_segments(op, mode, lane_slots, t, &found)) {
@@ -3020,17 +3021,16 @@ static entro_status build_plan(entro_plan *plan, const entro_tensor *ts, uint32_
     // Measured, prepared launches, before -> now.  2048 x 2048 matrices, 8 bits, pieces of 512: one to bf16 47.6 -> 22.7 us, its
     // product 46.8 -> 23.9; five 90.2 -> 48.8, 85.0 -> 47.8.  Pieces of 1024: 86.2 -> 26.4, 82.4 -> 27.7.  4 bits, pieces of 512:
     // 27.8 -> 15.2, five 53.1 -> 32.3.
-    // Two exceptions, where the tests hold this form's times against others': decoding without entry points keeps a lane per
-    // segment, and so do 4-bit products in pieces of up to 512 symbols whose rows a wavefront adds up itself (2048 x 4096:
-    // 25.6 us, and 19.0 shared).
+    // Without entry points, 4096 x 4096 in segments of 4096: 8 bits to bf16 319 -> 86 us, to bytes 303 -> 80, 4 bits to nibbles
+    // 135 -> 55.  4-bit products whose rows a wavefront adds up itself, pieces of 512: 2048 x 4096 25.3 -> 15.7 us; of 256 they
+    // are not shared: 1024 x 4096 15.1 us, and 17.0 shared (4096 x 1024: 14.9 and 17.3).
     uint64_t segments = 0;
     for (uint32_t i = 0; i < count; ++i) segments += dts[i].n_chunks;
     bool shared = few_segments(segments, lane_slots);
     uint32_t wave_bytes = 1;
     for (uint32_t i = 0; shared && i < count; ++i) {
         uint32_t bytes = 0;
-        shared = (op == ENTRO_OP_GEMV || ts[i].sub_symbols) && !(dts[i].bits == 4 && dts[i].row_lanes && dts[i].chunk_symbols <= 512u) &&
-                 share_fits(op, &ts[i], &dts[i], &bytes);
+        shared = !(op == ENTRO_OP_GEMV && dts[i].bits == 4 && dts[i].row_lanes && dts[i].chunk_symbols < 512u) && share_fits(op, &ts[i], &dts[i], &bytes);
         wave_bytes = std::max(wave_bytes, bytes);
     }
     if (shared) {
@@ -3042,7 +3042,7 @@ static entro_status build_plan(entro_plan *plan, const entro_tensor *ts, uint32_
         const double share = busiest_us(count, slots0, [&](uint32_t i) { return items_of(dts[i].share_units, share_item_units(dts[i].share_per)); },
                                         [&](uint32_t i, uint64_t items) {
                                             const uint64_t n = std::min<uint64_t>(dts[i].share_units, items * share_item_units(dts[i].share_per));
-                                            return share_us(op, dts[i], static_cast<uint32_t>(n), take);
+                                            return share_us(op, out_type, dts[i], static_cast<uint32_t>(n), take);
                                         });
         const double lane = busiest_us(count, slots0, [&](uint32_t i) { return items_of((dts[i].n_chunks + kUnit - 1u) / kUnit, item_units); },
                                        [&](uint32_t i, uint64_t items) {

@@ -216,6 +216,30 @@ def test_staircase_codes_around_the_widths_of_the_tables(bits, deepest):
         _assert_gemv_close(_gpu_gemv(enc, x, E.ENTRO_F32, batch), y_ref)
 
 
+@pytest.mark.parametrize("batch", [False, True])
+@pytest.mark.parametrize("bits,deepest", [(8, 9), (8, 14), (8, 15), (8, 21), (8, 32), (4, 9), (4, 14), (4, 15)])
+def test_lane_per_segment_codes_of_every_length_every_output(bits, deepest, batch):
+    # segments of 384 symbols are too short to be shared by lanes: the kernels that give each a lane, with blocks in full and in
+    # part, two wavefronts of segments and a shorter last one, whose symbols go one by one
+    ln = np.zeros(1 << bits, np.uint8)
+    ln[: deepest + 1] = list(range(1, deepest + 1)) + [deepest]
+    rng = np.random.default_rng(deepest)
+    cols, chunk = 192, 384
+    sym = rng.integers(0, deepest + 1, 211 * cols).astype(np.uint8)
+    stream, off = oracle.encode(sym, ln, oracle.canonical_codes(ln), chunk)
+    qp = B.QParams(np.float32(0.25), 7, bits, E.ENTRO_ASYMMETRIC)
+    enc = B.EncodedTensor(stream, off, sym.size, chunk, E.entro_codebook_from_lengths(ln, bits), qp, sym.size // cols, cols)
+    x = synth.make_x_bf16(9, deepest, cols)
+    y_ref, _ = oracle.gemv(sym, enc.rows, cols, 0.25, 7, x)
+    assert np.array_equal(_gpu_decode(enc, E.ENTRO_U8, batch), sym)
+    assert np.array_equal(_gpu_dequant(enc, E.ENTRO_F32, batch), oracle.dequant_f32(sym, 0.25, 7))
+    assert np.array_equal(_gpu_dequant(enc, E.ENTRO_BF16, batch), oracle.dequant_bf16(sym, 0.25, 7))
+    if bits == 4:
+        assert np.array_equal(_gpu_decode(enc, E.ENTRO_U4_PACKED, batch), oracle.pack_u4(sym))
+    _assert_gemv_close(_gpu_gemv(enc, x, E.ENTRO_F32, batch), y_ref)
+    _assert_gemv_close(_gpu_gemv(enc, x, E.ENTRO_BF16, batch), y_ref, tol=5e-3)   # y itself rounded to bf16
+
+
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("chunk,segments,last", [
     (512, 3, 0), (1024, 9, 0), (4096, 5, 0), (8192, 2, 0), (4096, 3, 1), (4096, 2, 63), (4096, 2, 65), (4096, 1, 4095), (3072, 4, 257),
@@ -373,21 +397,23 @@ def test_runs_of_codes_around_the_starts_that_a_lane_keeps(chunk, sub, run_len):
 
 @pytest.mark.parametrize("bits,chunk", [(8, 4096), (8, 512), (4, 4096)])
 def test_segments_without_entry_points_whose_offsets_do_not_fit(bits, chunk):
-    # a segment starts where the table says and holds the symbols that it holds, wherever the table puts its end
+    # a segment starts where the table says and holds the symbols that it holds, wherever the table puts its end: as the oracle
+    # decodes it
     sym = _with_runs(bits, chunk, 5, chunk // 2 + 3, 0.5, 64, 1)
     enc = _oracle_encoded(sym, bits, chunk, 1, sym.size, 0.25, 7)
     true = enc.offsets.copy()
     for end in (true[-1] - 300, true[-2], true[-2] - 5, np.uint64(0), true[-1] + 900, np.uint64(1) << np.uint64(63)):
         enc.offsets = true.copy()
         enc.offsets[-1] = end
-        assert np.array_equal(_gpu_decode(enc, E.ENTRO_U8), sym)
-        assert np.array_equal(_gpu_dequant(enc, E.ENTRO_BF16), oracle.dequant_bf16(sym, 0.25, 7))
+        for batch in (False, True):
+            assert np.array_equal(_gpu_decode(enc, E.ENTRO_U8, batch), sym)
+            assert np.array_equal(_gpu_dequant(enc, E.ENTRO_BF16, batch), oracle.dequant_bf16(sym, 0.25, 7))
     for shift in (-37, 41):                                    # segment 2 begins inside a neighbour: as one lane decodes it
         enc.offsets = true.copy()
         enc.offsets[2] = np.uint64(int(true[2]) + shift)
-        got = _gpu_decode(enc, E.ENTRO_U8)
-        assert np.array_equal(got, _gpu_decode(enc, E.ENTRO_U8, batch=True))
-        assert np.array_equal(got[: 2 * chunk], sym[: 2 * chunk]) and np.array_equal(got[3 * chunk:], sym[3 * chunk:])
+        ref = oracle.decode_chunks(enc.stream, enc.offsets, sym.size, chunk, enc.cb.lengths(), enc.cb.codes(), 2, 1, sym.copy())
+        for batch in (False, True):
+            assert np.array_equal(_gpu_decode(enc, E.ENTRO_U8, batch), ref)
 
 
 def _times_us(calls, inner=5):
@@ -464,6 +490,49 @@ def test_runs_in_every_segment_are_counted_once_a_start(bits, out, most):
     sym = _with_runs(bits, 8192, 4096, 0, 0.9, 1, 3)
     single, lane = _single_and_lane_per_segment_us(sym, bits, 8192, out)
     assert single <= most * lane, (single, lane)
+
+
+@pytest.mark.parametrize("bits,out", [(8, E.ENTRO_BF16), (8, E.ENTRO_U8), (4, E.ENTRO_U4_PACKED)])
+def test_prepared_decoding_without_entry_points_shares_segments(bits, out):
+    # 4096 segments of 4096 symbols: 0.31, 0.29 and 0.41 of a lane per segment's time
+    sym = _with_runs(bits, 4096, 4096, 0, 0.0, 1, 3)
+    encs = [_oracle_encoded(sym, bits, 4096, 1, sym.size, 0.25, 7), _out_of_step(bits, 4096, sym.size)[0]]
+    op = E.ENTRO_OP_DEQUANT if out == E.ENTRO_BF16 else E.ENTRO_OP_DECODE
+    y = torch.zeros(sym.size, dtype=torch.bfloat16 if out == E.ENTRO_BF16 else torch.uint8, device=DEV)
+    dts, plans = [E.to_device(e, DEV) for e in encs], []
+    ws = [torch.zeros(E.entro_workspace_bytes([d.ctensor(y)], op), dtype=torch.uint8, device=DEV) for d in dts]
+    for d, w in zip(dts, ws):
+        plans.append(E.entro_plan_init([d.ctensor(y)], op, out, w))
+    assert [p.shared_wave_bytes > 0 for p in plans] == [True, False]
+    us = _times_us([lambda p=p: E.entro_plan_run(p) for p in plans])
+    assert us[0] <= 0.6 * us[1], us
+    E.entro_plan_run(plans[0])
+    if out == E.ENTRO_BF16:
+        assert np.array_equal(y.view(torch.int16).cpu().numpy().view(np.uint16), oracle.dequant_bf16(sym, 0.25, 7))
+    else:
+        assert np.array_equal(y.cpu().numpy()[: sym.size * bits // 8], sym if bits == 8 else oracle.pack_u4(sym))
+
+
+@pytest.mark.parametrize("sub,shared", [(512, True), (256, False)])
+def test_products_of_4bit_rows_in_pieces(sub, shared):
+    # 16384 pieces, rows of eight of them: shared in pieces of 512 (15.7 us, 25.3 with a lane each), not of 256 (17.3, and 14.9)
+    rows, cols = 2048, 8 * sub
+    enc, sym = _out_of_step(4, 16 * sub, rows * cols, rows, cols, sub)
+    rng = np.random.default_rng(sub)
+    bell = np.clip(np.rint(rng.laplace(size=rows * cols) * 0.7 + 7), 0, 15).astype(np.uint8)
+    x = synth.make_x_bf16(9, sub, cols)
+    xd = torch.from_numpy(x.view(np.int16)).to(DEV).view(torch.bfloat16)
+    us, plans = [], []
+    for e, s in ((_oracle_encoded(bell, 4, 16 * sub, rows, cols, 0.25, 7, sub), bell), (enc, sym)):
+        dt, y = E.to_device(e, DEV), torch.zeros(rows, dtype=torch.float32, device=DEV)
+        ts = [dt.ctensor(y, xd)]
+        ws = torch.zeros(E.entro_workspace_bytes(ts, E.ENTRO_OP_GEMV), dtype=torch.uint8, device=DEV)
+        plans.append(E.entro_plan_init(ts, E.ENTRO_OP_GEMV, E.ENTRO_F32, ws))
+        us.append(_times_us([lambda: E.entro_plan_run(plans[-1])], 20)[0])
+        y_ref, _ = oracle.gemv(s, rows, cols, 0.25, 7, x)
+        _assert_gemv_close(y.cpu().numpy().astype(np.float64), y_ref)
+    assert [p.shared_wave_bytes > 0 for p in plans] == [shared, False]
+    assert not shared or us[0] <= 0.85 * us[1], us
 
 
 def test_twice_the_segments_take_twice_the_time():
