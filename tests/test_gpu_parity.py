@@ -395,6 +395,60 @@ def test_runs_of_codes_around_the_starts_that_a_lane_keeps(chunk, sub, run_len):
     assert np.array_equal(_gpu_dequant(enc, E.ENTRO_BF16), oracle.dequant_bf16(sym, 0.25, 7))
 
 
+# segments longer than lanes share in LDS: 8 to 64 lanes look for their starts in each (find_start)
+SEARCHED = [(8, 16384, 70), (8, 12288, 300), (8, 65536, 5), (8, 8704, 9), (8, 1 << 20, 1), (4, 16384, 70), (4, 12288, 9), (4, 65536, 5), (4, 1 << 20, 1)]
+
+
+@pytest.mark.parametrize("bits,chunk,segments", SEARCHED)
+@pytest.mark.parametrize("fraction,every", [(0.0, 1), (0.5, 3), (0.97, 2)])
+def test_long_segments_without_entry_points_every_output(bits, chunk, segments, fraction, every):
+    # bell-shaped symbols, and runs on which the wavefronts that hold them give the search up
+    for last in (0, 1, 63, chunk // 3 + 1, chunk - 1):
+        if chunk == 1 << 20 and last not in (0, chunk // 3 + 1):
+            continue
+        sym = _with_runs(bits, chunk, segments, last, fraction, every, last % 7)
+        sym[sym.size // 2], sym[-1] = 0, (1 << bits) - 1
+        enc = _oracle_encoded(sym, bits, chunk, 1, sym.size, 0.25, 7)
+        assert np.array_equal(_gpu_decode(enc, E.ENTRO_U8), sym)
+        assert np.array_equal(_gpu_dequant(enc, E.ENTRO_F32), oracle.dequant_f32(sym, 0.25, 7))
+        assert np.array_equal(_gpu_dequant(enc, E.ENTRO_BF16), oracle.dequant_bf16(sym, 0.25, 7))
+        if bits == 4:
+            assert np.array_equal(_gpu_decode(enc, E.ENTRO_U4_PACKED), oracle.pack_u4(sym))
+
+
+@pytest.mark.parametrize("bits,chunk,segments", SEARCHED)
+def test_long_segments_whose_offsets_do_not_fit(bits, chunk, segments):
+    sym = _with_runs(bits, chunk, segments, chunk // 2 + 3, 0.0, 1, 1)
+    enc = _oracle_encoded(sym, bits, chunk, 1, sym.size, 0.25, 7)
+    true = enc.offsets.copy()
+    for end in (true[-1] - 300, true[-2], true[-2] - 5, np.uint64(0), true[-1] + 900, np.uint64(1) << np.uint64(63)):
+        enc.offsets = true.copy()
+        enc.offsets[-1] = end
+        assert np.array_equal(_gpu_decode(enc, E.ENTRO_U8), sym)
+        assert np.array_equal(_gpu_dequant(enc, E.ENTRO_BF16), oracle.dequant_bf16(sym, 0.25, 7))
+    k = segments // 2
+    for shift in (-37, 41) if k else ():                       # a segment begins inside a neighbour: as the oracle decodes it
+        enc.offsets = true.copy()
+        enc.offsets[k] = np.uint64(int(true[k]) + shift)
+        ref = oracle.decode_chunks(enc.stream, enc.offsets, sym.size, chunk, enc.cb.lengths(), enc.cb.codes(), k, 1, sym.copy())
+        assert np.array_equal(_gpu_decode(enc, E.ENTRO_U8), ref)
+
+
+def test_dense_segments_of_8192_are_searched():
+    # where the search for starts is the faster of the two, though the segments fit LDS: 4096 of them at 7.5 bits a symbol
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(5)
+    w = torch.randn(4096 * 8192 - 1000, device=DEV, generator=gen).clamp_(-3.0, 3.0)
+    d, q = E.compress_on_device(w, 8, E.ENTRO_ASYMMETRIC, 8192, return_q=True)
+    out = torch.zeros(q.numel(), dtype=torch.uint8, device=DEV)
+    E.entro_decode(d.ctensor(out), E.ENTRO_U8)
+    assert torch.equal(out, q)
+    for out_type, dtype in ((E.ENTRO_F32, torch.float32), (E.ENTRO_BF16, torch.bfloat16)):
+        y = torch.zeros(q.numel(), dtype=dtype, device=DEV)
+        E.entro_decode_dequant(d.ctensor(y), out_type)
+        assert torch.equal(y, ((q.to(torch.float32) - d.enc.qp.zero_point) * float(d.enc.qp.scale)).to(dtype))
+
+
 @pytest.mark.parametrize("bits,chunk", [(8, 4096), (8, 512), (4, 4096)])
 def test_segments_without_entry_points_whose_offsets_do_not_fit(bits, chunk):
     # a segment starts where the table says and holds the symbols that it holds, wherever the table puts its end: as the oracle

@@ -78,7 +78,8 @@ def host_search(tmp_path_factory):
 
 
 @pytest.mark.parametrize("bits,chunk,shift", [(8, 4096, 6), (8, 2048, 5), (8, 1024, 4), (8, 512, 3), (8, 448, 3),
-                                              (4, 8192, 6), (4, 4096, 5), (4, 2048, 4)])
+                                              (4, 8192, 6), (4, 4096, 5), (4, 2048, 4),
+                                              (8, 16384, 6), (8, 12288, 6), (8, 65536, 3), (4, 16384, 6), (4, 12288, 5), (4, 65536, 4)])
 @pytest.mark.parametrize("run", [False, True])
 def test_starts_inside_segments_are_the_true_ones(host_search, bits, chunk, shift, run):
     """Every piece's start bit, as 8 to 64 lanes per segment find it, against the sum of the code lengths in front of it;
