@@ -363,8 +363,7 @@ def test_tensors_of_different_segments_shared_in_one_launch(y_type):
 
 
 @pytest.mark.parametrize("bits,chunk,segments", [(8, 8192, 2700), (8, 1024, 17000), (4, 512, 41000), (8, 512, 49152), (8, 512, 49153)])
-def test_more_shared_segments_than_wavefronts_and_the_line_to_a_lane_each(bits, chunk, segments):
-    # (the prepared launch of the same tensor gives every segment a lane)
+def test_more_segments_than_wavefronts_single_calls(bits, chunk, segments):
     gen = torch.Generator(device=DEV)
     gen.manual_seed(segments)
     w = torch.randn(segments * chunk, device=DEV, generator=gen)
@@ -393,6 +392,30 @@ def test_runs_of_codes_around_the_starts_that_a_lane_keeps(chunk, sub, run_len):
     assert np.array_equal(_gpu_decode(enc, E.ENTRO_U8), sym)
     assert np.array_equal(_gpu_decode(enc, E.ENTRO_U8, batch=True), sym)
     assert np.array_equal(_gpu_dequant(enc, E.ENTRO_BF16), oracle.dequant_bf16(sym, 0.25, 7))
+
+
+@pytest.mark.parametrize("out_type,dtype,waves", [(E.ENTRO_U8, torch.uint8, 14), (E.ENTRO_F32, torch.float32, 16), (E.ENTRO_BF16, torch.bfloat16, 16)])
+def test_the_line_between_shared_segments_and_a_lane_each(out_type, dtype, waves):
+    # three sixteenths of the lanes that the device holds for this output, and one segment more; peaked data, whose lookups answer
+    # many codes, so that the launch's estimated time does not draw the line before
+    line = torch.cuda.get_device_properties(0).multi_processor_count * 64 * waves * 3 // 16
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(waves)
+    op = E.ENTRO_OP_DECODE if out_type == E.ENTRO_U8 else E.ENTRO_OP_DEQUANT
+    for segments in (line, line + 1):
+        w = torch.randn(segments * 512, device=DEV, generator=gen).pow_(3)
+        d, q = E.compress_on_device(w, 8, E.ENTRO_ASYMMETRIC, 512, return_q=True)
+        ref = q if out_type == E.ENTRO_U8 else ((q.to(torch.float32) - d.enc.qp.zero_point) * float(d.enc.qp.scale)).to(dtype)
+        y = torch.zeros(q.numel(), dtype=dtype, device=DEV)
+        t = d.ctensor(y)
+        ws = torch.zeros(E.entro_workspace_bytes([t], op), dtype=torch.uint8, device=DEV)
+        plan = E.entro_plan_init([t], op, out_type, ws)
+        assert (plan.shared_wave_bytes > 0) == (segments == line)
+        E.entro_plan_run(plan)
+        assert torch.equal(y, ref)
+        y.zero_()
+        (E.entro_decode if op == E.ENTRO_OP_DECODE else E.entro_decode_dequant)(t, out_type)
+        assert torch.equal(y, ref)
 
 
 # segments longer than lanes share in LDS: 8 to 64 lanes look for their starts in each (find_start)
