@@ -128,10 +128,11 @@ typedef struct {
     uint32_t count;       /* tensors */
     uint32_t n_items;     /* work items in the launch */
     uint32_t n_fix;       /* GEMV: rows that need the second-stage sum */
-    uint32_t item_units;  /* units (the segments or pieces of one tensor that the 64 lanes of a wavefront take) per work item */
-    uint32_t pair_tables; /* 1: every tensor holds 4-bit symbols, the kernels decode two per table lookup */
+    uint32_t item_units;  /* units (the segments or pieces of one tensor that the 64 lanes of a wavefront take) per work item; not used
+                           * where shared_wave_bytes is not 0: an item is then about 64 segments of a tensor */
+    uint32_t pair_tables; /* 1: every tensor holds 4-bit symbols, the kernels decode two per table lookup (unless shared_wave_bytes) */
     uint32_t gemv_multirow; /* 1: a tensor's segments are longer than its matrix rows (information only) */
-    uint32_t wide_tables; /* 1: GEMV over 8-bit tensors with zero-points in [-1, 256]: table entries hold the centred value */
+    uint32_t wide_tables; /* 1: GEMV over 8-bit tensors with zero-points in [-1, 256]: table entries hold the centred value (unless shared_wave_bytes) */
     uint32_t shared_wave_bytes; /* 0, or the LDS of a wavefront where the lanes of a small launch share segments or pieces */
     uint64_t off_tensors, off_items, off_partials, off_fix;   /* byte offsets inside the workspace */
 } entro_plan;
@@ -277,7 +278,7 @@ uint64_t entro_workspace_bytes(const entro_tensor *ts, uint32_t count, entro_op 
  * decides how many units a work item holds and, for tensors with entry points
  * inside their segments, how many pieces a lane takes: as coarse as still gives
  * the device's lanes work; launches too small for that let several lanes share a
- * piece or segment, see shared_wave_bytes): run the plan on the device it was prepared on.  The
+ * piece or segment where that is estimated to be faster, see shared_wave_bytes): run the plan on the device it was prepared on.  The
  * launch is one workgroup per compute unit at most; inside a workgroup the
  * wavefronts draw their segments from a counter, so which wavefront decodes which
  * segment differs from run to run, the result does not.  (A GEMV's sums are taken

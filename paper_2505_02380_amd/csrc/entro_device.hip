@@ -256,10 +256,8 @@ __device__ __forceinline__ void wave_sync_lds() {
 
 // Tables that a launch's preparation has built, from memory into LDS by the whole workgroup of WG lanes: every lane asks for
 // its 16-byte pieces at once.
-// (In a loop each step waited for its piece, four or five times the way to the L2 and back.)  Measured with seg_start's fifteen
-// loads at once, before -> now: 24-layer set to bytes 838 -> 815 us, phi3-shaped to nibbles 891 -> 868,
-// seven tensors validated and launched to bf16 180 -> 176, 4-bit products of the phi3 shapes 33.4 -> 32.6, 26.2 -> 25.5, and
-// through seg_start alone the step over 32 layers of 8-bit products 6224 -> 6111.
+// (In a loop each step waited for its piece, four or five times the way to the L2 and back.)  Measured, loop -> now: step over
+// 32 layers of 4-bit products 4086 -> 4036 us; launches of longer stretches do not notice (24-layer set to bytes 804).
 template <uint32_t BYTES, uint32_t WG>
 __device__ __forceinline__ void copy_tables(void *dst, const void *src) {
     static_assert(BYTES % 16 == 0, "16-byte pieces");
@@ -534,7 +532,9 @@ __device__ __forceinline__ uint64_t seg_start(const DevTensor &t, uint32_t k) {
     const global_u16_ptr sb = (global_u16_ptr)t.sub + (static_cast<uint64_t>(c) << (sh + t.sub_merge));
     const uint64_t base = offsets[c];
     // All fifteen are asked for at once, the segment's first entry in the place of those that the lane does not need: loads
-    // under a condition each came back one after the other.  Measured with copy_tables: see there.
+    // under a condition each came back one after the other.  Measured, before -> now: 24-layer set to bytes 831 -> 799 us,
+    // phi3-shaped 4-bit set to nibbles 882 -> 857, one layer of seven tensors validated and launched to bf16 194 -> 190, steps
+    // over 32 layers of 8-bit products 6205 -> 6098 and of 4-bit products 4167 -> 4036.
     uint32_t len[ENTRO_MAX_SUB_PER_CHUNK - 1], add = 0;
 #pragma unroll
     for (uint32_t i = 0; i + 1 < ENTRO_MAX_SUB_PER_CHUNK; ++i) len[i] = sb[i < before ? i : 0u];
@@ -1938,7 +1938,7 @@ __global__ __launch_bounds__(64 * Cfg<MODE>::waves) void k_tables(const DevTenso
 
 // ---------------------------------------------------------------- segments shared by a wavefront's lanes
 // Small launches (k_shared, k_shared_batch).  What bounds them is not the bytes but one lane's serial chain of lookups, so
-// 2^part_shift lanes share a segment, about 64 symbols each, and a lookup answers up to four codes at once.
+// 2^share_shift lanes share a segment, about 64 symbols each, and a lookup answers up to four codes at once.
 //   1. The unit's part of the stream (the segments of a wavefront lie side by side) comes into LDS in whole lines.
 //   2. Each lane takes an equal stretch of its segment's bits and counts the codes that start in it, from a guessed first
 //      bit: Huffman codes fall into step with the true boundaries within a few codes.  Then a lane whose neighbour ended
@@ -2172,7 +2172,7 @@ __device__ __forceinline__ void share_store(const DevTensor &t, lds_w32 sym, uin
 // The rows of the product that m symbols in LDS, the tensor's from u0 on, hold in full or in part.  As many
 // lanes take a row as have eight columns each of it (a power of two, at most all), several rows at a time where rows are short.
 // cols and m are multiples of 8, u0 of 128: eight columns lie side by side, and their activations on 16 bytes.
-// A row that does not lie in the unit as a whole leaves a partial sum, as k_fix_* reads it (chunk_symbols: the unit's).
+// A row that does not lie in the unit as a whole leaves a partial sum, as k_fix_* reads it (fix_symbols: the unit's).
 template <int MODE>
 __device__ __forceinline__ void share_rows(const DevTensor &t, lds_w32 sym, uint32_t unit, uint64_t u0, uint32_t m) {
     const uint32_t lane = threadIdx.x & 63u, cols = t.cols;
