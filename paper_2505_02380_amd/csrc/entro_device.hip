@@ -2739,11 +2739,11 @@ uint32_t share_waves(uint32_t wave_bytes) { return std::min<uint32_t>(kShareWave
 // symbol behind that (4096 segments of 4096 in rows of 11008: 864 us, 298 without one).
 // Shared: rounds of units, one a wavefront.  A round's time goes with the bits (more of them, fewer codes a lookup; 4-bit symbols
 // leave a lookup's four codes as the limit), with the symbols of a unit, and less than in proportion with the wavefronts.
-// Searched (find_start): every piece is decoded three times, slower the more bits a symbol has; below 4096 symbols a segment the
+// Searched (find_start): every piece is decoded three times, slower the more bits a symbol has; up to 4096 symbols a segment the
 // search gives up on dense codes and has cost a lane per segment then (4096 x 4096 at 7.5 bits to bf16 296 us, 86 shared).
 // Measured, a lane per segment -> shared, at the places where the choice turns.  Prepared products of 8 bits: 40960 segments of
 // 512 symbols at 3.5 bits 48 -> 42 us, at 5.4 54.7 -> 57.1, at 7.5 46 -> 80; of 4096 at 5.2 338 -> 363; 28672 of 4096 at 6.5
-// 396 -> 292, at 7.5 314 -> 346.  Of 4 bits: 40960 of 1024 44.3 -> 53.5, 28672 39.9 -> 41.7.  Single calls to bytes: 28672 of
+// 396 -> 292, at 7.5 314 -> 346.  Of 4 bits: 40960 of 1024 44.3 -> 53.5, 28672 43.1 -> 37.8.  Single calls to bytes: 28672 of
 // 8192 at 3.3 bits searched 631, shared 295.
 bool few_segments(uint64_t segments, uint64_t lane_slots) { return segments * 16u <= lane_slots * 3u; }
 
@@ -3023,7 +3023,7 @@ static entro_status build_plan(entro_plan *plan, const entro_tensor *ts, uint32_
     // 27.8 -> 15.2, five 53.1 -> 32.3.
     // Without entry points, 4096 x 4096 in segments of 4096: 8 bits to bf16 319 -> 86 us, to bytes 303 -> 80, 4 bits to nibbles
     // 135 -> 55.  4-bit products whose rows a wavefront adds up itself, pieces of 512: 2048 x 4096 25.3 -> 15.7 us; of 256 they
-    // are not shared: 1024 x 4096 15.1 us, and 17.0 shared (4096 x 1024: 14.9 and 17.3).
+    // are not shared: 4096 x 1024 at 1.5 bits a symbol 15.3 us, and 17.0 shared, at 3.6 bits 14.9 and 17.3.
     uint64_t segments = 0;
     for (uint32_t i = 0; i < count; ++i) segments += dts[i].n_chunks;
     bool shared = few_segments(segments, lane_slots);
