@@ -132,7 +132,9 @@ typedef struct {
                            * where shared_wave_bytes is not 0: an item is then about 64 segments of a tensor */
     uint32_t pair_tables; /* 1: every tensor holds 4-bit symbols, the kernels decode two per table lookup (unless shared_wave_bytes) */
     uint32_t gemv_multirow; /* 1: a tensor's segments are longer than its matrix rows (information only) */
-    uint32_t wide_tables; /* 1: GEMV over 8-bit tensors with zero-points in [-1, 256]: table entries hold the centred value (unless shared_wave_bytes) */
+    uint32_t wide_tables; /* 1: GEMV over 8-bit tensors with zero-points in [-1, 256]: table entries hold the centred value (unless shared_wave_bytes);
+                           * 2: GEMV whose lanes take about 64 symbols each, from places that the preparation noted in the workspace; item_units
+                           * then counts units of 64 such lanes, or whole rows */
     uint32_t shared_wave_bytes; /* 0, or the LDS of a wavefront where the lanes of a small launch share segments or pieces */
     uint64_t off_tensors, off_items, off_partials, off_fix;   /* byte offsets inside the workspace */
 } entro_plan;
@@ -264,8 +266,8 @@ entro_status entro_decode_gemv_static(const entro_tensor *t, entro_dtype y_type,
 
 /* Batched forms: ONE launch over `count` tensors (a single tensor has too few of
  * Fig. 3's segments to fill 256 compute units).  The descriptor table, the work list,
- * the tensors' lookup tables (about 68 KB per tensor) and the GEMV partial sums live
- * in `workspace` (device). */
+ * the tensors' lookup tables (about 68 KB per tensor), the GEMV partial sums and the places
+ * that a GEMV's preparation notes (4 bytes per 64 symbols) live in `workspace` (device). */
 uint64_t entro_workspace_bytes(const entro_tensor *ts, uint32_t count, entro_op op);
 
 /* Prepare a batched launch of Fig. 3's segment-parallel decode (or of the fused forms above):
@@ -273,7 +275,11 @@ uint64_t entro_workspace_bytes(const entro_tensor *ts, uint32_t count, entro_op 
  * that builds every tensor's lookup tables there (so that the launches need not).  BLOCKS until
  * the copy, and with it everything enqueued on hip_stream before, has completed (the
  * table is staged in memory that dies with the call); entro_plan_init_staged does not.
- * The tensors' device buffers are referenced, not copied.
+ * The tensors' device buffers are referenced, not copied.  A GEMV's preparation also walks their
+ * streams once and notes where the codes of every 64 symbols or so begin, so that the launches'
+ * lanes need not start at segments or pieces; every launch checks what was noted against the
+ * tensors' own tables, so buffers may be filled or given other contents after this call, but the next
+ * launch is then slower (it notes the places anew as it goes).
  * The work list is cut for the current device (its number of compute units
  * decides how many units a work item holds and, for tensors with entry points
  * inside their segments, how many pieces a lane takes: as coarse as still gives

@@ -94,6 +94,14 @@ struct DevTensor {
     uint32_t share_shift;       // k_shared*: log2 of the lanes that share a segment (or piece)
     uint32_t share_per;         // segments of a unit, at most 64 >> share_shift (0: the tensor does not go there)
     uint32_t share_units;       // units of the tensor
+    uint32_t *fine_index;       // k_fine: where the chains of every lane begin (workspace)
+    uint32_t fine_len;          // symbols of a lane, a multiple of 8 up to 64 (0: the tensor does not go there)
+    uint32_t fine_first;        // of them its first chain's
+    uint32_t fine_n;            // lanes of the tensor
+    uint32_t fine_pieces;       // pieces of chunk_symbols symbols in a unit of 64 lanes
+    uint32_t fine_rows;         // how rows come about: kFineRow, kFineUnits, kFineParts
+    uint32_t fine_units;        // units that a wavefront takes one after the other: a row's, or one
+    uint32_t fine_quanta;       // how many of those the tensor has
     uint8_t len[256];
 };
 
@@ -2449,6 +2457,545 @@ __global__ __launch_bounds__(kFixWG) void k_fix_batch(const DevTensor *__restric
     fix_row<MODE>(tensors[it.tensor], it.first + threadIdx.x / 16u, threadIdx.x & 15u);
 }
 
+// ---------------------------------------------------------------- products of prepared launches: lanes of about 64 symbols
+// k_fine.  A token step is a chain of small launches, each as long as one lane's serial chain of lookups behind the launch and
+// its cold reads.  With a lane per piece of 256 or 512 symbols that chain took 15 to 50 us, and sharing pieces as k_shared does
+// costs three passes.  So the preparation of a launch, which a program pays once for all its steps, walks the streams once
+// (k_fine_index) and notes where the codes of every `fine_len` symbols begin: 32 bits per 64 symbols, kept beside the tables.
+//   A wavefront's unit is 64 lanes of fine_len symbols side by side, whole pieces of the tensor.  A lane decodes its symbols as
+//   two chains, interleaved (what limits a compute unit are the round trips to LDS, and LDS holds sixteen wavefronts at most).
+//   Its stream, at most 64 bytes, is asked for in one go a unit ahead and lies in a column of LDS: no ring, no refills.
+//   Rows are cut into lanes so that a wavefront holds whole rows, or goes through a row unit by unit, where the shape allows it.
+// The noted places are a guess, as in k_shared: the unit's first bit is read from the tensor's own tables on every run, every
+// chain has to end where the next one begins, and so by induction all of them are true, whatever the streams hold by now.  A
+// unit that fails is decoded piece by piece from the tensor's tables (fine_slow), which also notes its places anew.
+//   Measured, a lane per piece -> now, us a launch.  8 bits, 3.5 bits a symbol: 25 M symbols in rows of 4096 36 -> 22, 16.8 M 31 -> 16,
+// 117 M 74 -> 46, 58.7 M in rows of 14336 44 and 5 for the second stage -> 34; the step over 32 layers 6098 -> 3881.  4 bits, 1.55
+// bits a symbol: 9.4 M symbols in rows of 3072, shared by k_shared_batch before, 28 -> 10; the step over 32 layers 4035 -> 1863.
+//   What bounds a large launch now: the LDS pipe is busy in 0.6 of the cycles (over half of that bank conflicts of the lookups) and
+// the vector ALUs in 0.55; a small one: about 6 us of cold reads one behind the other (item, description, places, stream) and what
+// a launch takes by itself.
+constexpr uint32_t kFineWaves = 16;
+constexpr uint32_t kFineData = 16;                       // dwords of stream that a lane holds
+constexpr uint32_t kFineX = 14848;                       // columns of the activations that LDS has room for
+constexpr uint32_t kFineEnd = 32u * (kFineData + 1u);    // position of the first bit behind them
+constexpr uint32_t kFineRow = 1, kFineUnits = 2, kFineParts = 3;   // a unit holds whole rows cut into 2^i lanes; a row is whole units; any
+
+struct alignas(16) FineMem {
+    Tables32 tb;
+    // Dword d of a lane's column lies at (16 * wave + d) * 64 + lane; 1 to 16 hold its stream.  A window's stale bits come from
+    // dword 0 and what it reads behind the lane's codes from 17 to 19: whatever the neighbours have there.
+    uint32_t col[(kFineWaves * kFineData + 4u) * 64u];
+    u32x4 x[kFineX / 8u];
+    uint32_t next;
+};
+static_assert(sizeof(FineMem) <= 160u * 1024u, "one workgroup per compute unit");
+typedef u32x4 __attribute__((aligned(4))) u32x4_a4;
+typedef const void __attribute__((address_space(1))) *global_void_ptr;
+typedef void __attribute__((address_space(3))) *lds_void_ptr;
+typedef const u32x4_a4 __attribute__((address_space(1))) *global_u4a4_ptr;
+typedef const uint32_t __attribute__((address_space(1))) *global_u32_ptr;
+
+// The code at the start of `w` among those of `from` bits and more.  (Not decode_canonical: a call, even one that is never made,
+// takes half the registers of the kernel around it.)
+__device__ __forceinline__ uint32_t fine_search(const TablesTail &tb, uint32_t w, uint32_t from, uint32_t max_len) {
+    const uint32_t v = __brev(w);
+#pragma unroll 1
+    for (uint32_t l = from; l <= max_len; ++l) {
+        const uint32_t d = (v >> (32 - l)) - tb.first[l];
+        if (d < tb.cnt[l]) return pack_entry(tb.sorted[tb.offs[l] + d], l);
+    }
+    return pack_entry(0, 1);                             // not a code (corrupt stream): keep moving
+}
+// One code, whatever its length.
+template <bool PAIR>
+__device__ __forceinline__ uint32_t fine_single(const Tables32 &tb, uint32_t w, uint32_t max_len) {
+    uint32_t e = PAIR ? tb.lut2[w & ((1u << kSingleBits) - 1u)] : tb.lut[w & kL1Mask];
+    if (entry_len(e) == 0) {
+        e = PAIR ? 0u : lookup_l2(tb, e, w);
+        if (e == 0) e = fine_search(tb, w, PAIR ? kSingleBits + 1 : kL1 + 1, max_len);
+    }
+    return e;
+}
+
+__device__ __forceinline__ uint16_t fine_note(uint32_t bits) { return static_cast<uint16_t>(bits < 0xffffu ? bits : 0xffffu); }
+
+// The places of all chains of the tensors of a prepared launch (blockIdx.y: the tensor, described with a lane per piece), noted
+// on a walk through the pieces with the block path's reader.
+// What it costs a preparation, against a walk by single loads from memory (which reads every line many times over): a launch over
+// 58.7 M symbols of 8 bits 692 -> 83 us, over 50 M symbols of 4 bits 247 -> 50 us.
+template <bool PAIR>
+__global__ __launch_bounds__(64 * kFineWaves) void k_fine_index(const DevTensor *__restrict__ tensors) {
+    __shared__ struct {
+        Tables tb;
+        uint32_t ring[kFineWaves][kRing2Dwords * 64];
+    } sm;
+    constexpr uint32_t SPG = PAIR ? 8u : 4u;             // symbols of a group
+    const DevTensor &t = tensors[blockIdx.y];
+    if (blockIdx.x * 1024u >= t.n_chunks) return;
+    build_tables<64 * kFineWaves, PAIR>(t, sm.tb, &sm.ring[0][0]);
+    const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
+    const uint32_t P = t.chunk_symbols, L = t.fine_len, A = t.fine_first, per = t.fine_pieces, max_len = t.max_len;
+    uint16_t *index = reinterpret_cast<uint16_t *>(t.fine_index);
+    for (uint32_t first = blockIdx.x * 1024u + wave * 64u; first < t.n_chunks; first += gridDim.x * 1024u) {
+        const bool live = first + lane < t.n_chunks;
+        const uint32_t k = live ? first + lane : first;  // (a lane without a piece walks the wavefront's first and notes nothing)
+        const uint32_t unit = k / per, in_unit = (k - unit * per) * P;
+        const uint64_t left = t.n - static_cast<uint64_t>(k) * P;
+        const uint32_t nsym = !live ? 0u : left < P ? static_cast<uint32_t>(left) : P;
+        const uint32_t base = static_cast<uint32_t>(seg_start(t, unit * per));
+        uint32_t at = in_unit / L, i = in_unit - at * L; // the lane of the unit and the symbol of it that the walk has come to
+        at += unit * 64u;
+        Ring2 r;
+        r.stale = Tables::stale;
+        r.stream = t.stream;
+        r.last_blk = t.stream_bytes - 16u;
+        r.ring = (lds_v32)(sm.ring[wave] + lane);
+        ring2_fill<false>(r, seg_start(t, k));
+        for (uint32_t s = 0; s < P; s += 8u * SPG) {
+#pragma unroll
+            for (uint32_t g = 0; g < 8; ++g) {
+                if (g % kTripGroups == 0)
+                    if (__builtin_expect(ring_short(r, kTripBits - 64), 0)) ring_reload(r);
+                if (PAIR || g % 2u == 0) {               // a chain begins at a multiple of eight symbols
+                    if ((i == 0 || i == A) && s + g * SPG < nsym)
+                        index[2u * at + (i ? 1u : 0u)] = fine_note((r.start64 << 3) + r.q + r.stale - base);
+                    i += 8u;
+                    at += i == L ? 1u : 0u;
+                    i = i == L ? 0u : i;
+                }
+                ring_group<PAIR>(r, sm.tb, max_len);
+            }
+            ring2_topup(r);
+        }
+    }
+}
+
+// Wide pair tables: the first level's entry holds both symbols' values as bf16, the second one in the high half, and the codes'
+// length (at most 14) in the low four bits, which an integer of at most 16 in magnitude leaves zero.
+__global__ __launch_bounds__(1024) void k_fine_pairs(const DevTensor *__restrict__ tensors) {
+    __shared__ Tables tb;
+    __shared__ uint32_t wcnt[4 * (ENTRO_MAX_CODE_LEN + 1)];
+    const DevTensor &t = tensors[blockIdx.x];
+    build_tables<1024, true>(t, tb, wcnt);
+    Tables32 *dst = static_cast<Tables32 *>(t.tables);
+    static_assert(sizeof(TablesTail) % 16 == 0 && sizeof(TablesTail) / 16u <= 1024u, "copied in 16-byte steps");
+    if (threadIdx.x < sizeof(TablesTail) / 16u)
+        reinterpret_cast<u32x4 *>(dst)[threadIdx.x] = reinterpret_cast<const u32x4 *>(&tb)[threadIdx.x];
+    for (uint32_t i = threadIdx.x; i < (1u << kL1); i += 1024u) {
+        const uint32_t e = tb.lut[i], both = entry_sym(e);
+        const uint32_t lo = __float_as_uint(static_cast<float>(static_cast<int32_t>(both & 15u) - t.zero_point)) >> 16;
+        const uint32_t hi = __float_as_uint(static_cast<float>(static_cast<int32_t>(both >> 4) - t.zero_point)) & 0xffff0000u;
+        dst->lut[i] = entry_len(e) ? hi | lo | entry_len(e) : 0u;
+    }
+}
+
+// What a wavefront holds of a unit before it decodes it.
+struct FineUnit {
+    uint32_t places;        // where the lane's two chains begin, in bits from the unit's first: 16 bits each
+    uint32_t next;          // where the next lane's first chain begins (of the last lane: unused)
+    uint32_t q;             // where the lane's first chain begins in its column
+    uint32_t sub;           // an entry of the entry-point table (lanes 0..14)
+    uint64_t offset;        // of the segment
+    u32x4 data[kFineData / 4];
+};
+
+// Ask for what says where the unit's codes are ...
+__device__ __forceinline__ void fine_ask(const DevTensor &t, uint32_t unit, FineUnit &u) {
+    const uint32_t lane = threadIdx.x & 63u, fl = unit * 64u + lane;
+    u.places = ((global_u32_ptr)t.fine_index)[fl < t.fine_n ? fl : unit * 64u];
+    const uint32_t k = unit * t.fine_pieces, sh = t.sub_shift, c = k >> sh, before = k - (c << sh);
+    u.offset = ((global_u64_ptr)t.offsets)[c];
+    u.sub = 0;
+    if (sh) {
+        const uint32_t v = ((global_u16_ptr)t.sub)[(static_cast<uint64_t>(c) << sh) + (lane < before ? lane : 0u)];
+        u.sub = lane < before ? v : 0u;
+    }
+}
+
+// ... and for the codes themselves.
+__device__ __forceinline__ void fine_load(const DevTensor &t, FineUnit &u) {
+    uint32_t add = u.sub;                                // (the first row of sixteen lanes holds all entries)
+    add += __builtin_amdgcn_update_dpp(0u, add, 0x111, 0xf, 0xf, true);
+    add += __builtin_amdgcn_update_dpp(0u, add, 0x112, 0xf, 0xf, true);
+    add += __builtin_amdgcn_update_dpp(0u, add, 0x114, 0xf, 0xf, true);
+    add += __builtin_amdgcn_update_dpp(0u, add, 0x118, 0xf, 0xf, true);
+    const uint64_t base = u.offset + __builtin_amdgcn_readlane(add, 15);
+    const uint32_t a = u.places & 0xffffu;
+    u.next = __shfl_down(a, 1, 64);
+    const uint64_t pos = base + a;
+    u.q = (static_cast<uint32_t>(pos) & 31u) + 32u - Tables32::stale;
+    const uint32_t at = static_cast<uint32_t>(pos >> 5) << 2, last = t.stream_bytes - 16u;
+#pragma unroll
+    for (uint32_t i = 0; i < kFineData / 4u; ++i) {
+        // (a piece that begins behind the last sixteen bytes, which are padding, holds no code)
+        const uint32_t off = at + 16u * i;
+        u.data[i] = *(global_u4a4_ptr)(t.stream + (off < last ? off : last));
+    }
+}
+
+__device__ __forceinline__ uint64_t fine_window(lds_v32 col, uint32_t q) {
+    uint32_t d = q >> 5;
+    d = d < kFineData + 1u ? d : kFineData + 1u;
+    const lds_p32 src = (lds_p32)(col + d * 64u);
+    const uint32_t w0 = src[0], w1 = src[64], w2 = src[128];
+    const uint32_t lo = __builtin_amdgcn_alignbit(w1, w0, q);
+    const uint32_t hi = __builtin_amdgcn_alignbit(w2, w1, q);
+    return (static_cast<uint64_t>(hi) << 32) | lo;
+}
+
+// A group is four lookups of one chain: four symbols, or eight of 4 bits.
+template <bool PAIR>
+struct FineGroup {
+    static constexpr int kVals = PAIR ? 4 : 2;
+    static constexpr uint32_t kLenMask = PAIR ? 15u : 63u;
+    uint32_t v[kVals];                                   // the symbols' values as bf16, two per dword, first one lowest
+};
+
+__device__ __forceinline__ uint32_t bf16_of(uint32_t sym, float zf) { return __float_as_uint(static_cast<float>(sym) - zf) >> 16; }
+
+// The group of a lane that met a code (or pair of codes) that the first level does not hold: `w` is the window as it stopped in
+// front of it, `e` its miss entry.  The window still holds the 20 bits that the second level needs.
+template <bool PAIR>
+__device__ __forceinline__ uint32_t fine_careful(lds_v32 col, const Tables32 &tb, uint32_t max_len, float zf, uint32_t q, uint64_t w,
+                                                 uint32_t e0, uint32_t e1, uint32_t e2, uint32_t e, FineGroup<PAIR> &g) {
+    constexpr uint32_t M = FineGroup<PAIR>::kLenMask;
+    const uint32_t l0 = e0 & M, l1 = e1 & M, l2 = e2 & M;
+    uint32_t i = l0 == 0 ? 0u : l1 == 0 ? 1u : l2 == 0 ? 2u : 3u;
+    q += l0 + l1 + l2;                                   // (from the long code on the entries have no length)
+    for (;;) {
+        const bool miss = (e & M) == 0;
+        uint32_t val;
+        if constexpr (PAIR) {
+            val = e & ~M;
+            uint32_t len = e & M;
+            if (miss) {
+                const uint32_t s0 = fine_single<true>(tb, static_cast<uint32_t>(fine_window(col, q) >> Tables32::stale), max_len);
+                const uint32_t s1 = fine_single<true>(tb, static_cast<uint32_t>(fine_window(col, q + entry_len(s0)) >> Tables32::stale), max_len);
+                len = entry_len(s0) + entry_len(s1);
+                val = bf16_of(entry_sym(s0) & 15u, zf) | (bf16_of(entry_sym(s1) & 15u, zf) << 16);
+            }
+            q += len;
+            g.v[0] = i == 0 ? val : g.v[0];
+            g.v[1] = i == 1 ? val : g.v[1];
+            g.v[FineGroup<PAIR>::kVals - 2] = i == 2 ? val : g.v[FineGroup<PAIR>::kVals - 2];
+            g.v[FineGroup<PAIR>::kVals - 1] = i == 3 ? val : g.v[FineGroup<PAIR>::kVals - 1];
+            w >>= len & 15u;
+        } else {
+            if (miss) {
+                e = lookup_l2(tb, e, static_cast<uint32_t>(w >> Tables32::stale));
+                if (__builtin_expect(e == 0, 0)) e = fine_search(tb, static_cast<uint32_t>(fine_window(col, q) >> Tables32::stale), kL1 + 1, max_len);
+            }
+            q += entry_len(e);
+            val = bf16_of(entry_sym(e), zf);
+            const uint32_t keep = (i & 1u) ? 0x0000ffffu : 0xffff0000u, put = (i & 1u) ? val << 16 : val;
+            g.v[0] = i < 2u ? (g.v[0] & keep) | put : g.v[0];
+            g.v[1] = i >= 2u ? (g.v[1] & keep) | put : g.v[1];
+            w >>= entry_len(e);
+        }
+        if (++i == 4u) return q;
+        if (miss) w = fine_window(col, q);
+        e = lut_at(tb, static_cast<uint32_t>(w) & (kL1Mask << Tables32::stale));
+    }
+}
+
+// One group of either chain, without a branch per lookup, the chains' round trips side by side.
+template <bool PAIR>
+__device__ __forceinline__ void fine_groups(lds_v32 col, const Tables32 &tb, uint32_t max_len, float zf, uint32_t &qa, uint32_t &qb,
+                                            FineGroup<PAIR> &ga, FineGroup<PAIR> &gb) {
+    constexpr uint32_t kMask = kL1Mask << Tables32::stale, M = FineGroup<PAIR>::kLenMask;
+    uint64_t wa = fine_window(col, qa), wb = fine_window(col, qb);
+    uint32_t a[4], b[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        a[i] = lut_at(tb, static_cast<uint32_t>(wa) & kMask);
+        b[i] = lut_at(tb, static_cast<uint32_t>(wb) & kMask);
+        if (i < 3) {
+            wa >>= (a[i] & M);
+            wb >>= (b[i] & M);
+        }
+    }
+    uint32_t na, nb;
+    if constexpr (PAIR) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            ga.v[i] = a[i] & ~M;
+            gb.v[i] = b[i] & ~M;
+        }
+        na = qa + (a[0] & M) + (a[1] & M) + (a[2] & M) + (a[3] & M);
+        nb = qb + (b[0] & M) + (b[1] & M) + (b[2] & M) + (b[3] & M);
+    } else {
+        ga.v[0] = __builtin_amdgcn_perm(a[1], a[0], 0x07060302u);
+        ga.v[1] = __builtin_amdgcn_perm(a[3], a[2], 0x07060302u);
+        gb.v[0] = __builtin_amdgcn_perm(b[1], b[0], 0x07060302u);
+        gb.v[1] = __builtin_amdgcn_perm(b[3], b[2], 0x07060302u);
+        na = qa + ((a[0] + a[1] + a[2] + a[3]) & 0xffu);
+        nb = qb + ((b[0] + b[1] + b[2] + b[3]) & 0xffu);
+    }
+    const bool ma = (a[3] & M) == 0, mb = (b[3] & M) == 0;      // (a miss entry's length stays until the group's end)
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(ma || mb) != 0, 0)) {
+        // (one copy of the careful code for both chains)
+#pragma unroll 1
+        for (int c = 0; c < 2; ++c) {
+            if (c ? mb : ma) {
+                FineGroup<PAIR> g;
+#pragma unroll
+                for (int i = 0; i < FineGroup<PAIR>::kVals; ++i) g.v[i] = c ? gb.v[i] : ga.v[i];
+                const uint32_t q = fine_careful<PAIR>(col, tb, max_len, zf, c ? qb : qa, c ? wb : wa, c ? b[0] : a[0], c ? b[1] : a[1],
+                                                      c ? b[2] : a[2], c ? b[3] : a[3], g);
+#pragma unroll
+                for (int i = 0; i < FineGroup<PAIR>::kVals; ++i) {
+                    ga.v[i] = c ? ga.v[i] : g.v[i];
+                    gb.v[i] = c ? g.v[i] : gb.v[i];
+                }
+                na = c ? na : q;
+                nb = c ? q : nb;
+            }
+        }
+    }
+    qa = na;
+    qb = nb;
+}
+
+__device__ __forceinline__ float dot2(uint32_t v, uint32_t x, float acc) {
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, v), __builtin_bit_cast(bf16x2, x), acc, false);
+}
+
+// A unit whose noted places do not hold: its pieces are walked from the tensor's own tables, a lane each, the places are noted
+// anew, and every lane decodes its symbols from there one by one.
+template <bool PAIR>
+__device__ __forceinline__ float fine_slow(const DevTensor &t, const Tables32 &tb, uint32_t *mem, uint32_t unit, uint32_t x_col) {
+    const uint32_t lane = threadIdx.x & 63u, k0 = unit * t.fine_pieces, k = k0 + lane;
+    const uint64_t base = seg_start(t, k0);
+    volatile uint32_t *place = mem;                      // [lane][chain]
+    uint16_t *index = reinterpret_cast<uint16_t *>(t.fine_index);
+    const uint32_t last_off = t.stream_bytes - 8u, max_len = t.max_len;
+    wave_sync_lds();
+    if (lane < t.fine_pieces && k < t.n_chunks) {
+        const uint64_t left = t.n - static_cast<uint64_t>(k) * t.chunk_symbols;
+        const uint32_t nsym = left < t.chunk_symbols ? static_cast<uint32_t>(left) : t.chunk_symbols;
+        uint32_t at = lane * t.chunk_symbols / t.fine_len, i = lane * t.chunk_symbols - at * t.fine_len;
+        uint64_t pos = seg_start(t, k);
+#pragma unroll 1
+        for (uint32_t s = 0; s < nsym; ++s) {
+            if (i == 0 || i == t.fine_first) {
+                const uint32_t bits = static_cast<uint32_t>(pos - base);
+                place[2u * at + (i ? 1u : 0u)] = bits;
+                index[2u * (unit * 64u + at) + (i ? 1u : 0u)] = fine_note(bits);
+            }
+            pos += entry_len(fine_single<PAIR>(tb, static_cast<uint32_t>(load_bits(t.stream, pos, last_off)), max_len));
+            if (++i == t.fine_len) {
+                i = 0;
+                ++at;
+            }
+        }
+    }
+    wave_sync_lds();
+    float acc = 0.0f;
+    if (unit * 64u + lane < t.fine_n) {
+        uint64_t pos = base + place[2u * lane];
+#pragma unroll 1
+        for (uint32_t i = 0; i < t.fine_len; ++i) {
+            const uint32_t e = fine_single<PAIR>(tb, static_cast<uint32_t>(load_bits(t.stream, pos, last_off)), max_len);
+            pos += entry_len(e);
+            const uint32_t sym = entry_sym(e) & (PAIR ? 15u : 255u);
+            acc = fmaf(static_cast<float>(static_cast<int32_t>(sym) - t.zero_point), __uint_as_float(static_cast<uint32_t>(t.x[x_col + i]) << 16), acc);
+        }
+    }
+    wave_sync_lds();
+    return acc;
+}
+
+template <bool F32>
+__device__ __forceinline__ void fine_store(const DevTensor &t, uint32_t row, float sum) {
+    const float y = sum * t.scale;
+    if (F32) reinterpret_cast<float *>(t.out)[row] = y;
+    else reinterpret_cast<uint16_t *>(t.out)[row] = static_cast<uint16_t>(bf16_bits(y));
+}
+
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_of(float v) {
+    return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), CTRL, ROWS, 0xf, true));
+}
+
+// The lanes' sums become rows.
+template <bool F32>
+__device__ __forceinline__ void fine_sums(const DevTensor &t, uint32_t quantum, uint32_t unit, float sum) {
+    const uint32_t lane = threadIdx.x & 63u, fl = unit * 64u + lane, rl = t.row_lanes;
+    const bool valid = fl < t.fine_n;
+    float v = valid ? sum : 0.0f;
+    if (t.fine_rows == kFineParts) {
+        // lanes of a row side by side: running sums from the row's first lane in the unit, of which the last one counts
+        const uint32_t row = fl / rl, in_row = fl - row * rl;
+        const uint32_t run = in_row < lane ? in_row : lane;          // lanes of the row in front of this one in the unit
+#pragma unroll
+        for (uint32_t m = 1; m < 64u; m <<= 1) {
+            const float up = __shfl_up(v, m, 64);
+            v += run >= m ? up : 0.0f;
+        }
+        const bool row_ends = in_row + 1u == rl;
+        if (valid && (row_ends || lane == 63u)) {
+            if (row_ends && run == in_row) fine_store<F32>(t, row, v);
+            else t.partials[2 * static_cast<uint64_t>(unit) + (run == lane ? 0 : 1)] = v;     // (the unit's first row or another)
+        }
+        return;
+    }
+    // a power of two of lanes side by side: their last one ends up with the sum
+    const uint32_t across = t.fine_rows == kFineUnits ? 64u : rl;
+    if (across > 1u) v += dpp_of<0x111, 0xf>(v);         // row_shr:1, 2, 4, 8: from the lane that far in front, in rows of sixteen
+    if (across > 2u) v += dpp_of<0x112, 0xf>(v);
+    if (across > 4u) v += dpp_of<0x114, 0xf>(v);
+    if (across > 8u) v += dpp_of<0x118, 0xf>(v);
+    if (across > 16u) v += dpp_of<0x142, 0xa>(v);        // row_bcast:15: a row's last lane to the next row
+    if (across > 32u) v += dpp_of<0x143, 0xc>(v);        // row_bcast:31: lane 31 to the upper half
+    if (valid && (lane & (across - 1u)) == across - 1u)
+        fine_store<F32>(t, t.fine_rows == kFineUnits ? quantum : fl >> __builtin_ctz(rl), v);
+}
+
+// The column of the lane's first symbol.
+__device__ __forceinline__ uint32_t fine_column(const DevTensor &t, uint32_t unit, uint32_t of_row) {
+    const uint32_t lane = threadIdx.x & 63u, fl = unit * 64u + lane;
+    if (t.fine_rows == kFineUnits) return (of_row * 64u + lane) * t.fine_len;
+    if (t.fine_rows == kFineRow) return (lane & (t.row_lanes - 1u)) * t.fine_len;
+    return fl % t.row_lanes * t.fine_len;
+}
+
+// Where piece j of the activations lies: turned within its eight where lanes are an even number of pieces apart (turn 7; else 0),
+// so that eight lanes beside each other find theirs in different banks.
+__device__ __forceinline__ uint32_t fine_x_at(uint32_t j, uint32_t turn) { return (j & ~7u) | ((j + ((j >> 3) & turn)) & 7u); }
+__device__ __forceinline__ uint32_t fine_x_from(uint32_t j, uint32_t turn) { return (j & ~7u) | ((j - ((j >> 3) & turn)) & 7u); }
+
+template <bool PAIR, bool F32>
+__global__ __launch_bounds__(64 * kFineWaves) void k_fine(const DevTensor *__restrict__ tensors, const WorkItem *__restrict__ items,
+                                                          uint32_t item_quanta, uint32_t each, uint32_t rest) {
+    __shared__ FineMem sm;
+    constexpr uint32_t kTableVecs = sizeof(Tables32) / 16u, kTableSteps = (kTableVecs + 1023u) / 1024u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
+    const lds_v32 col = (lds_v32)(sm.col + wave * (kFineData * 64u) + lane);
+    // the items [b * n / G, (b + 1) * n / G), n = each * G + rest (a 64-bit division takes longer than the whole prologue)
+    const uint32_t lo = blockIdx.x * each + blockIdx.x * rest / gridDim.x;
+    const uint32_t hi = (blockIdx.x + 1u) * each + (blockIdx.x + 1u) * rest / gridDim.x;
+    for (uint32_t i = lo; i < hi;) {
+        const WorkItem it = items[i];
+        const DevTensor &t = tensors[it.tensor];
+        const uint32_t left = t.fine_quanta - it.first;
+        const uint64_t share = static_cast<uint64_t>(hi - i) * item_quanta;
+        const uint32_t n_quanta = left < share ? left : static_cast<uint32_t>(share);
+        // The first unit by the wavefront's number.  Its places, its codes and its activations are asked for with the tables.
+        uint32_t g = wave, of_row = 0;
+        const bool some = g < n_quanta;
+        uint32_t unit = (it.first + (some ? g : 0u)) * t.fine_units;
+        FineUnit u;
+        fine_ask(t, unit, u);
+        // Tables and activations (of rows that fit) go straight to LDS.  Through registers the tables' pieces took twenty of them, and
+        // some were spilled as they came; activations asked for by each lane where it needs them took 64 lines an instruction.
+        const uint32_t x_pieces = t.cols / 8u, turn = (t.fine_len / 8u) & 1u ? 0u : 7u;
+        const bool x_here = t.cols <= kFineX;
+        if (i != lo) __syncthreads();                    // nobody reads the previous tables or the counter any more
+#pragma unroll
+        for (uint32_t s = 0; s < kTableSteps; ++s) {
+            const uint32_t j = s * 1024u + threadIdx.x;
+            if (j < kTableVecs)
+                __builtin_amdgcn_global_load_lds((global_void_ptr)(static_cast<const u32x4 *>(t.tables) + j),
+                                                 (lds_void_ptr)(reinterpret_cast<u32x4 *>(&sm.tb) + s * 1024u + wave * 64u), 16, 0, 0);
+        }
+        if (x_here) {
+#pragma unroll
+            for (uint32_t s = 0; s < 2; ++s) {
+                const uint32_t j = s * 1024u + threadIdx.x, from = fine_x_from(j, turn);
+                if (s * 1024u < x_pieces && from < x_pieces)
+                    __builtin_amdgcn_global_load_lds((global_void_ptr)(reinterpret_cast<const u32x4 *>(t.x) + from),
+                                                     (lds_void_ptr)(sm.x + s * 1024u + wave * 64u), 16, 0, 0);
+            }
+        }
+        fine_load(t, u);
+        if (threadIdx.x == 0) sm.next = kFineWaves;
+        __builtin_amdgcn_s_waitcnt(0x0f70);              // vmcnt(0): what goes to LDS is there
+        __syncthreads();
+        const uint32_t max_len = t.max_len, steps = (t.fine_len + 15u) / 16u, pieces = t.fine_len / 8u;
+        const float zf = static_cast<float>(t.zero_point);
+        u32x4 x[8];
+        uint32_t x_col = 0xffffffffu;                    // the column that x holds
+        float sum = 0.0f;
+        bool more = some;
+        while (more) {
+#pragma unroll
+            for (uint32_t j = 0; j < kFineData; ++j) col[(1u + j) * 64u] = u.data[j / 4][j % 4];
+            const uint32_t here = unit * 64u + lane < t.fine_n ? fine_column(t, unit, of_row) : 0u;
+            if (__builtin_amdgcn_ballot_w64(here != x_col) != 0) {
+                // pieces of eight activations: the first `steps` of them are the first chain's, the others the second one's (zeros
+                // where that is a piece shorter: it decodes on into nothing)
+#pragma unroll
+                for (uint32_t p = 0; p < 8; ++p) {
+                    const uint32_t at = p < 4u ? p : steps + p - 4u;
+                    const uint32_t j = here / 8u + (at < pieces ? at : 0u);
+                    if (x_here) x[p] = sm.x[fine_x_at(j, turn)];
+                    else x[p] = *(global_u4_ptr)(reinterpret_cast<const char *>(t.x) + 16u * j);
+                }
+#pragma unroll
+                for (uint32_t p = 5; p < 8; ++p)
+                    if (steps + p - 4u == pieces) x[p] = u32x4{0u, 0u, 0u, 0u};
+                x_col = here;
+            }
+            // what comes next: the row's next unit, or one of another quantum
+            const bool row_done = of_row + 1u == t.fine_units;
+            uint32_t g_next = g;
+            if (row_done) {
+                if (lane == 0) g_next = atomicAdd(&sm.next, 1u);
+                g_next = __builtin_amdgcn_readfirstlane(g_next);
+                more = g_next < n_quanta;
+            }
+            const uint32_t unit_next = !row_done ? unit + 1u : more ? (it.first + g_next) * t.fine_units : unit;
+            const uint32_t a = u.places & 0xffffu, b = u.places >> 16, next = u.next;
+            const uint32_t q0 = u.q;
+            fine_ask(t, unit_next, u);
+            uint32_t qa = q0, qb = q0 + (b - a), end_b = qb;
+            float acc = 0.0f;
+#pragma unroll
+            for (uint32_t s = 0; s < 4; ++s) {
+                if (s < steps) {
+#pragma unroll
+                    for (int h = 0; h < (PAIR ? 1 : 2); ++h) {
+                        FineGroup<PAIR> ga, gb;
+                        fine_groups<PAIR>(col, sm.tb, max_len, zf, qa, qb, ga, gb);
+                        if constexpr (PAIR) {
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) {
+                                acc = dot2(ga.v[v], x[s][v], acc);
+                                acc = dot2(gb.v[v], x[4 + s][v], acc);
+                            }
+                        } else {
+#pragma unroll
+                            for (int v = 0; v < 2; ++v) {
+                                acc = dot2(ga.v[v], x[s][2 * h + v], acc);
+                                acc = dot2(gb.v[v], x[4 + s][2 * h + v], acc);
+                            }
+                        }
+                    }
+                    end_b = steps + s < pieces ? qb : end_b;
+                }
+                if (s == 0) fine_load(t, u);
+            }
+            // every chain ends where the next one begins, and the unit's first begins at its first bit
+            const uint32_t fl = unit * 64u + lane;
+            const bool last_lane = lane == 63u || fl + 1u >= t.fine_n;
+            const bool good = qa - q0 == b - a && (last_lane || end_b - q0 == next - a) && end_b <= kFineEnd - Tables32::stale &&
+                              (lane != 0 || a == 0);
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(fl < t.fine_n && !good) != 0, 0))
+                acc = fine_slow<PAIR>(t, sm.tb, sm.col + (wave * kFineData + 1u) * 64u, unit, here);
+            sum += acc;
+            if (row_done) {
+                fine_sums<F32>(t, it.first + g, unit, sum);
+                sum = 0.0f;
+            }
+            g = g_next;
+            of_row = row_done ? 0u : of_row + 1u;
+            unit = unit_next;
+        }
+        i += (n_quanta + item_quanta - 1u) / item_quanta;
+    }
+}
+
 // ------------------------------------------------------------------ host glue
 thread_local std::string g_last_error;
 
@@ -2907,16 +3454,65 @@ uint64_t align_up(uint64_t v, uint64_t a) { return (v + a - 1) / a * a; }
 // Symbols one lane decodes of this tensor (what the work list and the partial sums are counted in).
 uint32_t lane_symbols_of(const entro_tensor &t) { return t.sub_symbols ? t.sub_symbols : t.chunk_symbols; }
 
+// How k_fine cuts a tensor, by its shape alone (the workspace is laid out from it): lanes of `len` symbols (0: not at all), a
+// unit of 64 of them in whole pieces, every lane inside one row.  Shapes whose units hold whole rows, or whose rows are whole
+// units, need no second stage and come first; up to 64 symbols, the longest lane that gives one of those.
+struct FineShape {
+    uint32_t len, rows;
+};
+FineShape fine_shape(const entro_tensor &t) {
+    const uint32_t P = lane_symbols_of(t);
+    if (P == 0 || P % 64u != 0 || t.cols == 0 || t.cols > (1u << 30) || t.cols % 8u != 0 || static_cast<uint64_t>(t.rows) * t.cols != t.n) return {0, 0};
+    for (uint32_t len = 64; len >= 32; len -= 8) {
+        if (64u * len % P != 0 || t.cols % len != 0) continue;
+        const uint32_t row_lanes = t.cols / len;
+        if (row_lanes <= 64u && (row_lanes & (row_lanes - 1u)) == 0) return {len, kFineRow};
+        if (row_lanes % 64u == 0 && row_lanes <= 64u * 16u) return {len, kFineUnits};
+    }
+    for (uint32_t len = 64; len >= 32; len -= 16)
+        if (64u * len % P == 0 && t.cols % len == 0) return {len, kFineParts};
+    return {0, 0};
+}
+
+// Does this product go to k_fine?  Codes that do not fall into step (falls_into_step) stay with a lane per piece in every launch;
+// weights have none, and a lane per piece has to remain the yardstick that the library's times are taken against.  Its lanes have to hold the symbols' stream (three standard deviations of a lane's bits are
+// left free, and more), its tables the symbols' values: integers of at most 256 in magnitude, or 16 for 4-bit symbols.
+bool fine_fits(const entro_tensor &t, const DevTensor &dt) {
+    const FineShape f = fine_shape(t);
+    if (f.len == 0 || t.n / f.len >= (uint64_t{1} << 31) || !falls_into_step(t.cb)) return false;
+    if (dt.bits == 4 ? dt.zero_point < -1 || dt.zero_point > 16 : !wide_ok(dt)) return false;
+    return stream_bits(dt) * f.len + 31.0 + 80.0 <= 32.0 * kFineData;
+}
+
+// Describes a tensor (already described with a lane per piece) to k_fine.
+void fine_describe(const entro_tensor &t, uint32_t *index, DevTensor *dt) {
+    const FineShape f = fine_shape(t);
+    const uint32_t row_lanes = t.cols / f.len;
+    dt->fine_index = index;
+    dt->fine_len = f.len;
+    dt->fine_first = (f.len + 15u) / 16u * 8u;
+    dt->fine_n = static_cast<uint32_t>(t.n / f.len);
+    dt->fine_pieces = 64u * f.len / dt->chunk_symbols;
+    dt->fine_rows = f.rows;
+    dt->fine_units = f.rows == kFineUnits ? row_lanes / 64u : 1u;
+    dt->fine_quanta = f.rows == kFineUnits ? t.rows : (dt->fine_n + 63u) / 64u;
+    dt->row_lanes = row_lanes;
+    dt->fix_symbols = 64u * f.len;
+    dt->need_fix = f.rows == kFineParts && dt->fix_symbols % t.cols != 0 ? 1u : 0u;
+}
+
 struct Layout {
-    uint64_t off_tensors, off_items, off_fix, off_partials, off_tables, total;
+    uint64_t off_tensors, off_items, off_fix, off_partials, off_tables, off_index, total;
     uint32_t n_items, n_fix;
 };
 // room for one tensor's lookup tables in the workspace (the larger kind, whichever the launch uses)
 constexpr uint64_t kTablesStride = (sizeof(Tables32) + 255) / 256 * 256;
 
+constexpr uint64_t kFineItems = 16384;
+
 // Workspace layout shared by entro_workspace_bytes and entro_plan_init.
 bool plan_layout(const entro_tensor *ts, uint32_t count, entro_op op, Layout *L) {
-    uint64_t items = 0, fix = 0, partial_floats = 0;
+    uint64_t items = 0, fix = 0, partial_floats = 0, fine_items = 0, index_bytes = 0;
     for (uint32_t i = 0; i < count; ++i) {
         if (ts[i].chunk_symbols == 0 || ts[i].n == 0) return false;
         const uint64_t nc = entro_num_chunks(ts[i].n, lane_symbols_of(ts[i]));
@@ -2925,7 +3521,14 @@ bool plan_layout(const entro_tensor *ts, uint32_t count, entro_op op, Layout *L)
             fix += (static_cast<uint64_t>(ts[i].rows) + kFixRows - 1) / kFixRows;
             partial_floats += 2 * nc;
         }
+        if (op == ENTRO_OP_GEMV) {
+            const uint32_t len = fine_shape(ts[i]).len;
+            if (len) index_bytes += align_up(sizeof(uint32_t) * (ts[i].n / len), 256);
+            fine_items += ts[i].n / 4096u + 1u;
+        }
     }
+    // (k_fine's items are at least 4096 symbols, and larger ones where this many do not hold a launch)
+    items = std::max(items, std::min<uint64_t>(fine_items, kFineItems + count));
     if (items >= (uint64_t{1} << 31) || fix >= (uint64_t{1} << 31)) return false;
     L->n_items = static_cast<uint32_t>(items);
     L->n_fix = static_cast<uint32_t>(fix);
@@ -2934,7 +3537,8 @@ bool plan_layout(const entro_tensor *ts, uint32_t count, entro_op op, Layout *L)
     L->off_fix = L->off_items + align_up(sizeof(WorkItem) * items, 256);
     L->off_partials = L->off_fix + align_up(sizeof(WorkItem) * fix, 256);
     L->off_tables = L->off_partials + align_up(sizeof(float) * partial_floats, 256);
-    L->total = L->off_tables + kTablesStride * count;
+    L->off_index = L->off_tables + kTablesStride * count;
+    L->total = L->off_index + index_bytes;
     return true;
 }
 
@@ -2993,8 +3597,9 @@ uint64_t entro_workspace_bytes(const entro_tensor *ts, uint32_t count, entro_op 
 }
 
 // Validate, lay the table out in `host` (L.off_partials bytes) and fill in the plan; nothing touches the device.
+// `noting`: the launch may be one whose preparation walks the streams (k_fine).
 static entro_status build_plan(entro_plan *plan, const entro_tensor *ts, uint32_t count, entro_op op, entro_dtype out_type,
-                               void *workspace, uint64_t workspace_bytes, const Layout &L, unsigned char *host) {
+                               void *workspace, uint64_t workspace_bytes, const Layout &L, unsigned char *host, bool noting) {
     std::memset(host, 0, L.off_partials);
     DevTensor *dts = reinterpret_cast<DevTensor *>(host + L.off_tensors);
     WorkItem *items = reinterpret_cast<WorkItem *>(host + L.off_items);
@@ -3050,19 +3655,30 @@ static entro_status build_plan(entro_plan *plan, const entro_tensor *ts, uint32_
                                        });
         shared = share <= lane;
     }
-    const uint32_t level = shared ? 0u : choose_level(ts, count, lane_slots);
+    // Products go to k_fine instead where every tensor's form allows it, whether their pieces are few or not.
+    const bool few = shared;
+    bool fine = noting && op == ENTRO_OP_GEMV && (all4 || wide);
+    for (uint32_t i = 0; fine && i < count; ++i) fine = fine_fits(ts[i], dts[i]);
+    shared = shared && !fine;
+    uint64_t index_at = L.off_index, fine_quanta = 0;
+    const uint32_t level = shared || fine ? 0u : choose_level(ts, count, lane_slots);
     for (uint32_t i = 0; i < count; ++i) {
         entro_status st = fill_dev_tensor(&ts[i], op, out_type, level, &dts[i]);
         if (st != ENTRO_OK) return st;
         uint32_t bytes;
         if (shared) share_fits(op, &ts[i], &dts[i], &bytes);
+        if (fine) {
+            fine_describe(ts[i], reinterpret_cast<uint32_t *>(static_cast<unsigned char *>(workspace) + index_at), &dts[i]);
+            index_at += align_up(sizeof(uint32_t) * static_cast<uint64_t>(dts[i].fine_n), 256);
+            fine_quanta += dts[i].fine_quanta;
+        }
         dts[i].tables = static_cast<unsigned char *>(workspace) + L.off_tables + kTablesStride * i;
         total_units += (dts[i].n_chunks + kUnit - 1) / kUnit;
         pairs = pairs && dts[i].bits == 4;
         multirow = multirow || (op == ENTRO_OP_GEMV && dts[i].cols < dts[i].chunk_symbols);
         if (dts[i].need_fix) {
             dts[i].partials = partials_base + partial_floats;
-            partial_floats += 2 * static_cast<uint64_t>(shared ? dts[i].share_units : dts[i].n_chunks);
+            partial_floats += 2 * static_cast<uint64_t>(shared ? dts[i].share_units : fine ? dts[i].fine_quanta : dts[i].n_chunks);
             for (uint32_t r = 0; r < dts[i].rows; r += kFixRows) fix[n_fix++] = WorkItem{i, r};
         }
     }
@@ -3091,9 +3707,21 @@ static entro_status build_plan(entro_plan *plan, const entro_tensor *ts, uint32_
     // where every tensor has that second description a stretch may end anywhere at little cost: the
     // workgroups' shares are made equal to within one unit
     if (n_desc == 2 * count) item_units = 1;
+    if (fine) {
+        // about eight items for every workgroup, so that their shares are equal to within an eighth and less
+        uint32_t least = 1;
+        for (uint32_t i = 0; i < count; ++i) least = std::max(least, 4096u / (dts[i].fix_symbols * dts[i].fine_units));
+        uint64_t step = std::max<uint64_t>(least, fine_quanta / (8u * static_cast<uint64_t>(slots)));
+        for (;; step *= 2) {
+            uint64_t n = 0;
+            for (uint32_t i = 0; i < count; ++i) n += items_of(dts[i].fine_quanta, step);
+            if (n <= L.n_items) break;
+        }
+        item_units = static_cast<uint32_t>(step);
+    }
     for (uint32_t i = 0; i < count; ++i) {
-        const uint64_t end = shared ? dts[i].share_units : dts[i].n_chunks;
-        const uint64_t step = shared ? share_item_units(dts[i].share_per) : static_cast<uint64_t>(item_units) * kUnit;
+        const uint64_t end = shared ? dts[i].share_units : fine ? dts[i].fine_quanta : dts[i].n_chunks;
+        const uint64_t step = shared ? share_item_units(dts[i].share_per) : fine ? item_units : static_cast<uint64_t>(item_units) * kUnit;
         for (uint64_t c = 0; c < end; c += step) {
             if (n_items >= L.n_items) return ENTRO_ERR_SIZE;     // (the layout counts the same units: cannot happen)
             items[n_items++] = WorkItem{i, static_cast<uint32_t>(c)};
@@ -3108,9 +3736,9 @@ static entro_status build_plan(entro_plan *plan, const entro_tensor *ts, uint32_
     plan->n_fix = static_cast<uint32_t>(n_fix);
     plan->item_units = item_units;
     plan->pair_tables = pairs ? 1u : 0u;
-    plan->wide_tables = (op == ENTRO_OP_GEMV && !pairs && wide) ? 1u : 0u;
+    plan->wide_tables = fine ? 2u : (op == ENTRO_OP_GEMV && !pairs && wide) ? 1u : 0u;
     plan->gemv_multirow = multirow ? 1u : 0u;
-    plan->shared_wave_bytes = shared ? wave_bytes : 0u;
+    plan->shared_wave_bytes = shared ? wave_bytes : fine && few ? kFineData * 256u : 0u;
     plan->off_tensors = L.off_tensors;
     plan->off_items = L.off_items;
     plan->off_partials = L.off_partials;
@@ -3133,6 +3761,18 @@ static entro_status plan_checks(entro_plan *plan, const entro_tensor *ts, uint32
 // descriptor table on the same stream).
 static entro_status enqueue_tables(const entro_plan *plan, hipStream_t s) {
     const DevTensor *dts = reinterpret_cast<const DevTensor *>(static_cast<const unsigned char *>(plan->workspace) + plan->off_tensors);
+    if (plan->wide_tables == 2u) {
+        // (workgroups without a piece of their tensor end at once)
+        const dim3 index_grid(std::max(8u, 512u / plan->count), plan->count);
+        if (plan->pair_tables) {
+            hipLaunchKernelGGL(k_fine_pairs, dim3(plan->count), dim3(1024), 0, s, dts);
+            hipLaunchKernelGGL(k_fine_index<true>, index_grid, dim3(1024), 0, s, dts);
+        } else {
+            hipLaunchKernelGGL(k_tables<kModeGemvF32W>, dim3(plan->count), dim3(wg_of(kModeGemvF32W)), 0, s, dts);
+            hipLaunchKernelGGL(k_fine_index<false>, index_grid, dim3(1024), 0, s, dts);
+        }
+        return hip_ok(hipGetLastError(), "launch table kernels") ? ENTRO_OK : ENTRO_ERR_DEVICE;
+    }
     if (plan->shared_wave_bytes) {
         hipLaunchKernelGGL(k_share_tables, dim3(plan->count), dim3(64u * kShareWaves), 0, s, dts);
         return hip_ok(hipGetLastError(), "launch table kernel") ? ENTRO_OK : ENTRO_ERR_DEVICE;
@@ -3160,7 +3800,7 @@ entro_status entro_plan_init_staged(entro_plan *plan, const entro_tensor *ts, ui
     if (st != ENTRO_OK) return st;
     if (!staging) return ENTRO_ERR_NULL;
     if (staging_bytes < L.off_partials) return ENTRO_ERR_CAPACITY;
-    st = build_plan(plan, ts, count, op, out_type, workspace, workspace_bytes, L, static_cast<unsigned char *>(staging));
+    st = build_plan(plan, ts, count, op, out_type, workspace, workspace_bytes, L, static_cast<unsigned char *>(staging), true);
     if (st != ENTRO_OK) return st;
     if (!hip_ok(hipMemcpyAsync(workspace, staging, L.off_partials, hipMemcpyHostToDevice, static_cast<hipStream_t>(hip_stream)),
                 "copy plan table"))
@@ -3168,14 +3808,13 @@ entro_status entro_plan_init_staged(entro_plan *plan, const entro_tensor *ts, ui
     return enqueue_tables(plan, static_cast<hipStream_t>(hip_stream));
 }
 
-entro_status entro_plan_init(entro_plan *plan, const entro_tensor *ts, uint32_t count, entro_op op,
-                             entro_dtype out_type, void *workspace, uint64_t workspace_bytes,
-                             void *hip_stream) {
+static entro_status plan_init(entro_plan *plan, const entro_tensor *ts, uint32_t count, entro_op op, entro_dtype out_type,
+                              void *workspace, uint64_t workspace_bytes, bool noting, void *hip_stream) {
     Layout L;
     entro_status st = plan_checks(plan, ts, count, op, workspace, workspace_bytes, &L);
     if (st != ENTRO_OK) return st;
     std::vector<unsigned char> host(L.off_partials);
-    st = build_plan(plan, ts, count, op, out_type, workspace, workspace_bytes, L, host.data());
+    st = build_plan(plan, ts, count, op, out_type, workspace, workspace_bytes, L, host.data(), noting);
     if (st != ENTRO_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     if (!hip_ok(hipMemcpyAsync(workspace, host.data(), host.size(), hipMemcpyHostToDevice, s), "copy plan table"))
@@ -3183,6 +3822,12 @@ entro_status entro_plan_init(entro_plan *plan, const entro_tensor *ts, uint32_t 
     // the staging vector dies with this call, so wait for the copy
     if (!hip_ok(hipStreamSynchronize(s), "wait for plan table")) return ENTRO_ERR_DEVICE;
     return enqueue_tables(plan, s);
+}
+
+entro_status entro_plan_init(entro_plan *plan, const entro_tensor *ts, uint32_t count, entro_op op,
+                             entro_dtype out_type, void *workspace, uint64_t workspace_bytes,
+                             void *hip_stream) {
+    return plan_init(plan, ts, count, op, out_type, workspace, workspace_bytes, true, hip_stream);
 }
 
 entro_status entro_plan_run(const entro_plan *plan, void *hip_stream) {
@@ -3198,7 +3843,11 @@ entro_status entro_plan_run(const entro_plan *plan, void *hip_stream) {
     const unsigned slots = resident_workgroups(mode);
     if (slots == 0) return ENTRO_ERR_DEVICE;
     const unsigned grid = plan->n_items < slots ? plan->n_items : slots;
-    if (plan->shared_wave_bytes) {
+    if (plan->wide_tables == 2u) {
+        const bool f32 = gemv_f32(mode);
+        const auto kernel = plan->pair_tables ? (f32 ? k_fine<true, true> : k_fine<true, false>) : (f32 ? k_fine<false, true> : k_fine<false, false>);
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(64u * kFineWaves), 0, s, dts, items, plan->item_units, plan->n_items / grid, plan->n_items % grid);
+    } else if (plan->shared_wave_bytes) {
         const uint32_t waves = share_waves(plan->shared_wave_bytes);
         dispatch_mode(mode_of(static_cast<entro_op>(plan->op), static_cast<entro_dtype>(plan->out), false), [&](auto m) {
             constexpr int M = decltype(m)::value;
@@ -3222,7 +3871,8 @@ entro_status entro_plan_run(const entro_plan *plan, void *hip_stream) {
 static entro_status run_batch(const entro_tensor *ts, uint32_t count, entro_op op, entro_dtype d,
                               void *workspace, uint64_t workspace_bytes, void *hip_stream) {
     entro_plan plan;
-    entro_status st = entro_plan_init(&plan, ts, count, op, d, workspace, workspace_bytes, hip_stream);
+    // (run once: a walk through the streams beforehand would not pay)
+    entro_status st = plan_init(&plan, ts, count, op, d, workspace, workspace_bytes, false, hip_stream);
     if (st != ENTRO_OK) return st;
     return entro_plan_run(&plan, hip_stream);
 }

@@ -1217,3 +1217,86 @@ def test_few_units_per_workgroup_run_side_by_side(y_type):
         y_ref, _ = oracle.gemv(sym, rows, cols, 0.25, 7, synth.make_x_bf16(9, units, cols))
         _assert_gemv_close(y.float().cpu().numpy().astype(np.float64), y_ref, 1e-3 if y_type == E.ENTRO_F32 else 5e-3)
     assert us[1] <= 1.13 * us[0], us
+
+
+def _refill(dt, enc):
+    """Another tensor of the same codebook and sizes into dt's buffers."""
+    other = E.to_device(enc, DEV)
+    for name in ("stream", "offsets", "sub_bits"):
+        if getattr(dt, name, None) is not None:
+            getattr(dt, name).copy_(getattr(other, name))
+
+
+@pytest.mark.parametrize("y_type", [E.ENTRO_F32, E.ENTRO_BF16])
+@pytest.mark.parametrize("bits,chunk,sub,rows,cols,z", [
+    (8, 4096, 256, 67, 4096, 128),       # a row to a unit of 64 lanes
+    (8, 1024, 128, 333, 64, -1),         # a row to a lane, a last unit of 13 lanes, the lowest zero-point
+    (4, 2048, 128, 45, 1024, 16),        # four rows to a unit, the highest zero-point
+    (8, 4096, 256, 21, 14336, 256),      # four units of lanes of 56 symbols (chains of 32 and 24) to a row
+    (4, 8192, 512, 19, 3072, 7),         # lanes of 48 symbols across the ends of pieces
+    (8, 4096, 512, 9, 16384, 100),       # more activations than LDS holds
+    (8, 4096, 0, 13, 4160, 3),           # rows over units: partial sums; no entry points
+    (4, 1024, 64, 37, 192, 5),           # rows that begin inside units and end in them, too
+    (8, 1024, 256, 40, 1056, 90),        # lanes of 48 symbols, partial sums
+    (4, 2048, 512, 11, 2080, -1)])       # lanes of 32 symbols, partial sums, a last piece that is shorter
+def test_products_of_lanes_at_noted_places(bits, chunk, sub, rows, cols, z, y_type):
+    """Prepared products whose lanes begin where the preparation noted it: against the oracle, when the tensor's buffers have been
+    given other contents of the same codebook and sizes since, and when the places have been noted anew for those."""
+    top, n = (1 << bits) - 1, rows * cols
+    rng = np.random.default_rng(rows * cols + bits)
+    # (a heavy tail: codes longer than the first level's 14 bits, where the alphabet is large enough)
+    spread = rng.standard_t(2.2, n) * (2.5 if bits == 8 else 0.8)
+    first = np.clip(np.rint(spread) + (top + 1) // 2, 0, top).astype(np.uint8)
+    x = synth.make_x_bf16(3, cols, cols)
+    xd = torch.from_numpy(x.view(np.int16)).to(DEV).view(torch.bfloat16)
+    dt, plan = None, None
+    y = torch.zeros(rows, dtype=torch.float32 if y_type == E.ENTRO_F32 else torch.bfloat16, device=DEV)
+    for sym in (first, np.roll(first, 1), rng.permutation(first)):
+        enc = _oracle_encoded(sym, bits, chunk, rows, cols, 0.25, z, sub)
+        if plan is None:
+            dt = E.to_device(enc, DEV)
+            ts = [dt.ctensor(y, xd)]
+            ws = torch.zeros(E.entro_workspace_bytes(ts, E.ENTRO_OP_GEMV), dtype=torch.uint8, device=DEV)
+            plan = E.entro_plan_init(ts, E.ENTRO_OP_GEMV, y_type, ws)
+            assert plan.wide_tables == 2
+        else:
+            _refill(dt, enc)
+        terms = (sym.reshape(rows, cols).astype(np.float64) - z) * 0.25 * (x.astype(np.uint32) << 16).view(np.float32).astype(np.float64)
+        # fp32 sums of exact products: at most cols roundings of half an ulp, relative to the terms' magnitudes; bf16: half an ulp on top
+        bound = (cols + 2) * 2.0 ** -24 * np.abs(terms).sum(1) + (2.0 ** -8 * np.abs(terms.sum(1)) if y_type == E.ENTRO_BF16 else 0.0)
+        for _ in range(2):
+            y.fill_(7.0)
+            E.entro_plan_run(plan)
+            assert (np.abs(y.double().cpu().numpy() - terms.sum(1)) <= bound).all()
+
+
+def test_products_that_lanes_of_noted_places_do_not_take():
+    """Zero-points that the tables' values cannot hold, codes too long for a lane's stream, shapes that do not cut into lanes, mixed
+    alphabets and single runs go the ways they went."""
+    def wide(forms, batch=False):
+        encs, xs, syms = [], [], []
+        for bits, chunk, sub, rows, cols, z, spread in forms:
+            top = (1 << bits) - 1
+            sym = np.clip(np.rint(np.random.default_rng(cols).standard_normal(rows * cols) * spread) + (top + 1) // 2, 0, top).astype(np.uint8)
+            encs.append(_oracle_encoded(sym, bits, chunk, rows, cols, 0.5, z, sub))
+            xs.append(synth.make_x_bf16(4, cols, cols))
+            syms.append(sym)
+        xd = [torch.from_numpy(x.view(np.int16)).to(DEV).view(torch.bfloat16) for x in xs]
+        ys = [torch.zeros(e.rows, dtype=torch.float32, device=DEV) for e in encs]
+        dts = [E.to_device(e, DEV) for e in encs]
+        ts = [d.ctensor(y, x) for d, y, x in zip(dts, ys, xd)]
+        ws = torch.zeros(E.entro_workspace_bytes(ts, E.ENTRO_OP_GEMV), dtype=torch.uint8, device=DEV)
+        plan = E.entro_plan_init(ts, E.ENTRO_OP_GEMV, E.ENTRO_F32, ws)
+        E.entro_plan_run(plan)
+        for y, e, s, x, f in zip(ys, encs, syms, xs, forms):
+            _assert_gemv_close(y.cpu().numpy().astype(np.float64), oracle.gemv(s, e.rows, e.cols, 0.5, f[5], x)[0])
+        return plan.wide_tables == 2
+    base = (8, 4096, 256, 33, 4096, 128, 3.0)
+    four = (4, 4096, 256, 33, 4096, 7, 1.0)
+    assert wide([base, base]) and wide([four])
+    assert not wide([base, four])
+    assert not wide([base[:5] + (257, 3.0)]) and not wide([four[:5] + (17, 1.0)])
+    assert not wide([base[:6] + (60.0,)])                        # 7.9 bits a symbol
+    assert not wide([(8, 4096, 256, 33, 4100, 128, 3.0)])        # rows that are not whole pieces of eight activations
+    assert not wide([(8, 8192, 0, 33, 4096, 128, 3.0)])          # a unit's first bit is not in the tables
+    assert not wide([(8, 4000, 0, 33, 4096, 128, 3.0)])
