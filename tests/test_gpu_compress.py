@@ -160,6 +160,19 @@ def test_encode_codes_of_every_length_up_to_32():
     _assert_same_stream(sym, ln, 8, 777)
 
 
+@pytest.mark.parametrize("longest", [27, 28])
+@pytest.mark.parametrize("n,chunk", [(5 * 1024 + 3, 1024), (3 * 2048, 2048), (9001, 4100), (16385 * 64 + 5, 64), (40001, 4099)])
+def test_encode_rounds_of_eight_symbols_a_lane(longest, n, chunk):
+    # codes of up to 27 bits are written eight a lane, as strings of up to 216 bits; 28 bits, what is left of a segment and segments
+    # that begin inside a dword four a lane; one more segment than the scan's tile has entries
+    ln = np.zeros(256, np.uint8)
+    ln[:longest + 1] = list(range(1, longest)) + [longest, longest]
+    rng = np.random.default_rng(n)
+    sym = np.where(rng.random(n) < 0.9, rng.integers(longest - 6, longest + 1, n), rng.integers(0, 4, n)).astype(np.uint8)
+    sym[: n // 2] = np.minimum(rng.geometric(0.4, n // 2) - 1, longest)
+    _assert_same_stream(sym, ln, 8, chunk)
+
+
 def test_encode_reports_missing_code_and_small_capacity_and_writes_nothing():
     rng = np.random.default_rng(5)
     sym = rng.integers(0, 16, 100000).astype(np.uint8)
