@@ -311,10 +311,16 @@ __device__ __forceinline__ void build_tables(const DevTensor &t, TB &tb, uint32_
     // symbols of each length per wave, and every symbol's place among those of its length in its wave
     uint32_t rank = 0;
     if (tid < 256) {
-        for (uint32_t b = 1; b <= max_len; ++b) {
+        // one step for each length that occurs among the wavefront's symbols
+        if ((tid & 63u) < kLens) wcnt[wave * kLens + (tid & 63u)] = 0;
+        wave_sync_lds();
+        uint64_t open = __builtin_amdgcn_ballot_w64(l != 0);
+        while (open) {
+            const uint32_t b = __builtin_amdgcn_readlane(l, static_cast<uint32_t>(__builtin_ctzll(open)));
             const uint64_t m = __builtin_amdgcn_ballot_w64(l == b);
             if (l == b) rank = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u));
             if ((tid & 63u) == 0) wcnt[wave * kLens + b] = static_cast<uint32_t>(__builtin_popcountll(m));
+            open &= ~m;
         }
     }
     __syncthreads();
@@ -322,15 +328,28 @@ __device__ __forceinline__ void build_tables(const DevTensor &t, TB &tb, uint32_
         // lane b: the symbols of length b, those of the lengths below and the first code of length b
         const uint32_t b = tid;
         const uint32_t mine = b >= 1 && b <= max_len ? wcnt[b] + wcnt[kLens + b] + wcnt[2 * kLens + b] + wcnt[3 * kLens + b] : 0u;
-        uint32_t first = 0, off = 0, code = 0, below = 0;
-        for (uint32_t j = 1; j <= ENTRO_MAX_CODE_LEN + 1; ++j) {
-            const bool here = b == j;
-            first = here ? code : first;
-            off = here ? below : off;
-            const uint32_t c = __builtin_amdgcn_readlane(mine, j);
-            code = (code + c) << 1;
-            below += c;
-        }
+        // Code space taken by the shorter codes, in units of 2^-32 (Kraft's inequality keeps it within 33 bits): the first code of
+        // length b is its upper b bits.  Both sums over the lanes in front by DPP (lanes 0 to 33: rows of sixteen, then the row
+        // totals); one length after the other, with each length's count read from its lane, they took 1.3 us.
+        const uint32_t sh = b <= ENTRO_MAX_CODE_LEN ? ENTRO_MAX_CODE_LEN - b : 0u;
+        const uint64_t space = static_cast<uint64_t>(mine) << sh;
+        uint64_t upto = space;
+        uint32_t below = mine;
+        auto in_front = [&](auto ctrl, auto rows) __attribute__((always_inline)) {
+            constexpr int C = decltype(ctrl)::value, R = decltype(rows)::value;
+            const uint32_t lo = __builtin_amdgcn_update_dpp(0u, static_cast<uint32_t>(upto), C, R, 0xf, true);
+            const uint32_t hi = __builtin_amdgcn_update_dpp(0u, static_cast<uint32_t>(upto >> 32), C, R, 0xf, true);
+            below += __builtin_amdgcn_update_dpp(0u, below, C, R, 0xf, true);
+            upto += (static_cast<uint64_t>(hi) << 32) | lo;
+        };
+        typedef std::integral_constant<int, 0xf> AllRows;
+        in_front(std::integral_constant<int, 0x111>{}, AllRows{});                      // row_shr:1, 2, 4, 8
+        in_front(std::integral_constant<int, 0x112>{}, AllRows{});
+        in_front(std::integral_constant<int, 0x114>{}, AllRows{});
+        in_front(std::integral_constant<int, 0x118>{}, AllRows{});
+        in_front(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});   // row_bcast:15, :31
+        in_front(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{});
+        const uint32_t first = static_cast<uint32_t>((upto - space) >> sh) << (b == ENTRO_MAX_CODE_LEN + 1 ? 1u : 0u), off = below - mine;
         if (b <= ENTRO_MAX_CODE_LEN + 1) {
             tb.cnt[b] = mine;
             tb.first[b] = first;
@@ -2004,7 +2023,11 @@ __device__ __forceinline__ uint32_t share_at(uint32_t dword) { return dword + (d
 // longer codes: limit j is the first value, of 32 stream bits in code order, that no code of up to kMulti + 1 + j bits has.
 __device__ __forceinline__ void build_multi(ShareMem &sm) {
     const Tables &tb = sm.building();
-    for (uint32_t i = threadIdx.x; i < (1u << kMulti); i += 64u * kShareWaves) {
+    // (a lane's four entries side by side: a chain of lookups each)
+    static_assert((1u << kMulti) == 4u * 64u * kShareWaves, "four entries a lane");
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) {
+        const uint32_t i = k * 64u * kShareWaves + threadIdx.x;
         uint32_t w = i, bits = 0, n = 0, syms = 0, ends = 0xfff000u;
         bool more = true;
 #pragma unroll
