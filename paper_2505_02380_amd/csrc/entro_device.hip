@@ -102,6 +102,7 @@ struct DevTensor {
     uint32_t fine_rows;         // how rows come about: kFineRow, kFineUnits, kFineParts
     uint32_t fine_units;        // units that a wavefront takes one after the other: a row's, or one
     uint32_t fine_quanta;       // how many of those the tensor has
+    uint32_t fine_item;         // and how many of them are a work item
     uint8_t len[256];
 };
 
@@ -2911,7 +2912,7 @@ __device__ __forceinline__ uint32_t fine_x_from(uint32_t j, uint32_t turn) { ret
 
 template <bool PAIR, bool F32>
 __global__ __launch_bounds__(64 * kFineWaves) void k_fine(const DevTensor *__restrict__ tensors, const WorkItem *__restrict__ items,
-                                                          uint32_t item_quanta, uint32_t each, uint32_t rest) {
+                                                          uint32_t each, uint32_t rest) {
     __shared__ FineMem sm;
     constexpr uint32_t kTableVecs = sizeof(Tables32) / 16u, kTableSteps = (kTableVecs + 1023u) / 1024u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
@@ -2922,7 +2923,7 @@ __global__ __launch_bounds__(64 * kFineWaves) void k_fine(const DevTensor *__res
     for (uint32_t i = lo; i < hi;) {
         const WorkItem it = items[i];
         const DevTensor &t = tensors[it.tensor];
-        const uint32_t left = t.fine_quanta - it.first;
+        const uint32_t left = t.fine_quanta - it.first, item_quanta = t.fine_item;
         const uint64_t share = static_cast<uint64_t>(hi - i) * item_quanta;
         const uint32_t n_quanta = left < share ? left : static_cast<uint32_t>(share);
         // The first unit by the wavefront's number.  Its places, its codes and its activations are asked for with the tables.
@@ -3568,10 +3569,10 @@ bool plan_layout(const entro_tensor *ts, uint32_t count, entro_op op, Layout *L)
         if (op == ENTRO_OP_GEMV) {
             const uint32_t len = fine_shape(ts[i]).len;
             if (len) index_bytes += align_up(sizeof(uint32_t) * (ts[i].n / len), 256);
-            fine_items += ts[i].n / 4096u + 1u;
+            fine_items += ts[i].n / 2048u + 1u;              // (units have 2048 symbols at least)
         }
     }
-    // (k_fine's items are at least 4096 symbols, and larger ones where this many do not hold a launch)
+    // (k_fine's items are units or rows at least, and larger where this many do not hold a launch)
     items = std::max(items, std::min<uint64_t>(fine_items, kFineItems + count));
     if (items >= (uint64_t{1} << 31) || fix >= (uint64_t{1} << 31)) return false;
     L->n_items = static_cast<uint32_t>(items);
@@ -3752,20 +3753,49 @@ static entro_status build_plan(entro_plan *plan, const entro_tensor *ts, uint32_
     // workgroups' shares are made equal to within one unit
     if (n_desc == 2 * count) item_units = 1;
     if (fine) {
-        // about eight items for every workgroup, so that their shares are equal to within an eighth and less
-        uint32_t least = 1;
-        for (uint32_t i = 0; i < count; ++i) least = std::max(least, 4096u / (dts[i].fix_symbols * dts[i].fine_units));
-        uint64_t step = std::max<uint64_t>(least, fine_quanta / (8u * static_cast<uint64_t>(slots)));
-        for (;; step *= 2) {
-            uint64_t n = 0;
-            for (uint32_t i = 0; i < count; ++i) n += items_of(dts[i].fine_quanta, step);
-            if (n <= L.n_items) break;
+        // Where every tensor is worth eight workgroups or more, each gets workgroups of its own, an item each: a workgroup whose share
+        // goes from one tensor to the next loads tables twice and comes in last (6144 rows of 4096 in three tensors, 25 M symbols:
+        // 23 -> 21 us).  Otherwise about eight items of one size for every workgroup, so that shares are equal to within an eighth.
+        uint64_t all = 0, least = UINT64_MAX, used = 0;
+        for (uint32_t i = 0; i < count; ++i) {
+            all += dts[i].fine_n;
+            least = std::min<uint64_t>(least, dts[i].fine_n);
         }
-        item_units = static_cast<uint32_t>(step);
+        if (least * slots >= 8u * all) {
+            for (uint32_t i = 0; i < count; ++i) {
+                const uint64_t groups = dts[i].fine_n * static_cast<uint64_t>(slots) / all;
+                dts[i].fine_item = static_cast<uint32_t>(items_of(dts[i].fine_quanta, groups));
+                used += items_of(dts[i].fine_quanta, dts[i].fine_item);
+            }
+            // (shares are rounded down: what is left goes to the tensor whose workgroups have most to do)
+            for (bool more = true; more;) {
+                uint32_t top = 0;
+                for (uint32_t i = 1; i < count; ++i)
+                    if (static_cast<uint64_t>(dts[i].fine_item) * dts[i].fine_units > static_cast<uint64_t>(dts[top].fine_item) * dts[top].fine_units) top = i;
+                const uint32_t smaller = dts[top].fine_item - 1u;
+                const uint64_t now = items_of(dts[top].fine_quanta, dts[top].fine_item);
+                more = smaller != 0 && used - now + items_of(dts[top].fine_quanta, smaller) <= slots;
+                if (more) {
+                    used += items_of(dts[top].fine_quanta, smaller) - now;
+                    dts[top].fine_item = smaller;
+                }
+            }
+        } else {
+            uint32_t symbols = 1;
+            for (uint32_t i = 0; i < count; ++i) symbols = std::max(symbols, 4096u / (dts[i].fix_symbols * dts[i].fine_units));
+            uint64_t step = std::max<uint64_t>(symbols, fine_quanta / (8u * static_cast<uint64_t>(slots)));
+            for (;; step *= 2) {
+                uint64_t n = 0;
+                for (uint32_t i = 0; i < count; ++i) n += items_of(dts[i].fine_quanta, step);
+                if (n <= L.n_items) break;
+            }
+            for (uint32_t i = 0; i < count; ++i) dts[i].fine_item = static_cast<uint32_t>(step);
+        }
+        item_units = dts[0].fine_item;
     }
     for (uint32_t i = 0; i < count; ++i) {
         const uint64_t end = shared ? dts[i].share_units : fine ? dts[i].fine_quanta : dts[i].n_chunks;
-        const uint64_t step = shared ? share_item_units(dts[i].share_per) : fine ? item_units : static_cast<uint64_t>(item_units) * kUnit;
+        const uint64_t step = shared ? share_item_units(dts[i].share_per) : fine ? dts[i].fine_item : static_cast<uint64_t>(item_units) * kUnit;
         for (uint64_t c = 0; c < end; c += step) {
             if (n_items >= L.n_items) return ENTRO_ERR_SIZE;     // (the layout counts the same units: cannot happen)
             items[n_items++] = WorkItem{i, static_cast<uint32_t>(c)};
@@ -3926,7 +3956,7 @@ entro_status entro_plan_run(const entro_plan *plan, void *hip_stream) {
     if (plan->wide_tables == 2u) {
         const bool f32 = gemv_f32(mode);
         const auto kernel = plan->pair_tables ? (f32 ? k_fine<true, true> : k_fine<true, false>) : (f32 ? k_fine<false, true> : k_fine<false, false>);
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(64u * kFineWaves), 0, s, dts, items, plan->item_units, plan->n_items / grid, plan->n_items % grid);
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(64u * kFineWaves), 0, s, dts, items, plan->n_items / grid, plan->n_items % grid);
     } else if (plan->shared_wave_bytes) {
         const uint32_t waves = share_waves(plan->shared_wave_bytes);
         dispatch_mode(mode_of(static_cast<entro_op>(plan->op), static_cast<entro_dtype>(plan->out), false), [&](auto m) {
