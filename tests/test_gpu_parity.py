@@ -1300,3 +1300,26 @@ def test_products_that_lanes_of_noted_places_do_not_take():
     assert not wide([(8, 4096, 256, 33, 4100, 128, 3.0)])        # rows that are not whole pieces of eight activations
     assert not wide([(8, 8192, 0, 33, 4096, 128, 3.0)])          # a unit's first bit is not in the tables
     assert not wide([(8, 4000, 0, 33, 4096, 128, 3.0)])
+
+
+@pytest.mark.parametrize("out", [E.ENTRO_F32, E.ENTRO_BF16])
+@pytest.mark.parametrize("lengths", [[8] * 256, [7] * 60 + [8] * 76 + [9] * 120, [5, 2, 3, 3, 4, 5, 4, 5, 2, 5], [1, 1], [3] * 7 + [6] * 8,
+                                     [1, 2, 3, 4, 5, 5], [1]])
+def test_small_calls_under_codes_of_nearly_one_length(lengths, out):
+    # four neighbouring lengths at most, and two codes that have more or leave space unused; pieces and segments of whole blocks and
+    # not, a last one that is shorter, lanes of one wavefront and of two
+    cb = E.entro_codebook_from_lengths(np.pad(np.array(lengths, np.uint8), (0, 256 - min(256, len(lengths))))[:256], 8)
+    rng = np.random.default_rng(len(lengths))
+    for n, chunk, sub in ((1, 4096, 0), (2048, 4096, 256), (2049, 2048, 128), (33000, 4096, 256), (5000, 1000, 0)):
+        sym = rng.integers(0, min(256, len(lengths)), n).astype(np.uint8)
+        stream, off = E.entro_encode(sym, cb, chunk)
+        enc = B.EncodedTensor(stream, off, n, chunk, cb, B.QParams(np.float32(0.37), 11, 8, E.ENTRO_ASYMMETRIC), 1, n)
+        if sub:
+            enc.sub_symbols, enc.sub_bits = sub, E.entro_sub_index(sym, cb, chunk, sub)
+        y = torch.zeros(n + 8, dtype=torch.float32 if out == E.ENTRO_F32 else torch.bfloat16, device=DEV)
+        E.entro_decode_dequant(E.to_device(enc, DEV).ctensor(y), out)
+        if out == E.ENTRO_F32:
+            assert np.array_equal(y.cpu().numpy()[:n], oracle.dequant_f32(sym, 0.37, 11))
+        else:
+            assert np.array_equal(y.view(torch.int16).cpu().numpy().view(np.uint16)[:n], oracle.dequant_bf16(sym, 0.37, 11))
+        assert float(y[n:].abs().sum()) == 0.0
