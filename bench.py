@@ -440,8 +440,9 @@ def main():
         y_before = torch.cat([y for (x, y, idx, xb) in pairs]).clone()
         wlg, klg = timed(lambda: E.entro_plan_run(plan_lg), args.steps, args.warmup)
         y_after = torch.cat([y for (x, y, idx, xb) in pairs])
-        # same symbols, same x, same summation order: the products must not change at all
-        if not torch.equal(y_before, y_after):
+        # same symbols, same x; rows are cut into lanes by the entry points, which this set does not carry, so the order of the
+        # fp32 sums may differ
+        if bool(((y_after - y_before).abs() > 1e-5 * y_before.abs().clamp_min(float(y_before.square().mean().sqrt()))).any()):
             print("bench.py: GEMV over length-limited streams differs from the unrestricted run", file=sys.stderr)
             sys.exit(1)
         bits_l = sum(e.total_bits for e in encs_l) / n_sym

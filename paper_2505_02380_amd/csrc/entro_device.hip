@@ -3763,7 +3763,7 @@ static entro_status build_plan(entro_plan *plan, const entro_tensor *ts, uint32_
     bool fine = noting && op == ENTRO_OP_GEMV && (all4 || wide);
     for (uint32_t i = 0; fine && i < count; ++i) fine = fine_fits(ts[i], dts[i]);
     shared = shared && !fine;
-    uint64_t index_at = L.off_index, fine_quanta = 0;
+    uint64_t index_at = L.off_index;
     const uint32_t level = shared || fine ? 0u : choose_level(ts, count, lane_slots);
     for (uint32_t i = 0; i < count; ++i) {
         entro_status st = fill_dev_tensor(&ts[i], op, out_type, level, &dts[i]);
@@ -3773,7 +3773,6 @@ static entro_status build_plan(entro_plan *plan, const entro_tensor *ts, uint32_
         if (fine) {
             fine_describe(ts[i], reinterpret_cast<uint32_t *>(static_cast<unsigned char *>(workspace) + index_at), &dts[i]);
             index_at += align_up(sizeof(uint32_t) * static_cast<uint64_t>(dts[i].fine_n), 256);
-            fine_quanta += dts[i].fine_quanta;
         }
         dts[i].tables = static_cast<unsigned char *>(workspace) + L.off_tables + kTablesStride * i;
         total_units += (dts[i].n_chunks + kUnit - 1) / kUnit;
@@ -3813,7 +3812,8 @@ static entro_status build_plan(entro_plan *plan, const entro_tensor *ts, uint32_
     if (fine) {
         // Where every tensor is worth eight workgroups or more, each gets workgroups of its own, an item each: a workgroup whose share
         // goes from one tensor to the next loads tables twice and comes in last (6144 rows of 4096 in three tensors, 25 M symbols:
-        // 23 -> 21 us).  Otherwise about eight items of one size for every workgroup, so that shares are equal to within an eighth.
+        // 23 -> 21 us).  Otherwise about sixteen items of as many symbols for every workgroup (not of as many rows: 224 products
+        // of rows of 4096 and 14336 in one launch took 195 us a layer).
         uint64_t all = 0, least = UINT64_MAX, used = 0;
         for (uint32_t i = 0; i < count; ++i) {
             all += dts[i].fine_n;
@@ -3839,15 +3839,18 @@ static entro_status build_plan(entro_plan *plan, const entro_tensor *ts, uint32_
                 }
             }
         } else {
-            uint32_t symbols = 1;
-            for (uint32_t i = 0; i < count; ++i) symbols = std::max(symbols, 4096u / (dts[i].fix_symbols * dts[i].fine_units));
-            uint64_t step = std::max<uint64_t>(symbols, fine_quanta / (8u * static_cast<uint64_t>(slots)));
+            uint64_t symbols = 0;
+            for (uint32_t i = 0; i < count; ++i) symbols += ts[i].n;
+            uint64_t step = std::max<uint64_t>(4096, symbols / (16u * static_cast<uint64_t>(slots)));
             for (;; step *= 2) {
                 uint64_t n = 0;
-                for (uint32_t i = 0; i < count; ++i) n += items_of(dts[i].fine_quanta, step);
+                for (uint32_t i = 0; i < count; ++i) {
+                    const uint64_t quantum = static_cast<uint64_t>(dts[i].fix_symbols) * dts[i].fine_units;
+                    dts[i].fine_item = static_cast<uint32_t>(std::max<uint64_t>(1, step / quantum));
+                    n += items_of(dts[i].fine_quanta, dts[i].fine_item);
+                }
                 if (n <= L.n_items) break;
             }
-            for (uint32_t i = 0; i < count; ++i) dts[i].fine_item = static_cast<uint32_t>(step);
         }
         item_units = dts[0].fine_item;
     }
