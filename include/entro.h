@@ -310,8 +310,8 @@ entro_status entro_plan_run(const entro_plan *plan, void *hip_stream);
 
 /* Fig. 3's decode, the inverse of Eq. 1 and the product of "Latency Reduction from Huffman
  * Coding" over many tensors: entro_plan_init followed by entro_plan_run.  They return without waiting for
- * their kernel; calls whose table is larger than about 30 KB (some dozens of tensors, or hundreds of
- * thousands of segments) wait for the stream once before it is enqueued. */
+ * their kernel; calls whose table is larger than about 11 KB (a dozen tensors, or more in larger
+ * work lists) wait for the stream once before it is enqueued. */
 entro_status entro_decode_batch(const entro_tensor *ts, uint32_t count, entro_dtype out_type,
                                 void *workspace, uint64_t workspace_bytes, void *hip_stream);
 entro_status entro_decode_dequant_batch(const entro_tensor *ts, uint32_t count, entro_dtype out_type,

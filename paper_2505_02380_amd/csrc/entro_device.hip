@@ -3949,8 +3949,8 @@ entro_status entro_plan_init_staged(entro_plan *plan, const entro_tensor *ts, ui
 // The table of a launch that is prepared and run in one call travels as arguments of a few small kernels, and its work list is written
 // beside the lookup tables (k_tables) unless lanes share segments: a copy from pageable memory has to be waited for, with everything
 // in front of it on the stream.  Measured: seven tensors of 218 M symbols to bf16, two such kernels, 187 -> 169 us a call.  Larger
-// tables are copied.
-constexpr uint64_t kMostPuts = 8;
+// tables are copied: such a kernel takes 5 us, the copy and the wait about 25 (a call with more of them than three 65.5 -> 68.7).
+constexpr uint64_t kMostPuts = 3;
 
 static bool put_table(const entro_plan &plan, const unsigned char *host, hipStream_t s) {
     const DevTensor *dts = reinterpret_cast<const DevTensor *>(host + plan.off_tensors);
