@@ -2547,7 +2547,7 @@ __global__ __launch_bounds__(kFixWG) void k_fix_batch(const DevTensor *__restric
 //   Rows are cut into lanes so that a wavefront holds whole rows, or goes through a row unit by unit, where the shape allows it.
 // The noted places are a guess, as in k_shared: the unit's first bit is read from the tensor's own tables on every run, every
 // chain has to end where the next one begins, and so by induction all of them are true, whatever the streams hold by now.  A
-// unit that fails is decoded piece by piece from the tensor's tables (fine_slow), which also notes its places anew.
+// unit that fails is walked piece by piece from the tensor's tables (fine_walk), which also notes its places anew, and decoded from there.
 //   Measured, a lane per piece -> now, us a launch.  8 bits, 3.5 bits a symbol: 25 M symbols in rows of 4096 36 -> 22, 16.8 M 31 -> 16,
 // 117 M 74 -> 46, 58.7 M in rows of 14336 44 and 5 for the second stage -> 34; the step over 32 layers 6098 -> 3881.  4 bits, 1.55
 // bits a symbol: 9.4 M symbols in rows of 3072, shared by k_shared_batch before, 28 -> 10; the step over 32 layers 4035 -> 1863.
@@ -2840,13 +2840,12 @@ __device__ __forceinline__ float dot2(uint32_t v, uint32_t x, float acc) {
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, v), __builtin_bit_cast(bf16x2, x), acc, false);
 }
 
-// A unit whose noted places do not hold: its pieces are walked from the tensor's own tables, a lane each, the places are noted
-// anew, and every lane decodes its symbols from there one by one.
+// A unit whose noted places do not hold: its pieces are walked from the tensor's own tables, a lane each, and the places are noted
+// anew.  Where the lane's two chains begin, in bits from the unit's first, is returned in a and b (place: room for both of every lane).
 template <bool PAIR>
-__device__ __forceinline__ float fine_slow(const DevTensor &t, const Tables32 &tb, uint32_t *mem, uint32_t unit, uint32_t x_col) {
-    const uint32_t lane = threadIdx.x & 63u, k0 = unit * t.fine_pieces, k = k0 + lane;
-    const uint64_t base = seg_start(t, k0);
-    volatile uint32_t *place = mem;                      // [lane][chain]
+__device__ __forceinline__ void fine_walk(const DevTensor &t, const Tables32 &tb, lds_v32 place, uint32_t unit, uint64_t base, uint32_t &a,
+                                          uint32_t &b) {
+    const uint32_t lane = threadIdx.x & 63u, k = unit * t.fine_pieces + lane;
     uint16_t *index = reinterpret_cast<uint16_t *>(t.fine_index);
     const uint32_t last_off = t.stream_bytes - 8u, max_len = t.max_len;
     wave_sync_lds();
@@ -2870,18 +2869,55 @@ __device__ __forceinline__ float fine_slow(const DevTensor &t, const Tables32 &t
         }
     }
     wave_sync_lds();
+    a = place[2u * lane];
+    b = place[2u * lane + 1u];
+    wave_sync_lds();
+}
+
+// `N` pieces of sixteen bytes of the stream, from absolute bit `pos` on, into the dwords that `col` is the first of.  Returns the
+// position of that bit, as if they were dwords 1 and up of the lane's column.
+template <uint32_t N>
+__device__ __forceinline__ uint32_t fine_fill(const DevTensor &t, lds_v32 col, uint64_t pos) {
+    const uint32_t at = static_cast<uint32_t>(pos >> 5) << 2, last = t.stream_bytes - 16u;
+    u32x4 v[N];
+#pragma unroll
+    for (uint32_t i = 0; i < N; ++i) {
+        const uint32_t off = at + 16u * i;
+        v[i] = *(global_u4a4_ptr)(t.stream + (off < last ? off : last));
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < 4u * N; ++j) col[j * 64u] = v[j / 4][j % 4];
+    return (static_cast<uint32_t>(pos) & 31u) + 32u - Tables32::stale;
+}
+
+// The sum of a lane whose chains begin a and b bits behind the unit's first, whatever their length: half of its column for the
+// next group of either chain, filled before each.  Groups, values and sums come in the order that k_fine's own loop has them in,
+// so that a unit's sums are the same to the last bit, however its places have been found.
+template <bool PAIR, class X>
+__device__ __forceinline__ float fine_again(const DevTensor &t, const Tables32 &tb, lds_v32 col, uint32_t max_len, float zf, uint64_t base,
+                                            uint32_t a, uint32_t b, X activations) {
+    const uint32_t pieces = t.fine_len / 8u, steps = (pieces + 1u) / 2u;
     float acc = 0.0f;
-    if (unit * 64u + lane < t.fine_n) {
-        uint64_t pos = base + place[2u * lane];
 #pragma unroll 1
-        for (uint32_t i = 0; i < t.fine_len; ++i) {
-            const uint32_t e = fine_single<PAIR>(tb, static_cast<uint32_t>(load_bits(t.stream, pos, last_off)), max_len);
-            pos += entry_len(e);
-            const uint32_t sym = entry_sym(e) & (PAIR ? 15u : 255u);
-            acc = fmaf(static_cast<float>(static_cast<int32_t>(sym) - t.zero_point), __uint_as_float(static_cast<uint32_t>(t.x[x_col + i]) << 16), acc);
+    for (uint32_t s = 0; s < steps; ++s) {
+        const u32x4 xa = activations(s);
+        u32x4 xb = activations(steps + s < pieces ? steps + s : 0u);
+        if (steps + s >= pieces) xb = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int h = 0; h < (PAIR ? 1 : 2); ++h) {
+            const uint32_t from_a = fine_fill<2>(t, col + 64u, base + a), from_b = fine_fill<2>(t, col + 9u * 64u, base + b) + 8u * 32u;
+            uint32_t qa = from_a, qb = from_b;
+            FineGroup<PAIR> ga, gb;
+            fine_groups<PAIR>(col, tb, max_len, zf, qa, qb, ga, gb);
+            a += qa - from_a;
+            b += qb - from_b;
+#pragma unroll
+            for (int v = 0; v < FineGroup<PAIR>::kVals; ++v) {
+                acc = dot2(ga.v[v], xa[(PAIR ? 0 : 2 * h) + v], acc);
+                acc = dot2(gb.v[v], xb[(PAIR ? 0 : 2 * h) + v], acc);
+            }
         }
     }
-    wave_sync_lds();
     return acc;
 }
 
@@ -2993,6 +3029,9 @@ __global__ __launch_bounds__(64 * kFineWaves) void k_fine(const DevTensor *__res
         __syncthreads();
         const uint32_t max_len = t.max_len, steps = (t.fine_len + 15u) / 16u, pieces = t.fine_len / 8u;
         const float zf = static_cast<float>(t.zero_point);
+        auto activations = [&](uint32_t j) __attribute__((always_inline)) {          // piece j of them
+            return x_here ? sm.x[fine_x_at(j, turn)] : *(global_u4_ptr)(reinterpret_cast<const char *>(t.x) + 16u * j);
+        };
         u32x4 x[8];
         uint32_t x_col = 0xffffffffu;                    // the column that x holds
         float sum = 0.0f;
@@ -3007,9 +3046,7 @@ __global__ __launch_bounds__(64 * kFineWaves) void k_fine(const DevTensor *__res
 #pragma unroll
                 for (uint32_t p = 0; p < 8; ++p) {
                     const uint32_t at = p < 4u ? p : steps + p - 4u;
-                    const uint32_t j = here / 8u + (at < pieces ? at : 0u);
-                    if (x_here) x[p] = sm.x[fine_x_at(j, turn)];
-                    else x[p] = *(global_u4_ptr)(reinterpret_cast<const char *>(t.x) + 16u * j);
+                    x[p] = activations(here / 8u + (at < pieces ? at : 0u));
                 }
 #pragma unroll
                 for (uint32_t p = 5; p < 8; ++p)
@@ -3060,8 +3097,19 @@ __global__ __launch_bounds__(64 * kFineWaves) void k_fine(const DevTensor *__res
             const bool last_lane = lane == 63u || fl + 1u >= t.fine_n;
             const bool good = qa - q0 == b - a && (last_lane || end_b - q0 == next - a) && end_b <= kFineEnd - Tables32::stale &&
                               (lane != 0 || a == 0);
-            if (__builtin_expect(__builtin_amdgcn_ballot_w64(fl < t.fine_n && !good) != 0, 0))
-                acc = fine_slow<PAIR>(t, sm.tb, sm.col + (wave * kFineData + 1u) * 64u, unit, here);
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(fl < t.fine_n && !good) != 0, 0)) {
+                const uint64_t base = seg_start(t, unit * t.fine_pieces);
+                uint32_t from_a, from_b;
+                fine_walk<PAIR>(t, sm.tb, (lds_v32)(sm.col + (wave * kFineData + 1u) * 64u), unit, base, from_a, from_b);
+                acc = fine_again<PAIR>(t, sm.tb, col, max_len, zf, base, from_a, from_b,
+                                       [&](uint32_t j) __attribute__((always_inline)) { return activations(here / 8u + j); });
+                // (what a wavefront holds for its next unit is asked for again: kept over all this, some of it is spilled)
+#pragma unroll
+                for (uint32_t p = 0; p < 8; ++p) x[p] = u32x4{0u, 0u, 0u, 0u};
+                x_col = 0xffffffffu;
+                fine_ask(t, unit_next, u);
+                fine_load(t, u);
+            }
             sum += acc;
             if (row_done) {
                 fine_sums<F32>(t, it.first + g, unit, sum);
@@ -3584,6 +3632,7 @@ bool fine_fits(const entro_tensor &t, const DevTensor &dt) {
     const FineShape f = fine_shape(t);
     if (f.len == 0 || t.n / f.len >= (uint64_t{1} << 31) || !falls_into_step(t.cb)) return false;
     if (dt.bits == 4 ? dt.zero_point < -1 || dt.zero_point > 16 : !wide_ok(dt)) return false;
+    if (dt.bits == 4 && dt.max_len > 28u) return false;      // (fine_again: eight codes and a dword's end in half a column)
     return stream_bits(dt) * f.len + 31.0 + 80.0 <= 32.0 * kFineData;
 }
 

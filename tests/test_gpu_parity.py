@@ -1227,8 +1227,8 @@ def _refill(dt, enc):
             getattr(dt, name).copy_(getattr(other, name))
 
 
-@pytest.mark.parametrize("y_type", [E.ENTRO_F32, E.ENTRO_BF16])
-@pytest.mark.parametrize("bits,chunk,sub,rows,cols,z", [
+# forms that k_fine takes
+NOTED_FORMS = [
     (8, 4096, 256, 67, 4096, 128),       # a row to a unit of 64 lanes
     (8, 1024, 128, 333, 64, -1),         # a row to a lane, a last unit of 13 lanes, the lowest zero-point
     (4, 2048, 128, 45, 1024, 16),        # four rows to a unit, the highest zero-point
@@ -1238,7 +1238,12 @@ def _refill(dt, enc):
     (8, 4096, 0, 13, 4160, 3),           # rows over units: partial sums; no entry points
     (4, 1024, 64, 37, 192, 5),           # rows that begin inside units and end in them, too
     (8, 1024, 256, 40, 1056, 90),        # lanes of 48 symbols, partial sums
-    (4, 2048, 512, 11, 2080, -1)])       # lanes of 32 symbols, partial sums, a last piece that is shorter
+    (4, 2048, 512, 11, 2080, -1),        # lanes of 32 symbols, partial sums, a last piece that is shorter
+]
+
+
+@pytest.mark.parametrize("y_type", [E.ENTRO_F32, E.ENTRO_BF16])
+@pytest.mark.parametrize("bits,chunk,sub,rows,cols,z", NOTED_FORMS)
 def test_products_of_lanes_at_noted_places(bits, chunk, sub, rows, cols, z, y_type):
     """Prepared products whose lanes begin where the preparation noted it: against the oracle, when the tensor's buffers have been
     given other contents of the same codebook and sizes since, and when the places have been noted anew for those."""
@@ -1268,6 +1273,37 @@ def test_products_of_lanes_at_noted_places(bits, chunk, sub, rows, cols, z, y_ty
             y.fill_(7.0)
             E.entro_plan_run(plan)
             assert (np.abs(y.double().cpu().numpy() - terms.sum(1)) <= bound).all()
+
+
+@pytest.mark.parametrize("bits,chunk,sub,rows,cols,z", NOTED_FORMS)
+def test_products_do_not_depend_on_how_their_places_were_found(bits, chunk, sub, rows, cols, z):
+    """The sums of a prepared product are taken in an order that depends on the launch, never on the run: when its buffers have been
+    given other contents, the first run, which finds the places, the next one, which finds them noted, and a plan prepared for
+    these contents agree to the last bit."""
+    top, n = (1 << bits) - 1, rows * cols
+    rng = np.random.default_rng(rows * cols + bits + 1)
+    first = np.clip(np.rint(rng.standard_t(2.2, n) * (2.5 if bits == 8 else 0.8)) + (top + 1) // 2, 0, top).astype(np.uint8)
+    x = torch.from_numpy(rng.standard_normal(cols).astype(np.float32)).to(DEV).to(torch.bfloat16)
+    y = torch.zeros(rows, dtype=torch.float32, device=DEV)
+
+    def plan_of(dt):
+        ts = [dt.ctensor(y, x)]
+        ws = torch.zeros(E.entro_workspace_bytes(ts, E.ENTRO_OP_GEMV), dtype=torch.uint8, device=DEV)
+        plan = E.entro_plan_init(ts, E.ENTRO_OP_GEMV, E.ENTRO_F32, ws)
+        assert plan.wide_tables == 2
+        return plan, ws, dt
+
+    def bits_of(plan):
+        y.fill_(7.0)
+        E.entro_plan_run(plan[0])
+        return y.view(torch.int32).clone()
+    dt = E.to_device(_oracle_encoded(first, bits, chunk, rows, cols, 0.25, z, sub), DEV)
+    plan = plan_of(dt)
+    for sym in (np.roll(first, 1), rng.permutation(first)):
+        enc = _oracle_encoded(sym, bits, chunk, rows, cols, 0.25, z, sub)
+        _refill(dt, enc)
+        found, noted, fresh = bits_of(plan), bits_of(plan), bits_of(plan_of(E.to_device(enc, DEV)))
+        assert torch.equal(found, noted) and torch.equal(noted, fresh)
 
 
 def test_products_that_lanes_of_noted_places_do_not_take():
