@@ -267,7 +267,10 @@ entro_status entro_decode_gemv_static(const entro_tensor *t, entro_dtype y_type,
 /* Batched forms: ONE launch over `count` tensors (a single tensor has too few of
  * Fig. 3's segments to fill 256 compute units).  The descriptor table, the work list,
  * the tensors' lookup tables (about 68 KB per tensor), the GEMV partial sums and the places
- * that a GEMV's preparation notes (4 bytes per 64 symbols) live in `workspace` (device). */
+ * that a GEMV's preparation notes (4 bytes per 32 to 64 symbols, where it notes any) live in `workspace` (device).
+ * A GEMV whose workspace, or staging memory, has no room for the places runs without them (all it has to
+ * have is what the same tensors take with a zero-point of 1000, say, for which no places are noted); so
+ * do the batch calls below, whatever the room. */
 uint64_t entro_workspace_bytes(const entro_tensor *ts, uint32_t count, entro_op op);
 
 /* Prepare a batched launch of Fig. 3's segment-parallel decode (or of the fused forms above):

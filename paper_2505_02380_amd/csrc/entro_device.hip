@@ -3285,10 +3285,10 @@ unsigned spb_of(int mode) {
     return spb;
 }
 
-// `pairs`: every tensor of the launch holds 4-bit symbols, so the tables can hold two codes per entry.
 // Does the GEMV of this tensor fit the wide tables?
 bool wide_ok(const DevTensor &dt) { return dt.bits == 8 && dt.zero_point >= -1 && dt.zero_point <= 256; }
 
+// `pairs`: every tensor of the launch holds 4-bit symbols, so the tables can hold two codes per entry.
 // `wide`: a GEMV all of whose tensors hold 8-bit symbols with a zero-point in [-1, 256] (symbol - zero_point is a
 // bf16 then, which the wide tables hold ready for use).
 int mode_of(entro_op op, entro_dtype d, bool pairs, bool wide = false) {
@@ -3384,7 +3384,10 @@ bool cut_segments(entro_op op, int mode, uint64_t lane_slots, const entro_tensor
 }
 
 // Stream bits of a symbol on average (as far as the rules below use them: at most the symbol's own).
-double stream_bits(const DevTensor &dt) { return std::min(static_cast<double>(dt.bits), 8.0 * dt.stream_bytes / static_cast<double>(dt.n)); }
+double stream_bits(uint32_t bits, uint64_t stream_bytes, uint64_t n) {
+    return std::min(static_cast<double>(bits), 8.0 * static_cast<double>(stream_bytes) / static_cast<double>(n));
+}
+double stream_bits(const DevTensor &dt) { return stream_bits(dt.bits, dt.stream_bytes, dt.n); }
 
 // A tensor in few segments, or few pieces between entry points: 4 to 64 lanes share one (k_shared), at about 64 symbols a
 // lane.  A wavefront's share of LDS is what its unit's symbols take, and its part of the stream at the tensor's mean rate and
@@ -3628,12 +3631,22 @@ FineShape fine_shape(const entro_tensor &t) {
 // Does this product go to k_fine?  Codes that do not fall into step (falls_into_step) stay with a lane per piece in every launch;
 // weights have none, and a lane per piece has to remain the yardstick that the library's times are taken against.  Its lanes have to hold the symbols' stream (three standard deviations of a lane's bits are
 // left free, and more), its tables the symbols' values: integers of at most 256 in magnitude, or 16 for 4-bit symbols.
-bool fine_fits(const entro_tensor &t, const DevTensor &dt) {
+// (Asked before the tensor has been looked at, by the calls that only say how much room a launch takes.)
+bool fine_fits(const entro_tensor &t) {
     const FineShape f = fine_shape(t);
-    if (f.len == 0 || t.n / f.len >= (uint64_t{1} << 31) || !falls_into_step(t.cb)) return false;
-    if (dt.bits == 4 ? dt.zero_point < -1 || dt.zero_point > 16 : !wide_ok(dt)) return false;
-    if (dt.bits == 4 && dt.max_len > 28u) return false;      // (fine_again: eight codes and a dword's end in half a column)
-    return stream_bits(dt) * f.len + 31.0 + 80.0 <= 32.0 * kFineData;
+    if (f.len == 0 || t.n / f.len >= (uint64_t{1} << 31) || check_codebook(t.cb) != ENTRO_OK || !falls_into_step(t.cb)) return false;
+    const bool four = t.cb->bits == 4;
+    if (t.qp.zero_point < -1 || t.qp.zero_point > (four ? 16 : 256)) return false;
+    if (four && t.cb->max_len > 28) return false;            // (fine_again: eight codes and a dword's end in half a column)
+    return stream_bits(static_cast<uint32_t>(t.cb->bits), t.stream_bytes, t.n) * f.len + 31.0 + 80.0 <= 32.0 * kFineData;
+}
+
+// Does a prepared launch go there: every tensor's form allows it, and all have the same alphabet?
+bool fine_launch(const entro_tensor *ts, uint32_t count, entro_op op) {
+    if (op != ENTRO_OP_GEMV) return false;
+    for (uint32_t i = 0; i < count; ++i)
+        if (!fine_fits(ts[i]) || ts[i].cb->bits != ts[0].cb->bits) return false;
+    return true;
 }
 
 // Describes a tensor (already described with a lane per piece) to k_fine.
@@ -3662,8 +3675,8 @@ constexpr uint64_t kTablesStride = (sizeof(Tables32) + 255) / 256 * 256;
 
 constexpr uint64_t kFineItems = 16384;
 
-// Workspace layout shared by entro_workspace_bytes and entro_plan_init.
-bool plan_layout(const entro_tensor *ts, uint32_t count, entro_op op, Layout *L) {
+// Workspace layout shared by entro_workspace_bytes and entro_plan_init.  `fine`: of a launch that goes to k_fine (fine_launch).
+bool plan_layout(const entro_tensor *ts, uint32_t count, entro_op op, bool fine, Layout *L) {
     uint64_t items = 0, fix = 0, partial_floats = 0, fine_items = 0, index_bytes = 0;
     for (uint32_t i = 0; i < count; ++i) {
         if (ts[i].chunk_symbols == 0 || ts[i].n == 0) return false;
@@ -3673,9 +3686,8 @@ bool plan_layout(const entro_tensor *ts, uint32_t count, entro_op op, Layout *L)
             fix += (static_cast<uint64_t>(ts[i].rows) + kFixRows - 1) / kFixRows;
             partial_floats += 2 * nc;
         }
-        if (op == ENTRO_OP_GEMV) {
-            const uint32_t len = fine_shape(ts[i]).len;
-            if (len) index_bytes += align_up(sizeof(uint32_t) * (ts[i].n / len), 256);
+        if (fine) {
+            index_bytes += align_up(sizeof(uint32_t) * (ts[i].n / fine_shape(ts[i]).len), 256);
             fine_items += ts[i].n / 2048u + 1u;              // (units have 2048 symbols at least)
         }
     }
@@ -3744,14 +3756,14 @@ entro_status entro_decode_gemv_static(const entro_tensor *t, entro_dtype y_type,
 
 uint64_t entro_workspace_bytes(const entro_tensor *ts, uint32_t count, entro_op op) {
     Layout L;
-    if (!ts || count == 0 || !plan_layout(ts, count, op, &L)) return 0;
+    if (!ts || count == 0 || !plan_layout(ts, count, op, fine_launch(ts, count, op), &L)) return 0;
     return L.total;
 }
 
 // Validate, lay the table out in `host` (L.off_partials bytes) and fill in the plan; nothing touches the device.
-// `noting`: the launch may be one whose preparation walks the streams (k_fine).
+// `fine`: the launch goes to k_fine.
 static entro_status build_plan(entro_plan *plan, const entro_tensor *ts, uint32_t count, entro_op op, entro_dtype out_type,
-                               void *workspace, uint64_t workspace_bytes, const Layout &L, unsigned char *host, bool noting) {
+                               void *workspace, uint64_t workspace_bytes, const Layout &L, unsigned char *host, bool fine) {
     std::memset(host, 0, L.off_partials);
     DevTensor *dts = reinterpret_cast<DevTensor *>(host + L.off_tensors);
     WorkItem *items = reinterpret_cast<WorkItem *>(host + L.off_items);
@@ -3807,10 +3819,8 @@ static entro_status build_plan(entro_plan *plan, const entro_tensor *ts, uint32_
                                        });
         shared = share <= lane;
     }
-    // Products go to k_fine instead where every tensor's form allows it, whether their pieces are few or not.
+    // (products that go to k_fine do so whether their pieces are few or not)
     const bool few = shared;
-    bool fine = noting && op == ENTRO_OP_GEMV && (all4 || wide);
-    for (uint32_t i = 0; fine && i < count; ++i) fine = fine_fits(ts[i], dts[i]);
     shared = shared && !fine;
     uint64_t index_at = L.off_index;
     const uint32_t level = shared || fine ? 0u : choose_level(ts, count, lane_slots);
@@ -3930,15 +3940,22 @@ static entro_status build_plan(entro_plan *plan, const entro_tensor *ts, uint32_
     return ENTRO_OK;
 }
 
+// `once`: the launch is prepared for one run, which a walk through the streams (k_fine) would not pay for.  Others go to k_fine
+// where they fit and workspace and staging memory hold what it keeps beside the tables; with less they go the ways of a lane per
+// piece or of shared ones, whose room is all that they have to have.
 static entro_status plan_checks(entro_plan *plan, const entro_tensor *ts, uint32_t count, entro_op op, void *workspace,
-                                uint64_t workspace_bytes, Layout *L) {
+                                uint64_t workspace_bytes, const void *staging, uint64_t staging_bytes, bool once, Layout *L, bool *fine) {
     if (!plan || !ts || !workspace) return ENTRO_ERR_NULL;
     if (count == 0) return ENTRO_ERR_SIZE;
     if (op != ENTRO_OP_DECODE && op != ENTRO_OP_DEQUANT && op != ENTRO_OP_GEMV) return ENTRO_ERR_SCHEME;
     if (!aligned16(workspace)) return ENTRO_ERR_ALIGN;
-    if (!plan_layout(ts, count, op, L)) return ENTRO_ERR_SIZE;
+    *fine = !once && fine_launch(ts, count, op) && plan_layout(ts, count, op, true, L) && workspace_bytes >= L->total &&
+            staging_bytes >= L->off_partials;
+    if (*fine) return staging ? ENTRO_OK : ENTRO_ERR_NULL;
+    if (!plan_layout(ts, count, op, false, L)) return ENTRO_ERR_SIZE;
     if (workspace_bytes < L->total) return ENTRO_ERR_CAPACITY;
-    return ENTRO_OK;
+    if (!staging) return ENTRO_ERR_NULL;
+    return staging_bytes < L->off_partials ? ENTRO_ERR_CAPACITY : ENTRO_OK;
 }
 
 // Enqueue the kernel that builds every tensor's lookup tables into the workspace (behind the copy of the
@@ -3975,7 +3992,7 @@ static entro_status enqueue_tables(const entro_plan *plan, hipStream_t s, bool w
 
 uint64_t entro_plan_staging_bytes(const entro_tensor *ts, uint32_t count, entro_op op) {
     Layout L;
-    if (!ts || count == 0 || !plan_layout(ts, count, op, &L)) return 0;
+    if (!ts || count == 0 || !plan_layout(ts, count, op, fine_launch(ts, count, op), &L)) return 0;
     return L.off_partials;
 }
 
@@ -3983,11 +4000,10 @@ entro_status entro_plan_init_staged(entro_plan *plan, const entro_tensor *ts, ui
                                     entro_dtype out_type, void *workspace, uint64_t workspace_bytes, void *staging,
                                     uint64_t staging_bytes, void *hip_stream) {
     Layout L;
-    entro_status st = plan_checks(plan, ts, count, op, workspace, workspace_bytes, &L);
+    bool fine;
+    entro_status st = plan_checks(plan, ts, count, op, workspace, workspace_bytes, staging, staging_bytes, false, &L, &fine);
     if (st != ENTRO_OK) return st;
-    if (!staging) return ENTRO_ERR_NULL;
-    if (staging_bytes < L.off_partials) return ENTRO_ERR_CAPACITY;
-    st = build_plan(plan, ts, count, op, out_type, workspace, workspace_bytes, L, static_cast<unsigned char *>(staging), true);
+    st = build_plan(plan, ts, count, op, out_type, workspace, workspace_bytes, L, static_cast<unsigned char *>(staging), fine);
     if (st != ENTRO_OK) return st;
     if (!hip_ok(hipMemcpyAsync(workspace, staging, L.off_partials, hipMemcpyHostToDevice, static_cast<hipStream_t>(hip_stream)),
                 "copy plan table"))
@@ -4029,10 +4045,11 @@ static bool put_table(const entro_plan &plan, const unsigned char *host, hipStre
 static entro_status plan_init(entro_plan *plan, const entro_tensor *ts, uint32_t count, entro_op op, entro_dtype out_type,
                               void *workspace, uint64_t workspace_bytes, bool once, void *hip_stream) {
     Layout L;
-    entro_status st = plan_checks(plan, ts, count, op, workspace, workspace_bytes, &L);
+    bool fine;
+    entro_status st = plan_checks(plan, ts, count, op, workspace, workspace_bytes, plan, UINT64_MAX, once, &L, &fine);
     if (st != ENTRO_OK) return st;
     std::vector<unsigned char> host(L.off_partials);
-    st = build_plan(plan, ts, count, op, out_type, workspace, workspace_bytes, L, host.data(), !once);
+    st = build_plan(plan, ts, count, op, out_type, workspace, workspace_bytes, L, host.data(), fine);
     if (st != ENTRO_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     if (once && put_table(*plan, host.data(), s))

@@ -1227,6 +1227,14 @@ def _refill(dt, enc):
             getattr(dt, name).copy_(getattr(other, name))
 
 
+def _without_places(ts):
+    """The same products with a zero-point for which no places are noted: their room is that of a launch without any."""
+    other = [B.CTensor.from_buffer_copy(t) for t in ts]
+    for t in other:
+        t.qp.zero_point = 1000
+    return other
+
+
 # forms that k_fine takes
 NOTED_FORMS = [
     (8, 4096, 256, 67, 4096, 128),       # a row to a unit of 64 lanes
@@ -1304,6 +1312,49 @@ def test_products_do_not_depend_on_how_their_places_were_found(bits, chunk, sub,
         _refill(dt, enc)
         found, noted, fresh = bits_of(plan), bits_of(plan), bits_of(plan_of(E.to_device(enc, DEV)))
         assert torch.equal(found, noted) and torch.equal(noted, fresh)
+
+
+@pytest.mark.parametrize("bits,rows,cols,z", [(8, 67, 4096, 128), (4, 37, 192, 5)])
+def test_products_with_room_for_no_places_run_without_them(bits, rows, cols, z):
+    rng = np.random.default_rng(cols)
+    sym = np.clip(np.rint(rng.standard_normal(rows * cols) * (3 if bits == 8 else 1)) + (1 << (bits - 1)), 0, (1 << bits) - 1).astype(np.uint8)
+    enc = _oracle_encoded(sym, bits, 1024, rows, cols, 0.25, z, 64 if bits == 4 else 128)
+    x = synth.make_x_bf16(3, cols, cols)
+    y_ref, _ = oracle.gemv(sym, rows, cols, 0.25, z, x)
+    dt, xd = E.to_device(enc, DEV), torch.from_numpy(x.view(np.int16)).to(DEV).view(torch.bfloat16)
+    y = torch.zeros(rows, dtype=torch.float32, device=DEV)
+    ts = [dt.ctensor(y, xd)]
+    most, least = (E.entro_workspace_bytes(t, E.ENTRO_OP_GEMV) for t in (ts, _without_places(ts)))
+    staged, staged_least = (E.entro_plan_staging_bytes(t, E.ENTRO_OP_GEMV) for t in (ts, _without_places(ts)))
+    assert most > least and staged >= staged_least
+
+    def room(n):
+        return torch.zeros(n, dtype=torch.uint8, device=DEV)
+
+    def pinned(n):
+        return torch.zeros(n, dtype=torch.uint8).pin_memory()
+    # (workspace, staging memory or none, are places noted?)
+    for ws, staging, noted in [(room(most), None, True), (room(most - 16), None, False), (room(least), None, False),
+                               (room(most), pinned(staged), True), (room(least), pinned(staged_least), False)]:
+        if staging is None:
+            plan = E.entro_plan_init(ts, E.ENTRO_OP_GEMV, E.ENTRO_F32, ws)
+        else:
+            plan = E.entro_plan_init_staged(ts, E.ENTRO_OP_GEMV, E.ENTRO_F32, ws, staging)
+        assert (plan.wide_tables == 2) == noted
+        y.zero_()
+        E.entro_plan_run(plan)
+        _assert_gemv_close(y.cpu().numpy().astype(np.float64), y_ref)
+    # a batch product never notes places, and takes the room of a launch without any
+    ws = room(least)
+    y.zero_()
+    E.entro_decode_gemv_batch(ts, E.ENTRO_F32, ws)
+    _assert_gemv_close(y.cpu().numpy().astype(np.float64), y_ref)
+    with pytest.raises(E.EntroError) as e:
+        E.entro_decode_gemv_batch(ts, E.ENTRO_F32, room(least - 16))
+    assert e.value.status == B.ENTRO_ERR_CAPACITY
+    with pytest.raises(E.EntroError) as e:
+        E.entro_plan_init_staged(ts, E.ENTRO_OP_GEMV, E.ENTRO_F32, ws, pinned(staged_least - 16))
+    assert e.value.status == B.ENTRO_ERR_CAPACITY
 
 
 def test_products_that_lanes_of_noted_places_do_not_take():

@@ -469,6 +469,39 @@ def test_device_entry_points_validate_before_touching_the_gpu():
     assert L.entro_plan_run(C.byref(B.Plan()), None) == B.ENTRO_ERR_NULL
 
 
+def test_room_for_noted_places_is_asked_for_only_where_a_launch_notes_them():
+    """What entro_workspace_bytes says for prepared products: of forms that keep no places, and of tensors that are not filled in
+    yet, no more than without them."""
+    L, op = E.lib(), E.ENTRO_OP_GEMV
+
+    def room(bits=8, sigma=3.0, z=128, cols=4096, chunk=4096, others=()):
+        rng = np.random.default_rng(bits)
+        n = 64 * cols
+        sym = np.clip(np.rint(rng.standard_normal(n) * sigma) + (1 << (bits - 1)), 0, (1 << bits) - 1).astype(np.uint8)
+        cb = E.entro_build_codebook(sym, bits)
+        t = B.CTensor()
+        t.n, t.chunk_symbols, t.rows, t.cols = n, chunk, 64, cols
+        t.stream_bytes = E.entro_encode(sym, cb, chunk)[0].size
+        t.cb, t.qp = C.pointer(cb), B.QParams(0.5, z, bits, 1)
+        ts = (B.CTensor * (1 + len(others)))(t, *others)
+        return L.entro_workspace_bytes(ts, len(ts), op), t, cb
+    least = room(z=1000)[0]
+    noted, t, keep = room()
+    assert noted - least >= 4 * 64 * 64                              # a word per lane of 64 symbols
+    assert room(bits=4, sigma=1.0, z=7)[0] > room(bits=4, sigma=1.0, z=17)[0]
+    for kw in (dict(z=257), dict(z=-2), dict(sigma=60.0)):           # values that the tables do not hold; a lane's stream too long
+        assert room(**kw)[0] == least, kw
+    assert room(cols=4100)[0] == room(cols=4100, z=1000)[0] and room(chunk=4000)[0] == room(chunk=4000, z=1000)[0]
+    assert room(others=(t,))[0] - room(z=1000, others=(t,))[0] >= 2 * 4 * 64 * 64
+    assert room(bits=4, sigma=1.0, z=7, others=(t,))[0] == room(bits=4, sigma=1.0, z=17, others=(t,))[0]     # (one alphabet a launch)
+    t.cb = None
+    assert L.entro_workspace_bytes(C.byref(t), 1, op) == least
+    bad = B.Codebook.from_buffer_copy(keep)
+    bad.len[:] = [255] * 256
+    t.cb = C.pointer(bad)
+    assert L.entro_workspace_bytes(C.byref(t), 1, op) == least
+
+
 @pytest.mark.parametrize("bits,scheme", [(8, 1), (8, 0), (4, 1), (4, 0)])
 def test_qparams_from_range_is_the_quantizer_s_first_half(bits, scheme):
     rng = np.random.default_rng(7 + bits + scheme)
