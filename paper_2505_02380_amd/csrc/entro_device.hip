@@ -2547,7 +2547,9 @@ __global__ __launch_bounds__(kFixWG) void k_fix_batch(const DevTensor *__restric
 //   Rows are cut into lanes so that a wavefront holds whole rows, or goes through a row unit by unit, where the shape allows it.
 // The noted places are a guess, as in k_shared: the unit's first bit is read from the tensor's own tables on every run, every
 // chain has to end where the next one begins, and so by induction all of them are true, whatever the streams hold by now.  A
-// unit that fails is walked piece by piece from the tensor's tables (fine_walk), which also notes its places anew, and decoded from there.
+// unit of lanes whose codes are longer than their columns is decoded from the same places with columns that are filled as it goes
+// (fine_again), and proven likewise; a unit whose places are not true is walked piece by piece from the tensor's tables (fine_walk),
+// which also notes its places anew, and decoded from there.
 //   Measured, a lane per piece -> now, us a launch.  8 bits, 3.5 bits a symbol: 25 M symbols in rows of 4096 36 -> 22, 16.8 M 31 -> 16,
 // 117 M 74 -> 46, 58.7 M in rows of 14336 44 and 5 for the second stage -> 34; the step over 32 layers 6098 -> 3881.  4 bits, 1.55
 // bits a symbol: 9.4 M symbols in rows of 3072, shared by k_shared_batch before, 28 -> 10; the step over 32 layers 4035 -> 1863.
@@ -2597,7 +2599,9 @@ __device__ __forceinline__ uint32_t fine_single(const Tables32 &tb, uint32_t w, 
     return e;
 }
 
-__device__ __forceinline__ uint16_t fine_note(uint32_t bits) { return static_cast<uint16_t>(bits < 0xffffu ? bits : 0xffffu); }
+// A place as it is noted.  (Of a unit of 2^16 bits and more, whose lanes cannot all hold their codes, the lower half: fine_again's
+// caller counts how often it begins anew.  A chain has at most 32 codes of 32 bits.)
+__device__ __forceinline__ uint16_t fine_note(uint32_t bits) { return static_cast<uint16_t>(bits); }
 
 // The places of all chains of the tensors of a prepared launch (blockIdx.y: the tensor, described with a lane per piece), noted
 // on a walk through the pieces with the block path's reader.
@@ -2747,11 +2751,15 @@ __device__ __forceinline__ uint32_t fine_careful(lds_v32 col, const Tables32 &tb
         uint32_t val;
         if constexpr (PAIR) {
             val = e & ~M;
-            uint32_t len = e & M;
+            uint32_t len = e & M, used = len;
             if (miss) {
-                const uint32_t s0 = fine_single<true>(tb, static_cast<uint32_t>(fine_window(col, q) >> Tables32::stale), max_len);
-                const uint32_t s1 = fine_single<true>(tb, static_cast<uint32_t>(fine_window(col, q + entry_len(s0)) >> Tables32::stale), max_len);
-                len = entry_len(s0) + entry_len(s1);
+                // (a window holds a code of 15 bits behind three lookups, and three lookups behind such a code)
+                if (max_len > 15u) w = fine_window(col, q);
+                const uint32_t s0 = fine_single<true>(tb, static_cast<uint32_t>(w >> Tables32::stale), max_len);
+                w = fine_window(col, q + entry_len(s0));
+                const uint32_t s1 = fine_single<true>(tb, static_cast<uint32_t>(w >> Tables32::stale), max_len);
+                used = entry_len(s1);
+                len = entry_len(s0) + used;
                 val = bf16_of(entry_sym(s0) & 15u, zf) | (bf16_of(entry_sym(s1) & 15u, zf) << 16);
             }
             q += len;
@@ -2759,7 +2767,7 @@ __device__ __forceinline__ uint32_t fine_careful(lds_v32 col, const Tables32 &tb
             g.v[1] = i == 1 ? val : g.v[1];
             g.v[FineGroup<PAIR>::kVals - 2] = i == 2 ? val : g.v[FineGroup<PAIR>::kVals - 2];
             g.v[FineGroup<PAIR>::kVals - 1] = i == 3 ? val : g.v[FineGroup<PAIR>::kVals - 1];
-            w >>= len & 15u;
+            w >>= used;
         } else {
             if (miss) {
                 e = lookup_l2(tb, e, static_cast<uint32_t>(w >> Tables32::stale));
@@ -2773,7 +2781,7 @@ __device__ __forceinline__ uint32_t fine_careful(lds_v32 col, const Tables32 &tb
             w >>= entry_len(e);
         }
         if (++i == 4u) return q;
-        if (miss) w = fine_window(col, q);
+        if (miss && (!PAIR || max_len > 15u)) w = fine_window(col, q);
         e = lut_at(tb, static_cast<uint32_t>(w) & (kL1Mask << Tables32::stale));
     }
 }
@@ -2840,40 +2848,6 @@ __device__ __forceinline__ float dot2(uint32_t v, uint32_t x, float acc) {
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, v), __builtin_bit_cast(bf16x2, x), acc, false);
 }
 
-// A unit whose noted places do not hold: its pieces are walked from the tensor's own tables, a lane each, and the places are noted
-// anew.  Where the lane's two chains begin, in bits from the unit's first, is returned in a and b (place: room for both of every lane).
-template <bool PAIR>
-__device__ __forceinline__ void fine_walk(const DevTensor &t, const Tables32 &tb, lds_v32 place, uint32_t unit, uint64_t base, uint32_t &a,
-                                          uint32_t &b) {
-    const uint32_t lane = threadIdx.x & 63u, k = unit * t.fine_pieces + lane;
-    uint16_t *index = reinterpret_cast<uint16_t *>(t.fine_index);
-    const uint32_t last_off = t.stream_bytes - 8u, max_len = t.max_len;
-    wave_sync_lds();
-    if (lane < t.fine_pieces && k < t.n_chunks) {
-        const uint64_t left = t.n - static_cast<uint64_t>(k) * t.chunk_symbols;
-        const uint32_t nsym = left < t.chunk_symbols ? static_cast<uint32_t>(left) : t.chunk_symbols;
-        uint32_t at = lane * t.chunk_symbols / t.fine_len, i = lane * t.chunk_symbols - at * t.fine_len;
-        uint64_t pos = seg_start(t, k);
-#pragma unroll 1
-        for (uint32_t s = 0; s < nsym; ++s) {
-            if (i == 0 || i == t.fine_first) {
-                const uint32_t bits = static_cast<uint32_t>(pos - base);
-                place[2u * at + (i ? 1u : 0u)] = bits;
-                index[2u * (unit * 64u + at) + (i ? 1u : 0u)] = fine_note(bits);
-            }
-            pos += entry_len(fine_single<PAIR>(tb, static_cast<uint32_t>(load_bits(t.stream, pos, last_off)), max_len));
-            if (++i == t.fine_len) {
-                i = 0;
-                ++at;
-            }
-        }
-    }
-    wave_sync_lds();
-    a = place[2u * lane];
-    b = place[2u * lane + 1u];
-    wave_sync_lds();
-}
-
 // `N` pieces of sixteen bytes of the stream, from absolute bit `pos` on, into the dwords that `col` is the first of.  Returns the
 // position of that bit, as if they were dwords 1 and up of the lane's column.
 template <uint32_t N>
@@ -2890,13 +2864,91 @@ __device__ __forceinline__ uint32_t fine_fill(const DevTensor &t, lds_v32 col, u
     return (static_cast<uint32_t>(pos) & 31u) + 32u - Tables32::stale;
 }
 
-// The sum of a lane whose chains begin a and b bits behind the unit's first, whatever their length: half of its column for the
-// next group of either chain, filled before each.  Groups, values and sums come in the order that k_fine's own loop has them in,
-// so that a unit's sums are the same to the last bit, however its places have been found.
+// Half a column, dwords 1 to 8 or 9 to 16, filled behind a dword's end holds a group of the longest codes: four of 32 bits, or
+// eight of 28 (fine_fits).  Does what is left of it, from position q on, hold one?
+constexpr uint32_t kFineHalf = 8;
+template <bool PAIR>
+__device__ __forceinline__ bool fine_short(uint32_t q, uint32_t max_len) {
+    return q + (PAIR ? 8u : 4u) * max_len > 32u * (kFineHalf + 1u) - Tables32::stale;
+}
+
+// The position behind the group of four lookups that begins at q.
+template <bool PAIR>
+__device__ __forceinline__ uint32_t fine_skip(lds_v32 col, const Tables32 &tb, uint32_t max_len, uint32_t q) {
+    constexpr uint32_t M = FineGroup<PAIR>::kLenMask;
+    uint64_t w = fine_window(col, q);
+    uint32_t bits = 0, len = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        len = lut_at(tb, static_cast<uint32_t>(w) & (kL1Mask << Tables32::stale)) & M;
+        w >>= len;
+        bits += len;
+    }
+    if (__builtin_expect(len == 0, 0)) {                 // (a code that the first level does not hold ends the others' advance)
+        bits = 0;
+#pragma unroll 1
+        for (int i = 0; i < (PAIR ? 8 : 4); ++i)
+            bits += entry_len(fine_single<PAIR>(tb, static_cast<uint32_t>(fine_window(col, q + bits) >> Tables32::stale), max_len));
+    }
+    return q + bits;
+}
+
+// A unit whose noted places do not hold: its pieces are walked from the tensor's own tables, a lane each, and the places are noted
+// anew.  Where the lane's two chains begin, in bits from the unit's first, is returned in a and b.  The stream comes through the
+// first half of a lane's column; places lie in the second.
+//   The lanes that are left over walk `ahead` - 1 units more, `stride` apart, that this workgroup has yet to come to, and note their
+// places: buffers that have been given other contents have them all over.  A launch behind other contents, symbol by symbol from
+// memory -> now: 16.8 M symbols of 3.6 bits in pieces of 256 121 -> 61 us, 58.7 M 367 -> 102, 16.8 M in pieces of 4096 934 -> 391.
+template <bool PAIR>
+__device__ __forceinline__ void fine_walk(const DevTensor &t, const Tables32 &tb, lds_v32 col, uint32_t max_len, uint32_t unit, uint32_t stride,
+                                          uint32_t ahead, uint32_t &a, uint32_t &b) {
+    constexpr uint32_t SPG = PAIR ? 8u : 4u;             // symbols of a group
+    const uint32_t lane = threadIdx.x & 63u, P = t.chunk_symbols, L = t.fine_len, per = t.fine_pieces;
+    uint32_t j = lane / per, of_unit = lane - j * per;
+    const bool live = j < ahead && (j + 1u) * per <= 64u && (unit + j * stride) * per + of_unit < t.n_chunks;
+    j = live ? j : 0u;                                   // (a lane without a piece walks the unit's first and notes nothing)
+    of_unit = live ? of_unit : 0u;
+    const uint32_t u = unit + j * stride, k = u * per + of_unit;
+    const uint64_t left = t.n - static_cast<uint64_t>(k) * P, base = seg_start(t, u * per);
+    const uint32_t nsym = !live ? 0u : left < P ? static_cast<uint32_t>(left) : P;
+    const lds_v32 place = col - lane + (kFineHalf + 1u) * 64u;
+    uint16_t *index = reinterpret_cast<uint16_t *>(t.fine_index) + 128u * static_cast<uint64_t>(u);
+    uint32_t at = of_unit * P / L, i = of_unit * P - at * L, from = 0, q = 0;
+    uint64_t pos = seg_start(t, k);
+    wave_sync_lds();
+#pragma unroll 1
+    for (uint32_t s = 0; s < P; s += SPG) {
+        if (s == 0 || __builtin_amdgcn_ballot_w64(fine_short<PAIR>(q, max_len)) != 0) {
+            pos += q - from;
+            from = q = fine_fill<kFineHalf / 4u>(t, col + 64u, pos);
+        }
+        if (s < nsym && (i == 0 || i == t.fine_first)) {
+            const uint32_t bits = static_cast<uint32_t>(pos - base) + q - from, chain = i ? 1u : 0u;
+            if (j == 0) place[chain * 64u + at] = bits;
+            index[2u * at + chain] = fine_note(bits);
+        }
+        q = fine_skip<PAIR>(col, tb, max_len, q);
+        i += SPG;
+        at += i == L ? 1u : 0u;
+        i = i == L ? 0u : i;
+    }
+    wave_sync_lds();
+    a = place[lane];
+    b = place[64u + lane];
+    wave_sync_lds();
+}
+
+// The sum of a lane whose chains begin a and b bits behind the unit's first, whatever their length: half of its column for either
+// chain, filled where that may not hold the next group.  a and b become where the chains end.  Groups, values and sums come in the
+// order that k_fine's own loop has them in, so that a unit's sums are the same to the last bit, however its places have been found.
+//   For units of lanes with more bits than a column, and those of walked pieces.  Rows of log-normal spread (0.8) at 4.8 bits a symbol
+// on average, walked in every launch -> now: 16.8 M symbols 120 -> 29 us, 58.7 M 219 -> 54; a lane per piece takes 96 and 127.
 template <bool PAIR, class X>
 __device__ __forceinline__ float fine_again(const DevTensor &t, const Tables32 &tb, lds_v32 col, uint32_t max_len, float zf, uint64_t base,
-                                            uint32_t a, uint32_t b, X activations) {
+                                            uint32_t &a, uint32_t &b, X activations) {
     const uint32_t pieces = t.fine_len / 8u, steps = (pieces + 1u) / 2u;
+    uint32_t from = 0, from_b = 0, qa = 0, qb = 0, end_b = 0;
+    uint64_t pos_a = base + a, pos_b = base + b;
     float acc = 0.0f;
 #pragma unroll 1
     for (uint32_t s = 0; s < steps; ++s) {
@@ -2905,19 +2957,25 @@ __device__ __forceinline__ float fine_again(const DevTensor &t, const Tables32 &
         if (steps + s >= pieces) xb = u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
         for (int h = 0; h < (PAIR ? 1 : 2); ++h) {
-            const uint32_t from_a = fine_fill<2>(t, col + 64u, base + a), from_b = fine_fill<2>(t, col + 9u * 64u, base + b) + 8u * 32u;
-            uint32_t qa = from_a, qb = from_b;
+            if ((s == 0 && h == 0) ||
+                __builtin_amdgcn_ballot_w64(fine_short<PAIR>(qa, max_len) || fine_short<PAIR>(qb - 32u * kFineHalf, max_len)) != 0) {
+                pos_a += qa - from;
+                pos_b += qb - from_b;
+                from = qa = fine_fill<kFineHalf / 4u>(t, col + 64u, pos_a);
+                from_b = qb = fine_fill<kFineHalf / 4u>(t, col + (kFineHalf + 1u) * 64u, pos_b) + 32u * kFineHalf;
+            }
             FineGroup<PAIR> ga, gb;
             fine_groups<PAIR>(col, tb, max_len, zf, qa, qb, ga, gb);
-            a += qa - from_a;
-            b += qb - from_b;
 #pragma unroll
             for (int v = 0; v < FineGroup<PAIR>::kVals; ++v) {
                 acc = dot2(ga.v[v], xa[(PAIR ? 0 : 2 * h) + v], acc);
                 acc = dot2(gb.v[v], xb[(PAIR ? 0 : 2 * h) + v], acc);
             }
         }
+        if (steps + s < pieces) end_b = static_cast<uint32_t>(pos_b - base) + qb - from_b;
     }
+    a = static_cast<uint32_t>(pos_a - base) + qa - from;
+    b = end_b;
     return acc;
 }
 
@@ -3065,44 +3123,65 @@ __global__ __launch_bounds__(64 * kFineWaves) void k_fine(const DevTensor *__res
             const uint32_t a = u.places & 0xffffu, b = u.places >> 16, next = u.next;
             const uint32_t q0 = u.q;
             fine_ask(t, unit_next, u);
-            uint32_t qa = q0, qb = q0 + (b - a), end_b = qb;
-            float acc = 0.0f;
-#pragma unroll
-            for (uint32_t s = 0; s < 4; ++s) {
-                if (s < steps) {
-#pragma unroll
-                    for (int h = 0; h < (PAIR ? 1 : 2); ++h) {
-                        FineGroup<PAIR> ga, gb;
-                        fine_groups<PAIR>(col, sm.tb, max_len, zf, qa, qb, ga, gb);
-                        if constexpr (PAIR) {
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) {
-                                acc = dot2(ga.v[v], x[s][v], acc);
-                                acc = dot2(gb.v[v], x[4 + s][v], acc);
-                            }
-                        } else {
-#pragma unroll
-                            for (int v = 0; v < 2; ++v) {
-                                acc = dot2(ga.v[v], x[s][2 * h + v], acc);
-                                acc = dot2(gb.v[v], x[4 + s][2 * h + v], acc);
-                            }
-                        }
-                    }
-                    end_b = steps + s < pieces ? qb : end_b;
-                }
-                if (s == 0) fine_load(t, u);
-            }
-            // every chain ends where the next one begins, and the unit's first begins at its first bit
+            // the last lane of the tensor or the unit has none behind it; do the others' codes fit their columns, as far as noted?
             const uint32_t fl = unit * 64u + lane;
             const bool last_lane = lane == 63u || fl + 1u >= t.fine_n;
-            const bool good = qa - q0 == b - a && (last_lane || end_b - q0 == next - a) && end_b <= kFineEnd - Tables32::stale &&
-                              (lane != 0 || a == 0);
-            if (__builtin_expect(__builtin_amdgcn_ballot_w64(fl < t.fine_n && !good) != 0, 0)) {
+            const uint32_t bits = (next - a) & 0xffffu;
+            bool again = __builtin_amdgcn_ballot_w64(!last_lane && q0 + bits > kFineEnd - Tables32::stale) != 0, walk = false;
+            float acc = 0.0f;
+            if (__builtin_expect(!again, 1)) {
+                uint32_t qa = q0, qb = q0 + (b - a), end_b = qb;
+#pragma unroll
+                for (uint32_t s = 0; s < 4; ++s) {
+                    if (s < steps) {
+#pragma unroll
+                        for (int h = 0; h < (PAIR ? 1 : 2); ++h) {
+                            FineGroup<PAIR> ga, gb;
+                            fine_groups<PAIR>(col, sm.tb, max_len, zf, qa, qb, ga, gb);
+                            if constexpr (PAIR) {
+#pragma unroll
+                                for (int v = 0; v < 4; ++v) {
+                                    acc = dot2(ga.v[v], x[s][v], acc);
+                                    acc = dot2(gb.v[v], x[4 + s][v], acc);
+                                }
+                            } else {
+#pragma unroll
+                                for (int v = 0; v < 2; ++v) {
+                                    acc = dot2(ga.v[v], x[s][2 * h + v], acc);
+                                    acc = dot2(gb.v[v], x[4 + s][2 * h + v], acc);
+                                }
+                            }
+                        }
+                        end_b = steps + s < pieces ? qb : end_b;
+                    }
+                    if (s == 0) fine_load(t, u);
+                }
+                // every chain ends where the next one begins, and the unit's first begins at its first bit
+                const bool good = qa - q0 == b - a && (last_lane || end_b - q0 == next - a) && end_b <= kFineEnd - Tables32::stale &&
+                                  (lane != 0 || a == 0);
+                const uint64_t bad = __builtin_amdgcn_ballot_w64(fl < t.fine_n && !good);
+                again = bad != 0;
+                walk = (bad & __builtin_amdgcn_ballot_w64(!last_lane)) != 0;      // (a last lane's column may be too short)
+            }
+            if (__builtin_expect(again, 0)) {
                 const uint64_t base = seg_start(t, unit * t.fine_pieces);
-                uint32_t from_a, from_b;
-                fine_walk<PAIR>(t, sm.tb, (lds_v32)(sm.col + (wave * kFineData + 1u) * 64u), unit, base, from_a, from_b);
-                acc = fine_again<PAIR>(t, sm.tb, col, max_len, zf, base, from_a, from_b,
-                                       [&](uint32_t j) __attribute__((always_inline)) { return activations(here / 8u + j); });
+                const uint64_t anew = __builtin_amdgcn_ballot_w64(!last_lane && next < a);
+                uint32_t from_a = a + (__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(anew >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(anew), 0u)) << 16);
+                uint32_t from_b = from_a + ((b - a) & 0xffffu);
+                const uint32_t next_a = from_a + bits;
+#pragma unroll 1
+                for (;; walk = true) {
+                    if (walk) {
+                        const bool one = t.fine_units == 1u;
+                        fine_walk<PAIR>(t, sm.tb, col, max_len, unit, one ? kFineWaves : 1u,
+                                        one ? (n_quanta - g + kFineWaves - 1u) / kFineWaves : t.fine_units - of_row, from_a, from_b);
+                    }
+                    uint32_t end_a = from_a, end_b = from_b;
+                    acc = fine_again<PAIR>(t, sm.tb, col, max_len, zf, base, end_a, end_b,
+                                           [&](uint32_t j) __attribute__((always_inline)) { return activations(here / 8u + j); });
+                    const bool good = end_a == from_b && (last_lane || end_b == next_a) && (lane != 0 || from_a == 0);
+                    if (walk || __builtin_amdgcn_ballot_w64(fl < t.fine_n && !good) == 0) break;
+                }
                 // (what a wavefront holds for its next unit is asked for again: kept over all this, some of it is spilled)
 #pragma unroll
                 for (uint32_t p = 0; p < 8; ++p) x[p] = u32x4{0u, 0u, 0u, 0u};

@@ -1314,6 +1314,74 @@ def test_products_do_not_depend_on_how_their_places_were_found(bits, chunk, sub,
         assert torch.equal(found, noted) and torch.equal(noted, fresh)
 
 
+def _plan_of(ts, out, places=True):
+    """A prepared product, and its workspace: with places where the form allows it, or in a workspace that has no room for any."""
+    ws = torch.zeros(E.entro_workspace_bytes(ts if places else _without_places(ts), E.ENTRO_OP_GEMV), dtype=torch.uint8, device=DEV)
+    plan = E.entro_plan_init(ts, E.ENTRO_OP_GEMV, out, ws)
+    assert (plan.wide_tables == 2) == places
+    return plan, ws
+
+
+@pytest.mark.parametrize("bits,chunk,sub,rows,cols,z", NOTED_FORMS)
+def test_products_of_lanes_with_more_bits_than_their_columns_hold(bits, chunk, sub, rows, cols, z):
+    """Stretches of long codes among short ones, up to 2^16 bits of a unit and more: against the oracle and, to the last bit, in every
+    run the same, with the places noted beforehand, found anew and noted then."""
+    top, n = (1 << bits) - 1, rows * cols
+    lengths = np.array(list(range(1, 32)) + [32, 32] if bits == 8 else list(range(1, 15)) + [15, 15])
+    rng = np.random.default_rng(n + bits)
+    first = rng.choice(lengths.size, n, p=0.5 ** lengths / (0.5 ** lengths).sum()).astype(np.uint8)
+    for at in rng.integers(0, n, n // 4096 + 2):             # stretches of 200 symbols with codes of 10 bits and more
+        first[at:at + 200] = rng.integers(9, 15, first[at:at + 200].size)
+    unit = n // 2 // 4096 * 4096                             # and a whole unit, or what there is, of the longest codes
+    first[unit:unit + min(4096, n // 12)] = lengths.size - 1
+    x = synth.make_x_bf16(3, cols, cols)
+    xd = torch.from_numpy(x.view(np.int16)).to(DEV).view(torch.bfloat16)
+    cb = E.entro_codebook_from_lengths(np.pad(lengths, (0, top + 1 - lengths.size)).astype(np.uint8), bits)
+    y = torch.zeros(rows, dtype=torch.float32, device=DEV)
+
+    def held(sym):
+        stream, off = E.entro_encode(sym, cb, chunk)
+        enc = B.EncodedTensor(stream, off, n, chunk, cb, B.QParams(np.float32(0.25), z, bits, E.ENTRO_ASYMMETRIC), rows, cols)
+        if sub:
+            enc.sub_symbols, enc.sub_bits = sub, E.entro_sub_index(sym, cb, chunk, sub)
+        return enc
+    other, dt, plan = rng.permutation(first), None, None
+    for sym in (first, np.roll(first, 1), other):
+        if dt is None:
+            dt = E.to_device(held(sym), DEV)
+            plan = _plan_of([dt.ctensor(y, xd)], E.ENTRO_F32)
+        else:
+            _refill(dt, held(sym))
+        terms = (sym.reshape(rows, cols).astype(np.float64) - z) * 0.25 * (x.astype(np.uint32) << 16).view(np.float32).astype(np.float64)
+        bound = (cols + 2) * 2.0 ** -24 * np.abs(terms).sum(1)   # fp32 sums of exact products
+        fresh, runs = _plan_of([dt.ctensor(y, xd)], E.ENTRO_F32), []
+        for p in (plan, plan, fresh):
+            y.fill_(7.0)
+            E.entro_plan_run(p[0])
+            assert (np.abs(y.double().cpu().numpy() - terms.sum(1)) <= bound).all()
+            runs.append(y.view(torch.int32).clone())
+        assert torch.equal(runs[0], runs[1]) and torch.equal(runs[1], runs[2])
+
+
+def test_rows_of_wide_spread_take_no_longer_than_a_lane_per_piece():
+    """Rows of different spread under one scale: some lanes have more bits than their columns hold.  0.3 of the time that a lane per
+    piece takes (1.25 where such a unit was walked in every launch)."""
+    rows, cols, gen = 4096, 4096, torch.Generator(device=DEV)
+    gen.manual_seed(1)
+    w = torch.randn(rows, cols, device=DEV, generator=gen) * torch.exp(torch.randn(rows, 1, device=DEV, generator=gen) * 0.8) * 0.02
+    d, q = E.compress_on_device(w.clamp_(-0.4, 0.4).view(-1), 8, E.ENTRO_ASYMMETRIC, 4096, rows=rows, cols=cols, return_q=True)
+    d.enc.sub_symbols = 256
+    ln = torch.from_numpy(d.enc.cb.lengths().astype(np.int32)).to(DEV)
+    d.sub_bits = ln[q.int()].view(-1, 256).sum(1).to(torch.int16)
+    x = torch.randn(cols, device=DEV, generator=gen).to(torch.bfloat16)
+    assert int(ln[q.int()].view(-1, 64).sum(1).max()) > 512 and float(ln[q.int()].float().mean()) < 6.0
+    ys = [torch.zeros(rows, dtype=torch.float32, device=DEV) for _ in range(2)]
+    plans = [_plan_of([d.ctensor(y, x)], E.ENTRO_F32, places) for y, places in zip(ys, (True, False))]
+    us = _times_us([lambda p=p: E.entro_plan_run(p[0]) for p in plans], 10)
+    assert float((ys[0] - ys[1]).norm() / ys[1].norm()) <= 1e-6
+    assert us[0] <= 0.7 * us[1], us
+
+
 @pytest.mark.parametrize("bits,rows,cols,z", [(8, 67, 4096, 128), (4, 37, 192, 5)])
 def test_products_with_room_for_no_places_run_without_them(bits, rows, cols, z):
     rng = np.random.default_rng(cols)
