@@ -3899,7 +3899,6 @@ static entro_status build_plan(entro_plan *plan, const entro_tensor *ts, uint32_
         shared = share <= lane;
     }
     // (products that go to k_fine do so whether their pieces are few or not)
-    const bool few = shared;
     shared = shared && !fine;
     uint64_t index_at = L.off_index;
     const uint32_t level = shared || fine ? 0u : choose_level(ts, count, lane_slots);
@@ -4011,7 +4010,7 @@ static entro_status build_plan(entro_plan *plan, const entro_tensor *ts, uint32_
     plan->pair_tables = pairs ? 1u : 0u;
     plan->wide_tables = fine ? 2u : (op == ENTRO_OP_GEMV && !pairs && wide) ? 1u : 0u;
     plan->gemv_multirow = multirow ? 1u : 0u;
-    plan->shared_wave_bytes = shared ? wave_bytes : fine && few ? kFineData * 256u : 0u;
+    plan->shared_wave_bytes = shared ? wave_bytes : 0u;
     plan->off_tensors = L.off_tensors;
     plan->off_items = L.off_items;
     plan->off_partials = L.off_partials;

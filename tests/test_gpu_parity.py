@@ -592,7 +592,7 @@ def test_prepared_decoding_without_entry_points_shares_segments(bits, out):
 
 @pytest.mark.parametrize("sub,shared", [(512, True), (256, False)])
 def test_products_of_4bit_rows_in_pieces(sub, shared):
-    # 16384 pieces, rows of eight of them: shared in pieces of 512 (15.7 us, 25.3 with a lane each), not of 256 (17.3, and 14.9)
+    # without places (_plan_of).  16384 pieces, rows of eight of them: shared in pieces of 512 (15.7 us, 25.3 with a lane each), not of 256 (17.3, and 14.9)
     rows, cols = 2048, 8 * sub
     enc, sym = _out_of_step(4, 16 * sub, rows * cols, rows, cols, sub)
     rng = np.random.default_rng(sub)
@@ -602,10 +602,9 @@ def test_products_of_4bit_rows_in_pieces(sub, shared):
     us, plans = [], []
     for e, s in ((_oracle_encoded(bell, 4, 16 * sub, rows, cols, 0.25, 7, sub), bell), (enc, sym)):
         dt, y = E.to_device(e, DEV), torch.zeros(rows, dtype=torch.float32, device=DEV)
-        ts = [dt.ctensor(y, xd)]
-        ws = torch.zeros(E.entro_workspace_bytes(ts, E.ENTRO_OP_GEMV), dtype=torch.uint8, device=DEV)
-        plans.append(E.entro_plan_init(ts, E.ENTRO_OP_GEMV, E.ENTRO_F32, ws))
-        us.append(_times_us([lambda: E.entro_plan_run(plans[-1])], 20)[0])
+        plan, ws = _plan_of([dt.ctensor(y, xd)], E.ENTRO_F32, places=False)
+        plans.append(plan)
+        us.append(_times_us([lambda: E.entro_plan_run(plan)], 20)[0])
         y_ref, _ = oracle.gemv(s, rows, cols, 0.25, 7, x)
         _assert_gemv_close(y.cpu().numpy().astype(np.float64), y_ref)
     assert [p.shared_wave_bytes > 0 for p in plans] == [shared, False]
@@ -631,7 +630,7 @@ def test_twice_the_segments_take_twice_the_time():
 @pytest.mark.parametrize("bits,most,chunk,segments,shared", [(8, 3.0, 512, 40960, False), (8, 3.0, 512, 14336, True), (4, 9.0, 1024, 40960, False),
                                                              (4, 9.0, 1024, 24576, True)])
 def test_products_share_pieces_only_where_that_is_not_slower(bits, most, chunk, segments, shared):
-    """The more bits a symbol takes, the more a shared segment costs and the fewer segments are shared.  Of the time of a lane
+    """Products without places (_plan_of).  The more bits a symbol takes, the more a shared segment costs and the fewer segments are shared.  Of the time of a lane
     per segment: up to 1.26 (a lane each as well, but the yardstick's stream is a third as long as 7.5 bits a symbol make it),
     2.1 where the number of segments alone decides."""
     cols, gen = 1024, torch.Generator(device=DEV)
@@ -643,9 +642,9 @@ def test_products_share_pieces_only_where_that_is_not_slower(bits, most, chunk, 
     lane, plans, ws = E.to_device(_out_of_step(bits, chunk, rows * cols, rows, cols)[0], DEV), [], []
     ys = [torch.zeros(rows, dtype=torch.float32, device=DEV) for _ in range(2)]
     for dt, y in zip((d, lane), ys):
-        ts = [dt.ctensor(y, x)]
-        ws.append(torch.zeros(E.entro_workspace_bytes(ts, E.ENTRO_OP_GEMV), dtype=torch.uint8, device=DEV))
-        plans.append(E.entro_plan_init(ts, E.ENTRO_OP_GEMV, E.ENTRO_F32, ws[-1]))
+        plan, room = _plan_of([dt.ctensor(y, x)], E.ENTRO_F32, places=False)
+        plans.append(plan)
+        ws.append(room)
     assert [p.shared_wave_bytes > 0 for p in plans] == [shared, False]
     us = _times_us([lambda p=p: E.entro_plan_run(p) for p in plans])
     terms = (q.view(rows, cols).to(torch.float32) - d.enc.qp.zero_point).double() * float(d.enc.qp.scale) * x.double()
@@ -1209,9 +1208,7 @@ def test_few_units_per_workgroup_run_side_by_side(y_type):
         dt = E.to_device(enc, DEV)
         x = torch.from_numpy(synth.make_x_bf16(9, units, cols).view(np.int16)).to(DEV).view(torch.bfloat16)
         y = torch.zeros(rows, dtype=torch.float32 if y_type == E.ENTRO_F32 else torch.bfloat16, device=DEV)
-        ts = [dt.ctensor(y, x)]
-        ws = torch.zeros(E.entro_workspace_bytes(ts, E.ENTRO_OP_GEMV), dtype=torch.uint8, device=DEV)
-        plan = E.entro_plan_init(ts, E.ENTRO_OP_GEMV, y_type, ws)
+        plan, ws = _plan_of([dt.ctensor(y, x)], y_type, places=False)
         assert plan.shared_wave_bytes == 0
         us.append(_times_us([lambda: E.entro_plan_run(plan)], 20)[0])
         y_ref, _ = oracle.gemv(sym, rows, cols, 0.25, 7, synth.make_x_bf16(9, units, cols))
@@ -1318,7 +1315,7 @@ def _plan_of(ts, out, places=True):
     """A prepared product, and its workspace: with places where the form allows it, or in a workspace that has no room for any."""
     ws = torch.zeros(E.entro_workspace_bytes(ts if places else _without_places(ts), E.ENTRO_OP_GEMV), dtype=torch.uint8, device=DEV)
     plan = E.entro_plan_init(ts, E.ENTRO_OP_GEMV, out, ws)
-    assert (plan.wide_tables == 2) == places
+    assert (plan.wide_tables == 2) == places and (plan.shared_wave_bytes == 0 or not places)
     return plan, ws
 
 
