@@ -3707,13 +3707,13 @@ FineShape fine_shape(const entro_tensor &t) {
     return {0, 0};
 }
 
-// Does this product go to k_fine?  Codes that do not fall into step (falls_into_step) stay with a lane per piece in every launch;
-// weights have none, and a lane per piece has to remain the yardstick that the library's times are taken against.  Its lanes have to hold the symbols' stream (three standard deviations of a lane's bits are
-// left free, and more), its tables the symbols' values: integers of at most 256 in magnitude, or 16 for 4-bit symbols.
+// Does this product go to k_fine?  Its lanes have to hold the stream of their symbols (at the tensor's mean rate and 80 bits more,
+// where rows are alike six standard deviations of a lane's bits; lanes that do not take longer), its tables the symbols' values:
+// integers of at most 256 in magnitude, or 16 for 4-bit symbols.
 // (Asked before the tensor has been looked at, by the calls that only say how much room a launch takes.)
 bool fine_fits(const entro_tensor &t) {
     const FineShape f = fine_shape(t);
-    if (f.len == 0 || t.n / f.len >= (uint64_t{1} << 31) || check_codebook(t.cb) != ENTRO_OK || !falls_into_step(t.cb)) return false;
+    if (f.len == 0 || t.n / f.len >= (uint64_t{1} << 31) || check_codebook(t.cb) != ENTRO_OK) return false;
     const bool four = t.cb->bits == 4;
     if (t.qp.zero_point < -1 || t.qp.zero_point > (four ? 16 : 256)) return false;
     if (four && t.cb->max_len > 28) return false;            // (fine_again: eight codes and a dword's end in half a column)

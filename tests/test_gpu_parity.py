@@ -1379,6 +1379,22 @@ def test_rows_of_wide_spread_take_no_longer_than_a_lane_per_piece():
     assert us[0] <= 0.7 * us[1], us
 
 
+@pytest.mark.parametrize("bits,chunk,sub,rows,cols", [(8, 4096, 256, 3000, 4096), (8, 4096, 0, 101, 2880), (4, 4096, 512, 3072, 3072)])
+def test_products_under_codes_that_do_not_fall_into_step(bits, chunk, sub, rows, cols):
+    # places are walked, not guessed: such codes have them like any other (9.3, 9.8 and 7.5 us; without 22.5, 245 and 26.0)
+    enc, sym = _out_of_step(bits, chunk, rows * cols, rows, cols, sub)
+    x = synth.make_x_bf16(5, 0, cols)
+    dt, xd = E.to_device(enc, DEV), torch.from_numpy(x.view(np.int16)).to(DEV).view(torch.bfloat16)
+    y = torch.zeros(rows, dtype=torch.float32, device=DEV)
+    plans = [_plan_of([dt.ctensor(y, xd)], E.ENTRO_F32, places) for places in (True, False)]
+    us = _times_us([lambda p=p: E.entro_plan_run(p[0]) for p in plans], 10)
+    E.entro_plan_run(plans[0][0])
+    y_ref, _ = oracle.gemv(sym, rows, cols, 0.25, 7, x)
+    terms = np.abs((sym.reshape(rows, cols).astype(np.float64) - 7) * 0.25) @ np.abs((x.astype(np.uint32) << 16).view(np.float32).astype(np.float64))
+    assert np.all(np.abs(y.double().cpu().numpy() - y_ref) <= (cols + 2) * 2.0 ** -24 * terms)
+    assert us[0] <= us[1], us
+
+
 @pytest.mark.parametrize("bits,rows,cols,z", [(8, 67, 4096, 128), (4, 37, 192, 5)])
 def test_products_with_room_for_no_places_run_without_them(bits, rows, cols, z):
     rng = np.random.default_rng(cols)
