@@ -2603,7 +2603,7 @@ __device__ __forceinline__ uint32_t fine_single(const Tables32 &tb, uint32_t w, 
 // caller counts how often it begins anew.  A chain has at most 32 codes of 32 bits.)
 __device__ __forceinline__ uint16_t fine_note(uint32_t bits) { return static_cast<uint16_t>(bits); }
 
-// The places of all chains of the tensors of a prepared launch (blockIdx.y: the tensor, described with a lane per piece), noted
+// The places of all chains of the tensors of a prepared launch (blockIdx.x: the tensor, described with a lane per piece), noted
 // on a walk through the pieces with the block path's reader.
 // What it costs a preparation, against a walk by single loads from memory (which reads every line many times over): a launch over
 // 58.7 M symbols of 8 bits 692 -> 83 us, over 50 M symbols of 4 bits 247 -> 50 us.
@@ -2614,13 +2614,13 @@ __global__ __launch_bounds__(64 * kFineWaves) void k_fine_index(const DevTensor 
         uint32_t ring[kFineWaves][kRing2Dwords * 64];
     } sm;
     constexpr uint32_t SPG = PAIR ? 8u : 4u;             // symbols of a group
-    const DevTensor &t = tensors[blockIdx.y];
-    if (blockIdx.x * 1024u >= t.n_chunks) return;
+    const DevTensor &t = tensors[blockIdx.x];
+    if (blockIdx.y * 1024u >= t.n_chunks) return;
     build_tables<64 * kFineWaves, PAIR>(t, sm.tb, &sm.ring[0][0]);
     const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
     const uint32_t P = t.chunk_symbols, L = t.fine_len, A = t.fine_first, per = t.fine_pieces, max_len = t.max_len;
     uint16_t *index = reinterpret_cast<uint16_t *>(t.fine_index);
-    for (uint32_t first = blockIdx.x * 1024u + wave * 64u; first < t.n_chunks; first += gridDim.x * 1024u) {
+    for (uint32_t first = blockIdx.y * 1024u + wave * 64u; first < t.n_chunks; first += gridDim.y * 1024u) {
         const bool live = first + lane < t.n_chunks;
         const uint32_t k = live ? first + lane : first;  // (a lane without a piece walks the wavefront's first and notes nothing)
         const uint32_t unit = k / per, in_unit = (k - unit * per) * P;
@@ -4041,8 +4041,8 @@ static entro_status plan_checks(entro_plan *plan, const entro_tensor *ts, uint32
 static entro_status enqueue_tables(const entro_plan *plan, hipStream_t s, bool with_items = false) {
     const DevTensor *dts = reinterpret_cast<const DevTensor *>(static_cast<const unsigned char *>(plan->workspace) + plan->off_tensors);
     if (plan->wide_tables == 2u) {
-        // (workgroups without a piece of their tensor end at once)
-        const dim3 index_grid(std::max(8u, 512u / plan->count), plan->count);
+        // (workgroups without a piece of their tensor end at once; tensors in x, which may be more than 65535)
+        const dim3 index_grid(plan->count, std::max(8u, 512u / plan->count));
         if (plan->pair_tables) {
             hipLaunchKernelGGL(k_fine_pairs, dim3(plan->count), dim3(1024), 0, s, dts);
             hipLaunchKernelGGL(k_fine_index<true>, index_grid, dim3(1024), 0, s, dts);

@@ -1438,6 +1438,28 @@ def test_products_with_room_for_no_places_run_without_them(bits, rows, cols, z):
     assert e.value.status == B.ENTRO_ERR_CAPACITY
 
 
+@pytest.mark.parametrize("bits", [8, 4])
+def test_more_products_in_one_launch_than_a_grid_has_rows(bits):
+    # 65537 products of one and two rows (about 70 KB of workspace each)
+    count, cols = 65537, 64
+    rng = np.random.default_rng(bits)
+    encs = [_oracle_encoded(np.clip(np.rint(rng.standard_normal(r * cols) * 2) + 7, 0, 15).astype(np.uint8), bits, 64, r, cols, 0.25, 7) for r in (1, 2)]
+    x = torch.from_numpy(synth.make_x_bf16(6, 0, cols).view(np.int16)).to(DEV).view(torch.bfloat16)
+    y = torch.zeros(count, 4, dtype=torch.float32, device=DEV)
+    dts, step = [E.to_device(e, DEV) for e in encs], y.element_size() * 4
+    kinds = [d.ctensor(y, x) for d in dts]
+    ts = [B.CTensor.from_buffer_copy(kinds[i & 1]) for i in range(count)]
+    for i, t in enumerate(ts):
+        t.out = y.data_ptr() + step * i
+    plan, ws = _plan_of(ts, E.ENTRO_F32)
+    E.entro_plan_run(plan)
+    y = y.cpu().numpy()
+    for k, e in enumerate(encs):
+        q = oracle.decode(e.stream, e.offsets, e.n, e.chunk_symbols, e.cb.lengths(), e.cb.codes())
+        y_ref, _ = oracle.gemv(q, e.rows, cols, 0.25, 7, synth.make_x_bf16(6, 0, cols))
+        assert np.abs(y[k::2, :e.rows] - y_ref).max() <= 1e-5 * max(1.0, np.abs(y_ref).max()) and not y[k::2, e.rows:].any()
+
+
 def test_products_that_lanes_of_noted_places_do_not_take():
     """Zero-points that the tables' values cannot hold, codes too long for a lane's stream, shapes that do not cut into lanes, mixed
     alphabets and single runs go the ways they went."""
