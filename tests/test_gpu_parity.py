@@ -950,7 +950,7 @@ def test_staged_plan_init_does_not_block_and_batch_calls_return_before_their_ker
     first = [o.clone() for o in outs]
     for o in outs:
         o.zero_()
-    # the batch form waits once for the stream (the table upload), then enqueues: it is back before its kernel ends
+    # the batch form waits once for the stream (so large a table is copied), then enqueues: it is back before its kernel ends
     done = torch.cuda.Event()
     E.entro_decode_dequant_batch(ts, E.ENTRO_BF16, ws)
     done.record()
@@ -962,6 +962,59 @@ def test_staged_plan_init_does_not_block_and_batch_calls_return_before_their_ker
     q = oracle.decode(e.stream, e.offsets, e.n, e.chunk_symbols, e.cb.lengths(), e.cb.codes())
     assert _bf16_ulp_diff(outs[3].view(torch.int16).cpu().numpy().view(np.uint16),
                           oracle.dequant_bf16(q, e.qp.scale, e.qp.zero_point)).max() <= 1
+
+
+@pytest.mark.parametrize("chunk,sub", [(4096, 256), (4096, 0), (1024, 512)])
+@pytest.mark.parametrize("count", [2, 5, 11, 12, 13, 14, 24, 25, 26, 27, 40])
+def test_batch_calls_whose_table_travels_as_arguments_and_is_copied(count, chunk, sub):
+    """Tensors of unequal sizes, a lane per piece or segment each (codes that do not fall into step), so many that their table takes
+    one to three kernels' arguments or more, where it is copied: to the last bit what a prepared launch gives, whose table is copied
+    always.  A call whose table travels does not wait for what is in front of it."""
+    rng, dts, syms = np.random.default_rng(count), [], []
+    shapes = [(301, 4096), (97, 1000), (9, 14336), (1, 64), (40, 1001), (700, 72)]
+    for i in range(count):
+        rows, cols = shapes[i % 6]
+        rows += int(rng.integers(0, 5))
+        enc, sym = _out_of_step(8 if i % 5 else 4, chunk, rows * cols, rows, cols, sub)
+        dts.append(E.to_device(enc, DEV))
+        syms.append(sym)
+    small = [i for i, d in enumerate(dts) if d.enc.cols % 8 == 0]          # (activations of whole pieces of eight)
+    xs = [torch.from_numpy(synth.make_x_bf16(1, i, d.enc.cols).view(np.int16)).to(DEV).view(torch.bfloat16) for i, d in enumerate(dts)]
+    filler = torch.empty(1 << 30, dtype=torch.uint8, device=DEV)
+    for op, out, dtype in ((E.ENTRO_OP_DECODE, E.ENTRO_U8, torch.uint8), (E.ENTRO_OP_DEQUANT, E.ENTRO_BF16, torch.bfloat16),
+                           (E.ENTRO_OP_DEQUANT, E.ENTRO_F32, torch.float32), (E.ENTRO_OP_GEMV, E.ENTRO_F32, torch.float32)):
+        gemv, runs = op == E.ENTRO_OP_GEMV, []
+        which = small if gemv else range(count)
+        call = {E.ENTRO_OP_DECODE: E.entro_decode_batch, E.ENTRO_OP_DEQUANT: E.entro_decode_dequant_batch, E.ENTRO_OP_GEMV: E.entro_decode_gemv_batch}[op]
+        for prepared in (False, True):
+            outs = [torch.full((dts[i].enc.rows if gemv else syms[i].size,), 77, dtype=dtype, device=DEV) for i in which]
+            ts = [dts[i].ctensor(o, xs[i] if gemv else None) for i, o in zip(which, outs)]
+            ws = torch.zeros(E.entro_workspace_bytes(_without_places(ts) if gemv else ts, op), dtype=torch.uint8, device=DEV)
+            if prepared:
+                plan = E.entro_plan_init(ts, op, out, ws)
+                assert plan.shared_wave_bytes == 0 and plan.wide_tables != 2
+                E.entro_plan_run(plan)
+            else:
+                call(ts, out, ws)
+                torch.cuda.synchronize()
+                for o in outs:
+                    o.fill_(78)
+                for _ in range(8):
+                    filler.fill_(1)
+                busy = torch.cuda.Event()
+                busy.record()
+                call(ts, out, ws)
+                assert count > 5 or not busy.query(), "waited for the stream"
+            runs.append(outs)
+        for a, b, i in zip(*runs, which):
+            assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+            if not gemv:
+                ref = syms[i] if op == E.ENTRO_OP_DECODE else (oracle.dequant_f32 if out == E.ENTRO_F32 else oracle.dequant_bf16)(syms[i], 0.25, 7)
+                got = a.cpu().numpy() if out != E.ENTRO_BF16 else a.view(torch.int16).cpu().numpy().view(np.uint16)
+                assert np.array_equal(got, ref)
+            else:
+                y_ref, _ = oracle.gemv(syms[i], dts[i].enc.rows, dts[i].enc.cols, 0.25, 7, synth.make_x_bf16(1, i, dts[i].enc.cols))
+                _assert_gemv_close(a.cpu().numpy().astype(np.float64), y_ref)
 
 
 def test_many_tensors_in_one_launch():
