@@ -2676,7 +2676,7 @@ __global__ __launch_bounds__(1024) void k_fine_pairs(const DevTensor *__restrict
 // What a wavefront holds of a unit before it decodes it.
 struct FineUnit {
     uint32_t places;        // where the lane's two chains begin, in bits from the unit's first: 16 bits each
-    uint32_t next;          // where the next lane's first chain begins (of the last lane: unused)
+    uint32_t next;          // where the next lane's first chain begins (of the last lane: its own)
     uint32_t q;             // where the lane's first chain begins in its column
     uint32_t sub;           // an entry of the entry-point table (lanes 0..14)
     uint64_t offset;        // of the segment
@@ -2686,7 +2686,7 @@ struct FineUnit {
 // Ask for what says where the unit's codes are ...
 __device__ __forceinline__ void fine_ask(const DevTensor &t, uint32_t unit, FineUnit &u) {
     const uint32_t lane = threadIdx.x & 63u, fl = unit * 64u + lane;
-    u.places = ((global_u32_ptr)t.fine_index)[fl < t.fine_n ? fl : unit * 64u];
+    u.places = ((global_u32_ptr)t.fine_index)[fl < t.fine_n ? fl : t.fine_n - 1u];
     const uint32_t k = unit * t.fine_pieces, sh = t.sub_shift, c = k >> sh, before = k - (c << sh);
     u.offset = ((global_u64_ptr)t.offsets)[c];
     u.sub = 0;
@@ -3123,52 +3123,51 @@ __global__ __launch_bounds__(64 * kFineWaves) void k_fine(const DevTensor *__res
             const uint32_t a = u.places & 0xffffu, b = u.places >> 16, next = u.next;
             const uint32_t q0 = u.q;
             fine_ask(t, unit_next, u);
-            // the last lane of the tensor or the unit has none behind it; do the others' codes fit their columns, as far as noted?
-            const uint32_t fl = unit * 64u + lane;
-            const bool last_lane = lane == 63u || fl + 1u >= t.fine_n;
-            const uint32_t bits = (next - a) & 0xffffu;
-            bool again = __builtin_amdgcn_ballot_w64(!last_lane && q0 + bits > kFineEnd - Tables32::stale) != 0, walk = false;
+            // Lanes whose codes do not fit their columns, as far as noted (which says nothing of the last lane): the unit is left to
+            // fine_again.  By no steps rather than a branch around all of them, which made a step over 32 layers 1 % longer.
+            const uint32_t q_mid = q0 + (b - a), q_next = q0 + (next - a);
+            const bool longer = __builtin_amdgcn_ballot_w64(q_next > kFineEnd - Tables32::stale) != 0;
+            const uint32_t steps_here = longer ? 0u : steps;
+            uint32_t qa = q0, qb = q_mid, end_b = qb;
             float acc = 0.0f;
-            if (__builtin_expect(!again, 1)) {
-                uint32_t qa = q0, qb = q0 + (b - a), end_b = qb;
 #pragma unroll
-                for (uint32_t s = 0; s < 4; ++s) {
-                    if (s < steps) {
+            for (uint32_t s = 0; s < 4; ++s) {
+                if (s < steps_here) {
 #pragma unroll
-                        for (int h = 0; h < (PAIR ? 1 : 2); ++h) {
-                            FineGroup<PAIR> ga, gb;
-                            fine_groups<PAIR>(col, sm.tb, max_len, zf, qa, qb, ga, gb);
-                            if constexpr (PAIR) {
+                    for (int h = 0; h < (PAIR ? 1 : 2); ++h) {
+                        FineGroup<PAIR> ga, gb;
+                        fine_groups<PAIR>(col, sm.tb, max_len, zf, qa, qb, ga, gb);
+                        if constexpr (PAIR) {
 #pragma unroll
-                                for (int v = 0; v < 4; ++v) {
-                                    acc = dot2(ga.v[v], x[s][v], acc);
-                                    acc = dot2(gb.v[v], x[4 + s][v], acc);
-                                }
-                            } else {
+                            for (int v = 0; v < 4; ++v) {
+                                acc = dot2(ga.v[v], x[s][v], acc);
+                                acc = dot2(gb.v[v], x[4 + s][v], acc);
+                            }
+                        } else {
 #pragma unroll
-                                for (int v = 0; v < 2; ++v) {
-                                    acc = dot2(ga.v[v], x[s][2 * h + v], acc);
-                                    acc = dot2(gb.v[v], x[4 + s][2 * h + v], acc);
-                                }
+                            for (int v = 0; v < 2; ++v) {
+                                acc = dot2(ga.v[v], x[s][2 * h + v], acc);
+                                acc = dot2(gb.v[v], x[4 + s][2 * h + v], acc);
                             }
                         }
-                        end_b = steps + s < pieces ? qb : end_b;
                     }
-                    if (s == 0) fine_load(t, u);
+                    end_b = steps + s < pieces ? qb : end_b;
                 }
-                // every chain ends where the next one begins, and the unit's first begins at its first bit
-                const bool good = qa - q0 == b - a && (last_lane || end_b - q0 == next - a) && end_b <= kFineEnd - Tables32::stale &&
-                                  (lane != 0 || a == 0);
-                const uint64_t bad = __builtin_amdgcn_ballot_w64(fl < t.fine_n && !good);
-                again = bad != 0;
-                walk = (bad & __builtin_amdgcn_ballot_w64(!last_lane)) != 0;      // (a last lane's column may be too short)
+                if (s == 0) fine_load(t, u);
             }
-            if (__builtin_expect(again, 0)) {
+            // every chain ends where the next one begins, and the unit's first begins at its first bit
+            const uint32_t fl = unit * 64u + lane;
+            const bool last_lane = lane == 63u || fl + 1u >= t.fine_n;
+            // (no short circuits, which are branches; a longer unit's qa stays q0, and not all of its lanes' chains are empty)
+            const bool end_good = last_lane ? end_b <= kFineEnd - Tables32::stale : end_b == q_next;
+            const bool good = (qa == q_mid) & end_good & ((lane != 0) | (a == 0));
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64((fl < t.fine_n) & !good) != 0, 0)) {
+                bool walk = !longer && __builtin_amdgcn_ballot_w64(fl < t.fine_n && !good && !last_lane) != 0;
                 const uint64_t base = seg_start(t, unit * t.fine_pieces);
                 const uint64_t anew = __builtin_amdgcn_ballot_w64(!last_lane && next < a);
                 uint32_t from_a = a + (__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(anew >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(anew), 0u)) << 16);
                 uint32_t from_b = from_a + ((b - a) & 0xffffu);
-                const uint32_t next_a = from_a + bits;
+                const uint32_t next_a = from_a + ((next - a) & 0xffffu);
 #pragma unroll 1
                 for (;; walk = true) {
                     if (walk) {
