@@ -22,11 +22,12 @@
  *   - Device entry points enqueue their work on `hip_stream` (a hipStream_t
  *     passed as void*, NULL = the default stream) and return without waiting
  *     for it.  Two exceptions wait for the stream ONCE, before their kernel is
- *     enqueued, because they upload a table from memory that dies with the
- *     call: entro_plan_init, and the three *_batch forms, which call it.  The
- *     form for callers that must not block is entro_plan_init_staged (the
- *     table goes through pinned memory of the caller's) followed by
- *     entro_plan_run.
+ *     enqueued, because they copy a table from memory that dies with the
+ *     call: entro_plan_init, and the three *_batch forms where their table is
+ *     larger than about 11 KB (smaller ones travel as kernel arguments).  The
+ *     form for callers that must not block, whatever the size, is
+ *     entro_plan_init_staged (the table goes through pinned memory of the
+ *     caller's) followed by entro_plan_run.
  *   - Every failure is a return code; nothing is thrown, nothing aborts.  All
  *     argument checks happen on the host before any launch.  A corrupt stream
  *     can decode to wrong symbols but is never read outside
@@ -282,7 +283,9 @@ uint64_t entro_workspace_bytes(const entro_tensor *ts, uint32_t count, entro_op 
  * streams once and notes where the codes of every 64 symbols or so begin, so that the launches'
  * lanes need not start at segments or pieces; every launch checks what was noted against the
  * tensors' own tables, so buffers may be filled or given other contents after this call, but the next
- * launch is then slower (it notes the places anew as it goes).
+ * launch is then slower (it notes the places anew as it goes: 1.5 to 2.5 times as long as without places
+ * for tensors with entry points, above 4 times without).  For contents that change with every launch, leave the room
+ * for places out of the workspace, see entro_workspace_bytes.
  * The work list is cut for the current device (its number of compute units
  * decides how many units a work item holds and, for tensors with entry points
  * inside their segments, how many pieces a lane takes: as coarse as still gives
@@ -312,9 +315,11 @@ entro_status entro_plan_init_staged(entro_plan *plan, const entro_tensor *ts, ui
 entro_status entro_plan_run(const entro_plan *plan, void *hip_stream);
 
 /* Fig. 3's decode, the inverse of Eq. 1 and the product of "Latency Reduction from Huffman
- * Coding" over many tensors: entro_plan_init followed by entro_plan_run.  They return without waiting for
- * their kernel; calls whose table is larger than about 11 KB (a dozen tensors, or more in larger
- * work lists) wait for the stream once before it is enqueued. */
+ * Coding" over many tensors: prepared, as entro_plan_init does, and run in one call, products without
+ * places (so they sum in the order of a plan without them).  They return without waiting for their kernel;
+ * calls whose table is larger than about 11 KB (some 25 tensors; half as many with entry points inside
+ * their segments, which are described twice; fewer where the work list travels, too) wait for the stream
+ * once before it is enqueued. */
 entro_status entro_decode_batch(const entro_tensor *ts, uint32_t count, entro_dtype out_type,
                                 void *workspace, uint64_t workspace_bytes, void *hip_stream);
 entro_status entro_decode_dequant_batch(const entro_tensor *ts, uint32_t count, entro_dtype out_type,

@@ -290,7 +290,7 @@ __device__ __forceinline__ void copy_tables(void *dst, const void *src) {
 // code lengths by the whole workgroup of WG >= 256 lanes (four waves hold the
 // symbols).  `wcnt` is scratch of 4 * 33 words.
 // A small launch waits for this, so little in it is serial: one wavefront turns the counts
-// into the canonical tables with its lanes as the lengths (33 steps in scalar registers), and
+// into the canonical tables with its lanes as the lengths (running sums by DPP), and
 // the first level is resolved for kSmallBits index bits only, copied to the indexes that end in
 // the same bits, and searched bit by bit for the few indexes that start with a longer code.
 // Pair tables resolve every index, with two reads of the small table of single codes.
@@ -2553,8 +2553,10 @@ __global__ __launch_bounds__(kFixWG) void k_fix_batch(const DevTensor *__restric
 //   Measured, a lane per piece -> now, us a launch.  8 bits, 3.5 bits a symbol: 25 M symbols in rows of 4096 36 -> 22, 16.8 M 31 -> 16,
 // 117 M 74 -> 46, 58.7 M in rows of 14336 44 and 5 for the second stage -> 34; the step over 32 layers 6098 -> 3881.  4 bits, 1.55
 // bits a symbol: 9.4 M symbols in rows of 3072, shared by k_shared_batch before, 28 -> 10; the step over 32 layers 4035 -> 1863.
-//   What bounds a large launch now: the LDS pipe is busy in 0.6 of the cycles (over half of that bank conflicts of the lookups) and
-// the vector ALUs in 0.55; a small one: about 6 us of cold reads one behind the other (item, description, places, stream) and what
+// Rows that begin and end inside units, second stage included (kFineParts), 8 bits: 60.5 M symbols in rows of 5504 73 -> 35, 41.5 M of
+// 13824 55 -> 28, 0.86 M of 2880 31 -> 15; 4 bits: 60.5 M of 5504 43 -> 22, 0.86 M of 2880 19 -> 10; no shape was found that loses.
+//   What bounds a large launch now: the LDS pipe is busy in 0.68 of the cycles (over half of that bank conflicts of the lookups) and
+// the vector ALUs in 0.62; a small one: about 6 us of cold reads one behind the other (item, description, places, stream) and what
 // a launch takes by itself.
 constexpr uint32_t kFineWaves = 16;
 constexpr uint32_t kFineData = 16;                       // dwords of stream that a lane holds
@@ -3648,7 +3650,8 @@ entro_status launch_single(const entro_tensor *t, entro_op op, entro_dtype d, fl
             }
         }
         if constexpr (short_ring(M)) {
-            // up to a wavefront for each compute unit
+            // Up to a wavefront for each compute unit, which waits for its own chain alone.  Lookups in the chain -> none, pieces of 256
+            // to fp32, us a call: 1 wavefront 26.0 -> 25.5, 64 27.0 -> 26.3, 256 28.4 -> 27.7; 512 30.0 -> 30.3 (to bf16 27.1 -> 28.1).
             if ((dt.n_chunks + kUnit - 1u) / kUnit <= slots && flat_code(t->cb, &dt)) {
                 hipLaunchKernelGGL((k_single<M, false, true>), dim3(grid), dim3(wg), 0, s, dt, static_cast<uint32_t>(wg_units));
                 return;
