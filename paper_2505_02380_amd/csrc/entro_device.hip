@@ -2900,7 +2900,7 @@ __device__ __forceinline__ uint32_t fine_skip(lds_v32 col, const Tables32 &tb, u
 // first half of a lane's column; places lie in the second.
 //   The lanes that are left over walk `ahead` - 1 units more, `stride` apart, that this workgroup has yet to come to, and note their
 // places: buffers that have been given other contents have them all over.  A launch behind other contents, symbol by symbol from
-// memory -> now: 16.8 M symbols of 3.6 bits in pieces of 256 121 -> 61 us, 58.7 M 367 -> 102, 16.8 M in pieces of 4096 934 -> 391.
+// memory -> now: 16.8 M symbols of 3.6 bits in pieces of 256 121 -> 61 us, 58.7 M 367 -> 102.
 template <bool PAIR>
 __device__ __forceinline__ void fine_walk(const DevTensor &t, const Tables32 &tb, lds_v32 col, uint32_t max_len, uint32_t unit, uint32_t stride,
                                           uint32_t ahead, uint32_t &a, uint32_t &b) {
@@ -2938,6 +2938,116 @@ __device__ __forceinline__ void fine_walk(const DevTensor &t, const Tables32 &tb
     a = place[lane];
     b = place[64u + lane];
     wave_sync_lds();
+}
+
+// Code by code through the stream from bit `start` behind `base` on, four of them a step, until every lane is at `limit` or behind:
+// each(where a code begins, its length).  (A lane that is there goes on until the others are.)
+template <bool PAIR, class F>
+__device__ __forceinline__ void fine_codes(const DevTensor &t, const Tables32 &tb, lds_v32 col, uint32_t max_len, uint64_t base, uint32_t start,
+                                           uint32_t limit, F each) {
+    uint32_t at = start, q = 0;
+    bool fill = true;
+#pragma unroll 1
+    while (__builtin_amdgcn_ballot_w64(at < limit) != 0) {
+        if (fill || __builtin_amdgcn_ballot_w64(fine_short<PAIR>(q, max_len)) != 0) q = fine_fill<kFineHalf / 4u>(t, col + 64u, base + at);
+        fill = false;
+        uint64_t w = fine_window(col, q);
+        uint32_t len[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t v = static_cast<uint32_t>(w >> Tables32::stale);
+            len[i] = entry_len(PAIR ? tb.lut2[v & ((1u << kSingleBits) - 1u)] : tb.lut[v & kL1Mask]);
+            w >>= len[i];
+        }
+        if (__builtin_expect(len[3] == 0, 0)) {          // (a code that the first level does not hold ends the others' advance)
+            uint32_t to = q;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                len[i] = entry_len(fine_single<PAIR>(tb, static_cast<uint32_t>(fine_window(col, to) >> Tables32::stale), max_len));
+                to += len[i];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            each(at, len[i]);
+            at += len[i];
+            q += len[i];
+        }
+    }
+}
+
+// The same places, found with all lanes where a piece is many lanes' symbols: as in k_shared every lane counts the codes that begin
+// in an equal stretch of its piece's bits, from a guessed one; a lane whose neighbour ended elsewhere than it began counts again
+// from there, until all agree.  Then every lane knows which symbols are its own, and notes the places among them.  False (and
+// nothing is noted) where lanes do not agree soon, or the counts are not the pieces'.
+//   A launch behind other contents, fine_walk -> this, 8 bits: 16.8 M symbols in pieces of 4096 397 -> 71 us, of 1024 120 -> 65, of 512
+// 79 -> 68, 58.7 M in pieces of 4096 747 -> 192; 4 bits: 9.4 M in pieces of 4096 210 -> 59, of 1024 72 -> 46, 25 M of 512 49 -> 92.
+constexpr int kFineRounds = 6;
+constexpr uint32_t kFineFind = 1024;                     // symbols of such a piece, and more
+template <bool PAIR>
+__device__ __forceinline__ bool fine_find(const DevTensor &t, const Tables32 &tb, lds_v32 col, uint32_t max_len, uint32_t unit, uint64_t base,
+                                          uint32_t &a, uint32_t &b) {
+    const uint32_t lane = threadIdx.x & 63u, P = t.chunk_symbols, L = t.fine_len, per = t.fine_pieces, of_piece = 64u / per;
+    const uint32_t piece = lane / of_piece, j = lane - piece * of_piece, k = unit * per + piece;
+    const bool live = piece < per && k < t.n_chunks;
+    uint32_t start = 0, limit = 0, nsym = 0;
+    bool fits = true;
+    if (live) {
+        const uint64_t left = t.n - static_cast<uint64_t>(k) * P, from = seg_start(t, k) - base;
+        // (behind the last piece there is no entry point to read)
+        const uint64_t to = (k + 1u < t.n_chunks ? seg_start(t, k + 1u) : ((global_u64_ptr)t.offsets)[(k >> t.sub_shift) + 1u]) - base;
+        nsym = left < P ? static_cast<uint32_t>(left) : P;
+        fits = to >= from && to - from <= 32u * nsym && from <= 32u * 64u * L;
+        const uint32_t bits = fits ? static_cast<uint32_t>(to - from) : 0u;
+        start = static_cast<uint32_t>(from) + bits * j / of_piece;
+        limit = static_cast<uint32_t>(from) + bits * (j + 1u) / of_piece;
+    }
+    if (__builtin_amdgcn_ballot_w64(!fits) != 0) return false;
+    uint32_t count = 0;
+#pragma unroll 1
+    for (int round = 0;; ++round) {
+        uint32_t end = start;
+        count = 0;
+        fine_codes<PAIR>(t, tb, col, max_len, base, start, limit, [&](uint32_t at, uint32_t len) __attribute__((always_inline)) {
+            count += at < limit ? 1u : 0u;
+            end = at < limit ? at + len : end;
+        });
+        const uint32_t before = __shfl_up(end, 1, 64);
+        const bool moves = live && j != 0 && before != start;
+        if (__builtin_amdgcn_ballot_w64(moves) == 0) break;
+        if (round == kFineRounds) return false;
+        start = moves ? before : start;
+    }
+    uint32_t upto = count;
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) {
+        const uint32_t y = __shfl_up(upto, m, 64);
+        upto += lane >= static_cast<uint32_t>(m) ? y : 0u;
+    }
+    const uint32_t first = live ? piece * of_piece : lane, before = __shfl(upto - count, first, 64);
+    const bool whole = !live || j + 1u != of_piece || upto - before == nsym;
+    if (__builtin_amdgcn_ballot_w64(!whole) != 0) return false;
+    const uint32_t symbol = piece * P + upto - count - before;
+    const lds_v32 place = col - lane + (kFineHalf + 1u) * 64u;
+    uint16_t *index = reinterpret_cast<uint16_t *>(t.fine_index) + 128u * static_cast<uint64_t>(unit);
+    uint32_t to = symbol / L, i = symbol - to * L, mine = count;     // (no more than were counted, whatever is read now)
+    wave_sync_lds();
+    fine_codes<PAIR>(t, tb, col, max_len, base, start, limit, [&](uint32_t at, uint32_t) __attribute__((always_inline)) {
+        if (mine != 0 && (i == 0 || i == t.fine_first)) {
+            const uint32_t chain = i ? 1u : 0u;
+            place[chain * 64u + to] = at;
+            index[2u * to + chain] = fine_note(at);
+        }
+        mine -= mine != 0 ? 1u : 0u;
+        ++i;
+        to += i == L ? 1u : 0u;
+        i = i == L ? 0u : i;
+    });
+    wave_sync_lds();
+    a = place[lane];
+    b = place[64u + lane];
+    wave_sync_lds();
+    return true;
 }
 
 // The sum of a lane whose chains begin a and b bits behind the unit's first, whatever their length: half of its column for either
@@ -3174,8 +3284,9 @@ __global__ __launch_bounds__(64 * kFineWaves) void k_fine(const DevTensor *__res
                 for (;; walk = true) {
                     if (walk) {
                         const bool one = t.fine_units == 1u;
-                        fine_walk<PAIR>(t, sm.tb, col, max_len, unit, one ? kFineWaves : 1u,
-                                        one ? (n_quanta - g + kFineWaves - 1u) / kFineWaves : t.fine_units - of_row, from_a, from_b);
+                        if (t.chunk_symbols < kFineFind || !fine_find<PAIR>(t, sm.tb, col, max_len, unit, base, from_a, from_b))
+                            fine_walk<PAIR>(t, sm.tb, col, max_len, unit, one ? kFineWaves : 1u,
+                                            one ? (n_quanta - g + kFineWaves - 1u) / kFineWaves : t.fine_units - of_row, from_a, from_b);
                     }
                     uint32_t end_a = from_a, end_b = from_b;
                     acc = fine_again<PAIR>(t, sm.tb, col, max_len, zf, base, end_a, end_b,

@@ -1297,6 +1297,9 @@ NOTED_FORMS = [
     (4, 1024, 64, 37, 192, 5),           # rows that begin inside units and end in them, too
     (8, 1024, 256, 40, 1056, 90),        # lanes of 48 symbols, partial sums
     (4, 2048, 512, 11, 2080, -1),        # lanes of 32 symbols, partial sums, a last piece that is shorter
+    (8, 1024, 0, 19, 3072, 90),          # three pieces to a unit, whose lanes share a piece's search by 21
+    (4, 2048, 0, 37, 1024, 6),           # two pieces to a unit
+    (4, 4096, 0, 5, 1600, 2),            # one piece to a unit, the last one of 3904 symbols
 ]
 
 
@@ -1441,7 +1444,16 @@ def test_products_under_codes_that_do_not_fall_into_step(bits, chunk, sub, rows,
     y = torch.zeros(rows, dtype=torch.float32, device=DEV)
     plans = [_plan_of([dt.ctensor(y, xd)], E.ENTRO_F32, places) for places in (True, False)]
     us = _times_us([lambda p=p: E.entro_plan_run(p[0]) for p in plans], 10)
-    E.entro_plan_run(plans[0][0])
+    sym, runs = np.roll(sym, 3), []                          # and other contents, where no search of starts would end soon
+    stream, off = E.entro_encode(sym, enc.cb, chunk)
+    other = B.EncodedTensor(stream, off, enc.n, chunk, enc.cb, enc.qp, rows, cols)
+    if sub:
+        other.sub_symbols, other.sub_bits = sub, E.entro_sub_index(sym, enc.cb, chunk, sub)
+    _refill(dt, other)
+    for _ in range(2):
+        E.entro_plan_run(plans[0][0])
+        runs.append(y.clone())
+    assert torch.equal(runs[0], runs[1])
     y_ref, _ = oracle.gemv(sym, rows, cols, 0.25, 7, x)
     terms = np.abs((sym.reshape(rows, cols).astype(np.float64) - 7) * 0.25) @ np.abs((x.astype(np.uint32) << 16).view(np.float32).astype(np.float64))
     assert np.all(np.abs(y.double().cpu().numpy() - y_ref) <= (cols + 2) * 2.0 ** -24 * terms)
