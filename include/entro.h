@@ -283,8 +283,9 @@ uint64_t entro_workspace_bytes(const entro_tensor *ts, uint32_t count, entro_op 
  * streams once and notes where the codes of every 64 symbols or so begin, so that the launches'
  * lanes need not start at segments or pieces; every launch checks what was noted against the
  * tensors' own tables, so buffers may be filled or given other contents after this call, but the next
- * launch is then slower (it notes the places anew as it goes: up to three times as long as without places).  For contents that change with every launch, leave the room
- * for places out of the workspace, see entro_workspace_bytes.
+ * launch is then slower (it notes the places anew as it goes: up to three times as long as without
+ * places).  For contents that change with every launch, leave the room for places out of the workspace,
+ * see entro_workspace_bytes.
  * The work list is cut for the current device (its number of compute units
  * decides how many units a work item holds and, for tensors with entry points
  * inside their segments, how many pieces a lane takes: as coarse as still gives
